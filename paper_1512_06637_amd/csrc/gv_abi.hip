@@ -17,6 +17,7 @@
 
 #include "../../include/gvgeom.h"
 #include "gv_baskets.h"
+#include "gv_inst.h"
 #include "gv_lane.h"
 #include "gv_probe.h"
 
@@ -1087,8 +1088,7 @@ extern "C" int basket_step(gv_geom* g, int64_t n, const double* x, const double*
   GV_TRY(check_i32(fn, "out_next_pv", out_next_pv));
   GV_TRY(check_i32(fn, "out_flags", out_flags, true));
   DeviceGuard dgd(g->device);
-  const auto kern = g->has_bool ? (precision == GV_FP64 ? k_step_nav<false, true> : k_step_nav<true, true>)
-                                : (precision == GV_FP64 ? k_step_nav<false, false> : k_step_nav<true, false>);
+  const auto kern = step_nav_kernel(g->has_bool, precision == GV_FP32_REFINE);
   hipLaunchKernelGGL(kern, dim3(lane_shape(g, n).grid), dim3(lane_shape(g, n).block), 0,
                      (hipStream_t)stream, g->dg, n, x, y, z, dx, dy, dz, pv, pstep, out_step, out_next_pv, out_flags);
   return launched(fn);
@@ -1247,28 +1247,6 @@ bool staging_ready(const gv_geom* g, int64_t steps) {
   return g->ob && g->ob_cap >= g->ws_tracks && g->ob_steps >= steps;
 }
 
-// The per-step kernel for this call: composites or not, FP32 screens or not,
-// physics-limited or not, the work-counting instance while counters are
-// asked for (geometries without composites), and the tuned register budget
-// of the navigation step (3 or 4 waves per SIMD).
-using StepKernel = void (*)(DevGeom, int, int, int, const int*, const int*, TRec*, const int*, int*, uint32_t*, int*,
-                            TCtl, int32_t*, double*, int32_t*, uint32_t*, const int*, double*, int*, int64_t,
-                            PhysArgs, int8_t*, int8_t*);
-StepKernel select_step_kernel(const gv_geom* g, bool fp32, bool phys) {
-  if (g->has_bool) {
-    if (phys) return fp32 ? k_bt_step<true, true, true, false, 3> : k_bt_step<false, true, true, false, 3>;
-    return fp32 ? k_bt_step<true, false, true, false, 4> : k_bt_step<false, false, true, false, 4>;
-  }
-  if (g->prof_work) {
-    if (phys) return fp32 ? k_bt_step<true, true, false, true, 3> : k_bt_step<false, true, false, true, 3>;
-    return fp32 ? k_bt_step<true, false, false, true, 4> : k_bt_step<false, false, false, true, 4>;
-  }
-  if (phys) return fp32 ? k_bt_step<true, true, false, false, 3> : k_bt_step<false, true, false, false, 3>;
-  if (g->tune.step_waves == 3)
-    return fp32 ? k_bt_step<true, false, false, false, 3> : k_bt_step<false, false, false, false, 3>;
-  return fp32 ? k_bt_step<true, false, false, false, 4> : k_bt_step<false, false, false, false, 4>;
-}
-
 constexpr int64_t kBasketMin = 8192;  // the basket form needs at least this many tracks
 
 unsigned stream_grid(int64_t n) {
@@ -1317,7 +1295,7 @@ int basket_transport(gv_geom* g, int64_t n, const double* x, const double* y, co
   double* ob_step = staged ? g->ob_step : nullptr;
   int* ob_pv = staged ? g->ob_pv : nullptr;
   int8_t* ob_proc = staged && phys && out_proc ? g->ob_proc : nullptr;
-  const auto step_kernel = select_step_kernel(g, fp32, phys);
+  const auto step = step_kernel(g->has_bool, g->prof_work, fp32, phys, g->tune.step_waves == 3);
   const unsigned step_grid = step_grid_for(g, n);
   const size_t lds_sc = 8 * (size_t)nl + 4;
   // Every step up to max_steps is enqueued at once and the call returns: a
@@ -1340,7 +1318,7 @@ int basket_transport(gv_geom* g, int64_t n, const double* x, const double* y, co
       g->prof_used += 2;
       (void)hipEventRecord(pe[0], s);
     }
-    hipLaunchKernelGGL(step_kernel, dim3(step_grid), dim3(kBlock), lds_step, s, g->dg, k, max_steps, cb,
+    hipLaunchKernelGGL(step, dim3(step_grid), dim3(kBlock), lds_step, s, g->dg, k, max_steps, cb,
                        (const int*)g->idx[c], len_cur, g->rec, (const int*)C.cnt[k0], g->nxt_lv, g->nxt_pos,
                        C.cnt[k1], C, out_pv, out_step, out_nsteps, out_flags, (const int*)g->slot_id, ob_step, ob_pv,
                        g->ob_cap, P, ob_proc, out_proc);
@@ -1408,29 +1386,6 @@ int ensure_lane_workspace(gv_geom* g, int64_t n) {
   return GV_OK;
 }
 
-using LaneKernel = void (*)(DevGeom, int64_t, const double*, const double*, const double*, const double*,
-                            const double*, const double*, const int32_t*, const int32_t*, uint32_t*, int, int32_t*,
-                            double*, int32_t*, uint32_t*, PhysArgs, int8_t*);
-
-// The lane-transport instance: composites or not, FP32 screens or not,
-// physics-limited or not, and the register budget (3 or 4 waves per SIMD)
-// and output staging.  Geometries with composites run one shape per
-// precision and physics.
-template <bool F32, bool PHYS>
-LaneKernel lane_kernel_for(int waves, bool stage, bool cls) {
-  if (cls) return waves == 3 ? k_lane_transport<F32, PHYS, false, 3, 8, true> : k_lane_transport<F32, PHYS, false, 4, 8, true>;
-  if (waves == 3) return stage ? k_lane_transport<F32, PHYS, false, 3, 8> : k_lane_transport<F32, PHYS, false, 3, 0>;
-  return stage ? k_lane_transport<F32, PHYS, false, 4, 8> : k_lane_transport<F32, PHYS, false, 4, 0>;
-}
-
-LaneKernel select_lane_kernel(bool has_bool, bool fp32, bool phys, int waves, bool stage, bool cls) {
-  if (has_bool)
-    return fp32 ? (phys ? k_lane_transport<true, true, true, 3, 0> : k_lane_transport<true, false, true, 3, 0>)
-                : (phys ? k_lane_transport<false, true, true, 3, 0> : k_lane_transport<false, false, true, 3, 0>);
-  if (phys) return fp32 ? lane_kernel_for<true, true>(waves, stage, cls) : lane_kernel_for<false, true>(waves, stage, cls);
-  return fp32 ? lane_kernel_for<true, false>(waves, stage, cls) : lane_kernel_for<false, false>(waves, stage, cls);
-}
-
 // Workgroups of 256 threads a CU holds at once for kernel k (cached per
 // kernel in a fixed table: nothing is allocated here).
 int resident_blocks(gv_geom* g, const void* k) {
@@ -1478,7 +1433,7 @@ int lane_transport(gv_geom* g, const LaneCtl& L, int64_t n, const double* x, con
   const bool stage = g->tune.lane_stage ? g->tune.lane_stage == 2 : true;
   // per-class scheduling by default (2.66 against 2.99 ms for navigation,
   // 7.6 against 9.5 ms physics-limited, on the detector workload)
-  const LaneKernel k = select_lane_kernel(g->has_bool, fp32, phys, waves, stage, g->tune.lane_sched != 1);
+  const LaneKernel k = lane_kernel(g->has_bool, fp32, phys, waves, stage, g->tune.lane_sched != 1);
   int64_t grid = g->tune.lane_grid > 0 ? g->tune.lane_grid
                                        : (int64_t)resident_blocks(g, reinterpret_cast<const void*>(k)) * g->n_cu;
   grid = std::max<int64_t>(1, std::min<int64_t>(grid, (n + 255) / 256));

@@ -124,7 +124,7 @@ __device__ __forceinline__ void stage_counts(const int* __restrict__ src, int n,
 }
 
 // Clears the control arrays at the start of a transport.
-__global__ void k_bt_clear(TCtl C, int nlv) {
+static __global__ void k_bt_clear(TCtl C, int nlv) {
   for (int64_t i = gtid(); i < nlv; i += gstride()) {
     for (int s = 0; s < 3; ++s) {
       C.cnt[s][i] = 0;
@@ -201,7 +201,7 @@ __global__ void k_bt_init(DevGeom G, int64_t n, const double* __restrict__ x, co
 // records and staged outputs are read and written in contiguous runs.  Slot s
 // takes track perm[s]: its record, slot_id[s] = track id, and entry s of the
 // first list.  Also stores the number of live tracks.
-__global__ void k_bt_place(const int* __restrict__ perm, const double* __restrict__ x, const double* __restrict__ y,
+static __global__ void k_bt_place(const int* __restrict__ perm, const double* __restrict__ x, const double* __restrict__ y,
                            const double* __restrict__ z, const double* __restrict__ dx,
                            const double* __restrict__ dy, const double* __restrict__ dz,
                            const int32_t* __restrict__ out_pv, int max_steps, int cb, int nb, TRec* __restrict__ rec,
@@ -321,7 +321,7 @@ __device__ __forceinline__ int wave_lds_reserve(int v, bool on, int* cnt) {
 // in a second pass, so a workgroup's entries keep their order in each bucket.
 // Workgroup 0 clears cnt_clear/cur_clear (nullable).  Needs 12 * nb + 4 bytes
 // of dynamic LDS.
-__global__ void __launch_bounds__(1024) k_bt_reindex(const int* __restrict__ src_idx, const int* __restrict__ cnt_src,
+static __global__ void __launch_bounds__(1024) k_bt_reindex(const int* __restrict__ src_idx, const int* __restrict__ cnt_src,
                                                       int nsrc_bins, int64_t nsrc_fixed, const int* __restrict__ key,
                                                       int gather, int* __restrict__ dst_idx,
                                                       const int* __restrict__ cnt_dst, int* __restrict__ cur_dst,
@@ -390,7 +390,7 @@ __global__ void __launch_bounds__(1024) k_bt_reindex(const int* __restrict__ src
 // reads them before the next transport clears them).  Needs 8 * nb + 4 bytes
 // of dynamic LDS.
 constexpr int kScatterUnroll = 4;
-__global__ void __launch_bounds__(1024) k_bt_scatter(const int* __restrict__ src_idx, const int* __restrict__ len_src,
+static __global__ void __launch_bounds__(1024) k_bt_scatter(const int* __restrict__ src_idx, const int* __restrict__ len_src,
                                                       const int* __restrict__ nxt_lv,
                                                       const uint32_t* __restrict__ nxt_pos,
                                                       const int* __restrict__ seg, const int* __restrict__ cnt_dst,

@@ -1,0 +1,51 @@
+// The large navigation kernels are instantiated in source files of their own
+// (gv_inst_*.hip), so that the library builds in parallel; these functions
+// hand their entry points to the host side in gv_abi.hip.
+#pragma once
+#include "gv_baskets.h"
+#include "gv_lane.h"
+#include "gv_serve_kernel.h"
+
+namespace gv {
+
+using StepKernel = void (*)(DevGeom, int, int, int, const int*, const int*, TRec*, const int*, int*, uint32_t*, int*,
+                            TCtl, int32_t*, double*, int32_t*, uint32_t*, const int*, double*, int*, int64_t,
+                            PhysArgs, int8_t*, int8_t*);
+using LaneKernel = void (*)(DevGeom, int64_t, const double*, const double*, const double*, const double*,
+                            const double*, const double*, const int32_t*, const int32_t*, uint32_t*, int, int32_t*,
+                            double*, int32_t*, uint32_t*, PhysArgs, int8_t*);
+using StepNavKernel = void (*)(DevGeom, int64_t, const double*, const double*, const double*, const double*,
+                               const double*, const double*, const int32_t*, const double*, double*, int32_t*,
+                               uint32_t*);
+using ServeKernel = void (*)(DevGeom, const SDesc*, int, int64_t, const char*, char*);
+
+// The per-step kernel of the basket form: composites or not, the work-counting
+// instance while counters are asked for (geometries without composites), FP32
+// screens or not, physics-limited or not, and the register budget of the
+// navigation step (3 or 4 waves per SIMD).
+StepKernel step_kernel(bool has_bool, bool work, bool fp32, bool phys, bool waves3);
+StepKernel step_kernel_phys(bool has_bool, bool work, bool fp32);
+
+// The lane-transport instance: composites or not, FP32 screens or not,
+// physics-limited or not, the register budget (3 or 4 waves per SIMD), output
+// staging and per-class scheduling.  Geometries with composites run one shape
+// per precision and physics.
+LaneKernel lane_kernel(bool has_bool, bool fp32, bool phys, int waves, bool stage, bool cls);
+LaneKernel lane_kernel_bool(bool fp32, bool phys);
+LaneKernel lane_kernel_nav32(int waves, bool stage, bool cls);
+LaneKernel lane_kernel_phys64(int waves, bool stage, bool cls);
+LaneKernel lane_kernel_phys32(int waves, bool stage, bool cls);
+
+// ComputeStep with each lane in its own volume, and the serving round.
+StepNavKernel step_nav_kernel(bool has_bool, bool fp32);
+ServeKernel serve_kernel(bool has_bool);
+
+// The launch shapes of one precision and kind of transport.
+template <bool F32, bool PHYS>
+LaneKernel lane_kernel_for(int waves, bool stage, bool cls) {
+  if (cls) return waves == 3 ? k_lane_transport<F32, PHYS, false, 3, 8, true> : k_lane_transport<F32, PHYS, false, 4, 8, true>;
+  if (waves == 3) return stage ? k_lane_transport<F32, PHYS, false, 3, 8> : k_lane_transport<F32, PHYS, false, 3, 0>;
+  return stage ? k_lane_transport<F32, PHYS, false, 4, 8> : k_lane_transport<F32, PHYS, false, 4, 0>;
+}
+
+}  // namespace gv

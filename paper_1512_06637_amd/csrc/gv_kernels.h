@@ -214,7 +214,7 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   return v;
 }
-__global__ void k_pcon_work(CQ q, int dir, int64_t n, const double* __restrict__ x, const double* __restrict__ y,
+static __global__ void k_pcon_work(CQ q, int dir, int64_t n, const double* __restrict__ x, const double* __restrict__ y,
                             const double* __restrict__ z, const double* __restrict__ dx,
                             const double* __restrict__ dy, const double* __restrict__ dz,
                             unsigned long long* __restrict__ out) {

@@ -86,7 +86,7 @@ struct LaneCtl {
 };
 
 // Zeroes the key counts and the work counter before a transport.
-__global__ void k_ls_clear(LaneCtl L, int cells) {
+static __global__ void k_ls_clear(LaneCtl L, int cells) {
   for (int64_t i = gtid(); i < cells; i += gstride()) L.cnt[i] = 0u;
   if (gtid() == 0) *L.queue = 0u;
 }
@@ -94,7 +94,7 @@ __global__ void k_ls_clear(LaneCtl L, int cells) {
 // Key of every track (z-axis or octahedral) and the per-key counts
 // (workgroup histogram in LDS, 4 cells bytes of dynamic LDS, one global
 // atomic per workgroup and key).
-__global__ void k_ls_count(int64_t n, const double* __restrict__ dx, const double* __restrict__ dy,
+static __global__ void k_ls_count(int64_t n, const double* __restrict__ dx, const double* __restrict__ dy,
                            const double* __restrict__ dz, int h, int zaxis, LaneCtl L) {
   extern __shared__ uint32_t key_hist[];
   const int cells = 1 << (2 * h);
@@ -112,7 +112,7 @@ __global__ void k_ls_count(int64_t n, const double* __restrict__ dx, const doubl
 
 // Exclusive scan of the key counts in place (one workgroup of 1024 threads):
 // cnt[c] becomes the first place of key c.
-__global__ void __launch_bounds__(1024) k_ls_scan(LaneCtl L, int cells) {
+static __global__ void __launch_bounds__(1024) k_ls_scan(LaneCtl L, int cells) {
   __shared__ uint32_t part[1024];
   const int t = threadIdx.x;
   const int per = (cells + 1023) / 1024;
@@ -141,7 +141,7 @@ __global__ void __launch_bounds__(1024) k_ls_scan(LaneCtl L, int cells) {
 // each of its tracks the next place of its key's run (4 cells bytes of
 // dynamic LDS).  The order inside a key depends on the atomics' order, which
 // changes no result.
-__global__ void __launch_bounds__(1024) k_ls_scatter(int64_t n, int64_t chunk, int cells, LaneCtl L) {
+static __global__ void __launch_bounds__(1024) k_ls_scatter(int64_t n, int64_t chunk, int cells, LaneCtl L) {
   extern __shared__ uint32_t key_run[];
   const int64_t a = (int64_t)blockIdx.x * chunk, b = min(n, a + chunk);
   for (int c = threadIdx.x; c < cells; c += blockDim.x) key_run[c] = 0u;

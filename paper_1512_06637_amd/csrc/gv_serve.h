@@ -14,97 +14,7 @@
 #include <utility>
 
 #include "gv_arena.h"
-
-namespace gv {
-
-enum { kQStep = 0, kQSafety = 1, kQInside = 2 };
-
-// One basket of a round; the fused kernel reads the round's table.
-struct SDesc {
-  int32_t kind, prec;
-  int64_t n;
-  int64_t tile0;    // first 64-track tile of the basket within the round
-  int64_t in_off;   // byte offset of its inputs in the input arena
-  int64_t out_off;  // byte offset of its outputs in the output arena
-  int64_t pad;
-};
-static_assert(sizeof(SDesc) == 48, "SDesc layout");
-
-constexpr int kServeMaxSlots = 1024;
-
-// Bytes of one basket in host layout (gvgeom.h, serving section).
-__host__ __device__ inline int64_t serve_in_bytes(int kind, int64_t n) { return (kind == kQStep ? 60 : 28) * n; }
-__host__ __device__ inline int64_t serve_out_bytes(int kind, int64_t n) {
-  return (kind == kQStep ? 16 : kind == kQSafety ? 8 : 1) * n;
-}
-
-// Fused mixed-query kernel: one wavefront answers one tile of 64 tracks of one
-// basket, so the query kind and precision are wavefront-uniform; a basket's
-// tracks may sit in different volumes (per-lane navigation state).
-template <bool B>
-__global__ void __launch_bounds__(256) k_serve(DevGeom G, const SDesc* __restrict__ desc, int nb, int64_t ntiles,
-                                               const char* __restrict__ din, char* __restrict__ dout) {
-  __shared__ int64_t t0[kServeMaxSlots + 1];
-  for (int b = threadIdx.x; b < nb; b += blockDim.x) t0[b] = desc[b].tile0;
-  if (threadIdx.x == 0) t0[nb] = ntiles;
-  __syncthreads();
-  const int lane = __lane_id();
-  const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64;
-  const int64_t nwaves = (int64_t)gridDim.x * blockDim.x / 64;
-  NoWork w;
-  for (int64_t t = wave; t < ntiles; t += nwaves) {
-    int lo = 0, hi = nb - 1;  // largest b with t0[b] <= t
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (t0[mid] <= t) lo = mid;
-      else hi = mid - 1;
-    }
-    const int b = __builtin_amdgcn_readfirstlane(lo);
-    const int kind = desc[b].kind, prec = desc[b].prec;
-    const int64_t n = desc[b].n;
-    const int64_t i = (t - t0[b]) * 64 + lane;
-    if (i >= n) continue;
-    const double* X = (const double*)(din + desc[b].in_off);
-    char* O = dout + desc[b].out_off;
-    const V3 p{X[i], X[n + i], X[2 * n + i]};
-    if (kind == kQStep) {
-      const V3 d{X[3 * n + i], X[4 * n + i], X[5 * n + i]};
-      const double ps = X[6 * n + i];
-      const int v = ((const int32_t*)(X + 7 * n))[i];
-      uint32_t fl = 0;
-      int nx = -1;
-      double st = 0.0;
-      if (v >= 0 && v < G.n_pv) {
-        st = prec == 0 ? step_culled_limited<false, B>(G, v, p, d, ps, &nx, &fl, w)
-                       : step_culled_limited<true, B>(G, v, p, d, ps, &nx, &fl, w);
-      } else {
-        fl = kFlagLocateFail;
-      }
-      double* os = (double*)O;
-      int32_t* on = (int32_t*)(os + n);
-      uint32_t* of = (uint32_t*)(on + n);
-      os[i] = st;
-      on[i] = nx;
-      of[i] = fl;
-    } else {
-      const int v = ((const int32_t*)(X + 3 * n))[i];
-      const bool ok = v >= 0 && v < G.n_pv;
-      if (kind == kQSafety) {
-        ((double*)O)[i] = !ok ? 0.0 : prec == 0 ? nav_safety<B>(G, v, p) : nav_safety_screened<B>(G, v, p);
-      } else {
-        int8_t c = (int8_t)kOutside;
-        if (ok) {
-          const int lv = G.pv_lv[v];
-          const V3 pl = to_child_p(G.pv_gxf + 12 * (size_t)v, p);
-          c = (int8_t)code_of(solid_sgn<B>(G.lv_type[lv], G.par + G.lv_par[lv], pl));
-        }
-        ((int8_t*)O)[i] = c;
-      }
-    }
-  }
-}
-
-}  // namespace gv
+#include "gv_serve_kernel.h"
 
 // ----------------------------------------------------------- host engine
 struct gv_server {
@@ -206,7 +116,7 @@ int server_launch(gv_server* s, int k) {
   const auto rout = runs(R.bs, [](const gv_server::Bk& b) { return std::make_pair(b.out_off, b.out_len); });
   gv::SDesc* dd = s->d_desc + (size_t)k * s->slots;
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((tiles + 3) / 4, 2048));
-  auto kernel = s->g->has_bool ? gv::k_serve<true> : gv::k_serve<false>;
+  auto kernel = gv::serve_kernel(s->g->has_bool);
   if (s->graphs && rin.size() <= 2 && rout.size() <= 2) {
     // one graph launch: the round's copies and kernel as the node parameters
     gv_server::RoundGraph& G = s->rg[k];
@@ -339,7 +249,7 @@ int server_round_graph(gv_server* s, int k) {
   char* dout = s->d_out;
   void* args[] = {&dg, &cdd, &nb, &tiles, &din, &dout};
   hipKernelNodeParams kp{};
-  kp.func = reinterpret_cast<void*>(s->g->has_bool ? gv::k_serve<true> : gv::k_serve<false>);
+  kp.func = reinterpret_cast<void*>(gv::serve_kernel(s->g->has_bool));
   kp.gridDim = dim3(1);
   kp.blockDim = dim3(kBlock);
   kp.sharedMemBytes = 0;
