@@ -184,8 +184,8 @@ int nav_transport(gv_geom* g, int64_t n, const double* x, const double* y, const
 /* Allocation-free nav_transport, for callers that cannot allocate device
  * memory: code under HIP graph capture, serving loops, harnesses that forbid
  * allocation.  Same arguments, definitions and outputs as nav_transport (its
- * lane form, whatever the tuned transport field says), but the keys, order and
- * counters live in a static device array of the library, 16.06 MiB per device
+ * lane form, whatever the tuned transport field says), but the start volumes,
+ * keys, order and counters live in a static device array of the library, 24.06 MiB per device
  * and held until the process ends, so the call allocates nothing and needs no
  * earlier call.  1 <= n <= 2,097,152 (GV_EINVAL beyond; n == 0 is a no-op).
  * Every call on one device shares that device's array, which keeps the last

@@ -43,13 +43,13 @@ static int hip_fail(hipError_t e, const char* what) {
 extern "C" const char* gv_last_error(void) { return t_err.c_str(); }
 
 // ------------------------------------------------- allocation-free scratch
-// Scratch of nav_transport_noalloc: the lane form's keys, order and counters
-// for up to kNoAllocMaxTracks tracks (16.06 MiB), one copy per device, held
+// Scratch of nav_transport_noalloc: the lane form's start volumes, keys, order and counters
+// for up to kNoAllocMaxTracks tracks (24.06 MiB), one copy per device, held
 // until the process ends.  In host code `scratch` names a host-side stand-in:
 // kernels get the device address that hipGetSymbolAddress returned for each
 // device (noalloc_scratch), never the symbol itself.
 constexpr int64_t kNoAllocMaxTracks = (int64_t)1 << 21;
-constexpr size_t kScratchBytes = 2 * 4 * (size_t)kNoAllocMaxTracks + 4 * (size_t)kSortMaxCells + 256;
+constexpr size_t kScratchBytes = 3 * 4 * (size_t)kNoAllocMaxTracks + 4 * (size_t)kSortMaxCells + 256;
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -358,6 +358,28 @@ void local_extent(int type, const double* q, double* lo, double* hi) {
   hi[0] = rx, hi[1] = ry, hi[2] = z1;
 }
 
+// How far a point of the solid's surface band (|signed term| <= kTolerance / 2)
+// can lie outside local_extent, bounded from the slopes of its faces: the terms
+// of cone, Trd and polycone sides are normalised, so the band of a steep side
+// reaches further along an axis.
+double band_reach(int type, const double* q) {
+  double k = 0;
+  switch (type) {
+    case kCons: k = std::max(std::fabs(q[L::CN_BO]), std::fabs(q[L::CN_BI])); break;
+    case kTrd: k = std::max(std::fabs(q[L::TD_TX]), std::fabs(q[L::TD_TY])); break;
+    case kPcon: {
+      const int nz = (int)q[0];
+      const double* b = q + 1 + 3 * nz;  // bo[nz-1] co[nz-1] bi[nz-1]
+      for (int j = 0; j + 1 < nz; ++j) k = std::max({k, std::fabs(b[j]), std::fabs(b[2 * (nz - 1) + j])});
+      break;
+    }
+    case kBool:
+      return std::max(band_reach((int)q[L::BO_TA], q + (int)q[L::BO_OA]),
+                      band_reach((int)q[L::BO_TC], q + (int)q[L::BO_OC]));
+  }
+  return 4.0 * kHalf * (1.0 + k);
+}
+
 // composed transform C = A o B (apply B then A): R = Ra Rb, t = Ra tb + ta
 void compose(const double* A, const double* B, double* C) {
   for (int i = 0; i < 3; ++i) {
@@ -445,7 +467,7 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
         }
       }
       for (int i = 0; i < 3; ++i) {
-        double pad = 1e-6 + 1e-9 * (std::fabs(blo[i]) + std::fabs(bhi[i]));
+        double pad = 1e-6 + 1e-9 * (std::fabs(blo[i]) + std::fabs(bhi[i])) + band_reach(lv_type[dau_lv[k]], q);
         dau_box[6 * (size_t)k + i] = blo[i] - pad;
         dau_box[6 * (size_t)k + 3 + i] = bhi[i] + pad;
       }
@@ -628,6 +650,24 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
       else mode = 8;
       lv_class[i] = mode * 8 + lv_type[i];
     }
+    // how point lookups reach an LV's daughters; placements that are not
+    // rotations keep the loop over every daughter
+    std::vector<int> lv_loc(n_lv, kLocPlain);
+    for (int i = 0; i < n_lv; ++i) {
+      bool rot = lv_dcnt[i] > 0;
+      for (int k = lv_doff[i]; k < lv_doff[i] + lv_dcnt[i] && rot; ++k) {
+        const double* X = &dau_xf[12 * (size_t)k];
+        for (int a = 0; a < 3; ++a)
+          for (int c = 0; c < 3; ++c) {
+            const double v = X[3 * a] * X[3 * c] + X[3 * a + 1] * X[3 * c + 1] + X[3 * a + 2] * X[3 * c + 2];
+            rot = rot && std::fabs(v - (a == c ? 1.0 : 0.0)) <= 1e-9;
+          }
+      }
+      if (!rot) continue;
+      if (lv_rad[i] >= 0) lv_loc[i] = kLocRadial;
+      else if (lv_phi[i] >= 0) lv_loc[i] = kLocPhi;
+      else lv_loc[i] = kLocBox;
+    }
     // count the tree first (depth and size limits also reject cycles)
     std::vector<long> subtree(n_lv, -1);
     std::vector<int> state(n_lv, 0), height(n_lv, 0);
@@ -725,7 +765,7 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
         {rad_k.data(), rad_k.size() * 4, 0},         {lv_phi.data(), lv_phi.size() * 4, 0},
         {phi_mask.data(), phi_mask.size() * 8, 0},   {nullptr, 5 * 8, 0},
         {lv_class.data(), lv_class.size() * 4, 0},   {pv_k.data(), pv_k.size() * 4, 0},
-        {pv_lc.data(), pv_lc.size() * 4, 0}};
+        {pv_lc.data(), pv_lc.size() * 4, 0},         {lv_loc.data(), lv_loc.size() * 4, 0}};
     size_t total = 0;
     for (auto& p : parts) {
       p.off = total;
@@ -794,6 +834,7 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
     D.lv_class = (CQI)(base + parts[28].off);
     D.pv_k = (CQI)(base + parts[29].off);
     D.pv_lc = (CQI)(base + parts[30].off);
+    D.lv_loc = (CQI)(base + parts[31].off);
     g->n_lv = n_lv;
     g->n_pv = (int)npv;
     g->n_place = n_place;
@@ -1348,12 +1389,14 @@ constexpr int kLaneSortBits = 7;  // default direction cells of the order: 128 x
 int sort_bits(const gv_geom* g) { return g->tune.sort_bits >= 0 ? g->tune.sort_bits : kLaneSortBits; }
 
 size_t lane_ws_bytes(int64_t cap) {
-  return 2 * al256(4 * (size_t)cap) + al256(4 * (size_t)kSortMaxCells) + al256(4);
+  return 3 * al256(4 * (size_t)cap) + al256(4 * (size_t)kSortMaxCells) + al256(4);
 }
 
 LaneCtl carve_lane_ctl(void* mem, int64_t cap) {
   char* p = (char*)mem;
   LaneCtl L;
+  L.pv0 = (int32_t*)p;
+  p += al256(4 * (size_t)cap);
   L.key = (uint32_t*)p;
   p += al256(4 * (size_t)cap);
   L.perm = (int32_t*)p;
@@ -1364,7 +1407,7 @@ LaneCtl carve_lane_ctl(void* mem, int64_t cap) {
   return L;
 }
 
-// Keys, order and counters for `n` tracks, allocated with hipMalloc on first
+// Start volumes, keys, order and counters for `n` tracks, allocated with hipMalloc on first
 // use and grown on demand (no clearing needed: every transport clears the
 // counters with a kernel and writes the keys and the order before reading).
 int ensure_lane_workspace(gv_geom* g, int64_t n) {
@@ -1410,8 +1453,11 @@ int lane_transport(gv_geom* g, const LaneCtl& L, int64_t n, const double* x, con
   const int h = std::min(sort_bits(g), kSortMaxBits);
   const bool sorted = h > 0;
   const int cells = sorted ? 1 << (2 * h) : 0;
-  hipLaunchKernelGGL(k_ls_clear, dim3((unsigned)std::max(1, (cells + 255) / 256)), dim3(256), 0, s, L, cells);
+  const Shape sh = lane_shape(g, start_pv ? cells : n);
+  hipLaunchKernelGGL(g->has_bool ? k_ls_begin<true> : k_ls_begin<false>, dim3(sh.grid), dim3(sh.block), 0, s, g->dg, n,
+                     start_pv ? (const double*)nullptr : x, y, z, L, cells);
   GV_TRY(launched(fn));
+  if (!start_pv) start_pv = L.pv0;
   if (sorted) {
     const unsigned cg = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 4095) / 4096, 256));
     hipLaunchKernelGGL(k_ls_count, dim3(cg), dim3(1024), 4 * (size_t)cells, s, n, dx, dy, dz, h,
@@ -1555,7 +1601,7 @@ extern "C" int nav_transport_noalloc(gv_geom* g, int64_t n, const double* x, con
   void* p = noalloc_scratch(g->device);
   if (!p) return fail(GV_ESTATE, "%s: no scratch address for device %d", fn, g->device);
   DeviceGuard dgd(g->device);
-  static_assert(2 * 4 * (size_t)kNoAllocMaxTracks + 4 * (size_t)kSortMaxCells + 4 <= kScratchBytes,
+  static_assert(3 * 4 * (size_t)kNoAllocMaxTracks + 4 * (size_t)kSortMaxCells + 4 <= kScratchBytes,
                 "scratch holds the lane form's arrays");
   const LaneCtl L = carve_lane_ctl(p, kNoAllocMaxTracks);
   return lane_transport(g, L, n, x, y, z, dx, dy, dz, start_pv, max_steps, out_pv, out_step, out_nsteps, out_flags,

@@ -54,6 +54,7 @@ struct DevGeom {
   CQI lv_mat;        // [n_lv] material of each LV
   CQI lv_class;      // [n_lv] step class: branch of the step code (daughter access mode x 8 + solid type)
   CQI pv_k;          // [n_pv] placement index of each PV among its parent's daughters (-1: the world)
+  CQI lv_loc;        // [n_lv] how point lookups reach the daughters (kLoc*)
   CQI pv_lc;         // [2 n_pv] logical volume and step class of each PV (one 8-byte load)
 };
 
@@ -74,29 +75,162 @@ __device__ __forceinline__ V3 to_child_d(CQ X, V3 d) {
 
 constexpr uint32_t kFlagOverflow = 1u, kFlagStuck = 2u, kFlagLocateFail = 4u;
 
+// Point lookups through the daughter indexes.  lv_loc says how an LV's
+// daughters that can hold a point (or, for NavSafety, be nearest to it) are
+// found; every candidate then goes through the same solid code as in the loop
+// over all daughters, so the answers are the same bit for bit.
+enum { kLocPlain = 0, kLocRadial = 1, kLocPhi = 2, kLocBox = 3 };
+
+// The access mode for a point: the indexes take finite coordinates only (a NaN
+// or infinity goes through every daughter's own code).
+__device__ __forceinline__ int loc_mode(const DevGeom& G, int lv, V3 p) {
+  return p.x * p.x + p.y * p.y + p.z * p.z < 1e200 ? G.lv_loc[lv] : kLocPlain;
+}
+
+__device__ __forceinline__ int phi_sector(double a) {
+  return min(kPhiSectors - 1, max(0, (int)(a * (kPhiSectors / 4.0))));
+}
+
+// Radial entries with rmin^2 <= rho^2.
+__device__ __forceinline__ int radial_rank(CQ R2, int cnt, double rho2) {
+  int j = 0;
+  for (int m = 0; m < cnt; ++m) j += R2[2 * m] <= rho2 ? 1 : 0;
+  return j;
+}
+
+// Index of the first daughter of lv whose Inside code is not outside (-1:
+// none).  Radial order: only the tubes whose radial range, widened by more than
+// the surface band, holds the point's radius (the ranges are disjoint and
+// sorted, so those are neighbours of its rank).  Phi sectors: the daughters of
+// the point's sector.  Boxes: the daughters whose padded box holds the point.
+// The plain loop made a point in the detector evaluate up to 84 daughters (128
+// us per 300,007 points spread over it), the indexes two or three (13 us, most
+// of it the call).
+template <bool B>
+__device__ __forceinline__ int first_daughter(const DevGeom& G, int lv, V3 pl) {
+  const int off = G.lv_dau_off[lv], cnt = G.lv_dau_cnt[lv];
+  if (cnt == 0) return -1;
+  int mode = loc_mode(G, lv, pl);
+  auto holds = [&](int k) {
+    const int clv = G.dau_lv[off + k];
+    const V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(off + k), pl);
+    return code_of(solid_sgn<B>(G.lv_type[clv], G.par + G.lv_par[clv], pc)) != kOutside;
+  };
+  if (mode == kLocRadial) {
+    const int r0 = G.lv_rad[lv];
+    CQ R2 = G.rad_r2 + 2 * (size_t)r0;
+    CQI K = G.rad_k + r0;
+    const double rho2 = pl.x * pl.x + pl.y * pl.y;
+    const int j = radial_rank(R2, cnt, rho2);
+    int best = cnt;
+    auto test = [&](int m) {
+      const int k = K[m];
+      if (k < best && code_of(Tubs::sgn(G.par + G.dau_par[off + k], pl)) != kOutside) best = k;
+    };
+    for (int m = j - 1; m >= 0 && rho2 <= fma(R2[2 * m + 1], 1.0 + 1e-8, 1e-8); --m) test(m);
+    for (int m = j; m < cnt && rho2 >= fma(R2[2 * m], 1.0 - 1e-8, -1e-8); ++m) test(m);
+    return best < cnt ? best : -1;
+  }
+  if (mode == kLocPhi && fabs(pl.x) + fabs(pl.y) > 1e-6) {
+    uint64_t cand = (G.phi_mask + (size_t)G.lv_phi[lv])[phi_sector(pseudo_angle_fast(pl.x, pl.y))];
+    const int type = G.lv_dau_type[lv];
+    while (cand) {
+      const int k = __builtin_ctzll(cand);
+      cand &= cand - 1;
+      CQ q = G.par + G.dau_par[off + k];
+      const V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(off + k), pl);
+      if (code_of(type == kBox ? Box::sgn(q, pc) : Tubs::sgn(q, pc)) != kOutside) return k;
+    }
+    return -1;
+  }
+  for (int k = 0; k < cnt; ++k) {
+    if (mode == kLocBox) {
+      CQ X = G.dau_box + 6 * (size_t)(off + k);
+      if (pl.x < X[0] || pl.y < X[1] || pl.z < X[2] || pl.x > X[3] || pl.y > X[4] || pl.z > X[5]) continue;
+    }
+    if (holds(k)) return k;
+  }
+  return -1;
+}
+
 template <bool B>
 __device__ __forceinline__ int locate(const DevGeom& G, V3 p) {
-  int lv0 = G.pv_lv[0];
-  if (code_of(solid_sgn<B>(G.lv_type[lv0], G.par + G.lv_par[lv0], p)) == kOutside) return -1;
+  int lv = G.pv_lv[0];
+  if (code_of(solid_sgn<B>(G.lv_type[lv], G.par + G.lv_par[lv], p)) == kOutside) return -1;
   int pv = 0;
   V3 pl = p;
   for (;;) {
-    int lv = G.pv_lv[pv];
-    int off = G.lv_dau_off[lv], cnt = G.lv_dau_cnt[lv];
-    int found = -1;
-    V3 pc;
-    for (int k = 0; k < cnt; ++k) {
-      int clv = G.dau_lv[off + k];
-      pc = to_child_p(G.dau_xf + 12 * (size_t)(off + k), pl);
-      if (code_of(solid_sgn<B>(G.lv_type[clv], G.par + G.lv_par[clv], pc)) != kOutside) {
-        found = k;
-        break;
-      }
-    }
-    if (found < 0) return pv;
-    pv = G.pv_child[G.pv_child_off[pv] + found];
-    pl = pc;
+    const int k = first_daughter<B>(G, lv, pl);
+    if (k < 0) return pv;
+    pl = to_child_p(G.dau_xf + 12 * (size_t)(G.lv_dau_off[lv] + k), pl);
+    pv = G.pv_child[G.pv_child_off[pv] + k];
+    lv = G.pv_lv[pv];
   }
+}
+
+// NavSafety's part over the daughters of an LV with a radial order or with phi
+// sectors of box daughters: lowers s to the smallest SafetyToIn (0 when the
+// point is not strictly outside a daughter), visiting only daughters whose
+// SafetyToIn can be below s; false when the LV has no such index.  Radial: a
+// tube's SafetyToIn is at least rmin - r and r - rmax, which grow away from the
+// point's rank.  Phi: the daughters of the point's own sector first; then those
+// within the angle beyond which the distance r sin(angle) exceeds sqrt(3) s (a
+// box's SafetyToIn, the largest of its three gaps, is at least its distance
+// over sqrt(3)), an arc of at most pi/2 sin(angle) in pseudo-angle.  kTolerance
+// on top of s keeps rounding of the bounds from mattering.  In the detector two
+// or three daughters instead of 20 or 64 (71 against 18 us per 200,003 points).
+__device__ __forceinline__ bool safety_indexed(const DevGeom& G, int lv, V3 pl, double& s) {
+  const int mode = loc_mode(G, lv, pl);
+  if (mode != kLocRadial && !(mode == kLocPhi && G.lv_dau_type[lv] == kBox)) return false;
+  const int off = G.lv_dau_off[lv], cnt = G.lv_dau_cnt[lv];
+  const double rho2 = pl.x * pl.x + pl.y * pl.y, r = sqrt(rho2);
+  auto limit = [&] { return fmax(s, kHalf) + kTol; };
+  if (mode == kLocRadial) {
+    const int r0 = G.lv_rad[lv];
+    CQI K = G.rad_k + r0;
+    const int j = radial_rank(G.rad_r2 + 2 * (size_t)r0, cnt, rho2);
+    auto eval = [&](CQ q) { s = code_of(Tubs::sgn(q, pl)) == kOutside ? fmin(s, Tubs::safety_in(q, pl)) : 0.0; };
+    for (int m = j - 1; m >= 0; --m) {
+      CQ q = G.par + G.dau_par[off + K[m]];
+      if (r - q[L::TB_RMAX] > limit()) break;
+      eval(q);
+    }
+    for (int m = j; m < cnt; ++m) {
+      CQ q = G.par + G.dau_par[off + K[m]];
+      if (q[L::TB_RMIN] - r > limit()) break;
+      eval(q);
+    }
+    return true;
+  }
+  CQL M = G.phi_mask + (size_t)G.lv_phi[lv];
+  const uint64_t all = cnt == 64 ? ~0ull : (1ull << cnt) - 1;
+  const bool off_axis = fabs(pl.x) + fabs(pl.y) > 1e-6;
+  const double a = off_axis ? pseudo_angle_fast(pl.x, pl.y) : 0.0;
+  uint64_t cand = off_axis ? M[phi_sector(a)] : all, done = 0;
+  for (int pass = 0; pass < 2; ++pass) {
+    done |= cand;
+    while (cand) {
+      const int k = __builtin_ctzll(cand);
+      cand &= cand - 1;
+      CQ q = G.par + G.dau_par[off + k];
+      const V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(off + k), pl);
+      s = code_of(Box::sgn(q, pc)) == kOutside ? fmin(s, Box::safety_in(q, pc)) : 0.0;
+    }
+    if (pass == 1 || done == all) break;
+    const double w = 1.5707964 * 1.7320509 * limit() * rcp_fast(r) + 1e-6;  // pi/2 sin(angle)
+    if (w < 0.5) {
+      const double b0 = a - w, b1 = a + w;
+      const int s1 = phi_sector(b1 >= 4.0 ? b1 - 4.0 : b1);
+      for (int c = phi_sector(b0 < 0.0 ? b0 + 4.0 : b0);; c = (c + 1) & (kPhiSectors - 1)) {
+        cand |= M[c];
+        if (c == s1) break;
+      }
+    } else {
+      cand = all;
+    }
+    cand &= ~done;
+  }
+  return true;
 }
 
 template <bool B>
@@ -107,6 +241,7 @@ __device__ __forceinline__ double nav_safety(const DevGeom& G, int pv, V3 p) {
   CQ q = G.par + G.lv_par[lv];
   if (code_of(solid_sgn<B>(t, q, pl)) != kInside) return 0.0;
   double s = solid_safety_out<B>(t, q, pl);
+  if (safety_indexed(G, lv, pl, s)) return fmax(s, 0.0);
   int off = G.lv_dau_off[lv], cnt = G.lv_dau_cnt[lv];
   for (int k = 0; k < cnt; ++k) {
     int clv = G.dau_lv[off + k];

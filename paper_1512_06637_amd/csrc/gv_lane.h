@@ -79,16 +79,25 @@ __device__ __forceinline__ uint32_t direction_key_zaxis(double dx, double dy, do
 // then the running place of each cell during the scatter, and the work
 // counter the persistent workers take places from.
 struct LaneCtl {
+  int32_t* pv0;     // [n] start volume of each track, where the caller gives none
   uint32_t* key;    // [n] direction key of each track
   int32_t* perm;    // [n] track of each place in the coherent order
   uint32_t* cnt;    // [cells] tracks per key
   uint32_t* queue;  // [1] next place to hand out
 };
 
-// Zeroes the key counts and the work counter before a transport.
-static __global__ void k_ls_clear(LaneCtl L, int cells) {
+// Before a transport: zeroes the key counts and the work counter, and locates
+// the tracks whose start volume the caller does not give (x not NULL).  With the
+// point lookup inside the transport kernel instead, its code took registers
+// from the step loop (1.89 against 1.85 ms per 2^20-track detector transport);
+// here it runs at full occupancy.
+template <bool B>
+__global__ void k_ls_begin(DevGeom G, int64_t n, const double* __restrict__ x, const double* __restrict__ y,
+                           const double* __restrict__ z, LaneCtl L, int cells) {
   for (int64_t i = gtid(); i < cells; i += gstride()) L.cnt[i] = 0u;
   if (gtid() == 0) *L.queue = 0u;
+  if (!x) return;
+  for (int64_t i = gtid(); i < n; i += gstride()) L.pv0[i] = locate<B>(G, ld3(x, y, z, i));
 }
 
 // Key of every track (z-axis or octahedral) and the per-key counts
@@ -165,10 +174,8 @@ struct LaneTrack {
   uint64_t procs;  // physics, staged outputs: the process codes of the run, byte k % 8 for step k
 };
 
-// Starts track i: its volume (given or located) and entry 0 of its sequence.
-// Returns false (and writes the track's zero count and flags) when it starts
-// outside the world.
-template <bool B>
+// Starts track i: its volume and entry 0 of its sequence.  Returns false (and
+// writes the track's zero count and flags) when it starts outside the world.
 __device__ __forceinline__ bool lane_begin(const DevGeom& G, LaneTrack& T, int64_t i, const double* __restrict__ x,
                                            const double* __restrict__ y, const double* __restrict__ z,
                                            const double* __restrict__ dx, const double* __restrict__ dy,
@@ -184,7 +191,7 @@ __device__ __forceinline__ bool lane_begin(const DevGeom& G, LaneTrack& T, int64
   T.left = -1;
   T.safe = 0.0;
   T.procs = 0;
-  int pv = start_pv ? start_pv[i] : locate<B>(G, T.p);
+  int pv = start_pv[i];
   if (pv < -1 || pv >= G.n_pv) {
     pv = -1;
     T.fl = kFlagLocateFail;
@@ -339,7 +346,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
     bool live = false;
     if (j < n) {
       const int64_t i = perm ? perm[j] : j;
-      live = lane_begin<B>(G, T, i, x, y, z, dx, dy, dz, start_pv, max_steps, out_pv, out_nsteps, out_flags);
+      live = lane_begin(G, T, i, x, y, z, dx, dy, dz, start_pv, max_steps, out_pv, out_nsteps, out_flags);
     }
     if (!CLS) {
       if (live)

@@ -318,8 +318,7 @@ __device__ __forceinline__ void daughters_radial(const DevGeom& G, int r0, int o
   const double rho2 = pl.x * pl.x + pl.y * pl.y;
   const double A = dl.x * dl.x + dl.y * dl.y, B = pl.x * dl.x + pl.y * dl.y;
   w.add(kWorkRadial);
-  int j = 0;  // entries with rmin^2 <= rho^2
-  for (int m = 0; m < cnt; ++m) j += R2[2 * m] <= rho2 ? 1 : 0;
+  const int j = radial_rank(R2, cnt, rho2);
   auto eval = [&](int m) {
     const int k = K[m];
     w.add(kWorkFull + kTubs);
@@ -378,11 +377,10 @@ __device__ __forceinline__ void daughters_phi(const DevGeom& G, int lv, int m0, 
   w.add(kWorkPhi);
   const double a0 = pseudo_angle_fast(pl.x, pl.y), a1 = pseudo_angle_fast(pl.x + T * dl.x, pl.y + T * dl.y);
   const bool ccw = pl.x * dl.y - pl.y * dl.x >= 0.0;
-  auto sec = [](double a) { return min(kPhiSectors - 1, max(0, (int)(a * (kPhiSectors / 4.0)))); };
-  const int s1 = sec(ccw ? a1 : a0);
+  const int s1 = phi_sector(ccw ? a1 : a0);
   CQL M = G.phi_mask + (size_t)m0;
   uint64_t cand = 0;
-  for (int s = sec(ccw ? a0 : a1);; s = (s + 1) & (kPhiSectors - 1)) {
+  for (int s = phi_sector(ccw ? a0 : a1);; s = (s + 1) & (kPhiSectors - 1)) {
     cand |= M[s];
     w.add(kWorkPhiSec);
     if (s == s1) break;
@@ -564,7 +562,7 @@ __device__ __forceinline__ double step_physics(const DevGeom& G, int lv, int pv,
   return st;
 }
 
-// NavSafety with the FP32 SafetyToIn screen: a box or tube daughter is skipped
+// NavSafety with the FP32 SafetyToIn screen where no index serves: a box or tube daughter is skipped
 // when its FP32 lower bound (minus its error) exceeds both the running minimum
 // and the surface half-band by kTolerance, i.e. when the point is provably
 // outside it and it cannot lower the minimum.  Equal to nav_safety bit for bit.
@@ -576,6 +574,7 @@ __device__ __forceinline__ double nav_safety_screened(const DevGeom& G, int pv, 
   CQ q = G.par + G.lv_par[lv];
   if (code_of(solid_sgn<B>(t, q, pl)) != kInside) return 0.0;
   double s = solid_safety_out<B>(t, q, pl);
+  if (safety_indexed(G, lv, pl, s)) return fmax(s, 0.0);
   const int off = G.lv_dau_off[lv], cnt = G.lv_dau_cnt[lv], dtype = G.lv_dau_type[lv];
   const F3 p32{(float)pl.x, (float)pl.y, (float)pl.z};
   const float pmax = max3f(fabsf(p32.x), fabsf(p32.y), fabsf(p32.z));
