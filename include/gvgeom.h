@@ -284,7 +284,8 @@ int gv_probe_fma64(double* out, int64_t n_lanes, int32_t iters, void* stream);
  *
  * The transports have two forms.  The lane form (default) orders the tracks
  * once by a direction key (counting sort into 2^sort_bits x 2^sort_bits
- * direction cells), then one
+ * direction cells; for geometries with composites by start volume and the
+ * daughters on the track's way first, with fewer cells), then one
  * persistent kernel carries each track in one lane from its start to its end,
  * wavefronts taking 64 places of the order at a time from an atomic counter.
  * The basket form (Sec. II.A baskets of tracks in the same volume) regroups
@@ -305,9 +306,8 @@ int gv_probe_fma64(double* out, int64_t n_lanes, int32_t iters, void* stream);
  *                 per track);
  *   step_waves    3 or 4: waves per SIMD the navigation step kernel is built
  *                 for (default 4);
- *   transport     1 basket form, 2 lane form (default: lane, or basket for
- *                 geometries holding composites; the basket form needs
- *                 n >= 8,192, smaller batches take the lane form);
+ *   transport     1 basket form, 2 lane form (default: lane; the basket form
+ *                 needs n >= 8,192, smaller batches take the lane form);
  *   sort_bits     0..7: the lane form's direction cells are 2^sort_bits x
  *                 2^sort_bits (0: no ordering, tracks in index order;
  *                 default 7);
@@ -324,7 +324,7 @@ int gv_probe_fma64(double* out, int64_t n_lanes, int32_t iters, void* stream);
  *                 class (solid type and daughter access) most of the
  *                 wavefront's live lanes are in take a step, the others wait,
  *                 so lanes that fell behind catch up (default 2; geometries
- *                 with composites always 1).
+ *                 with composites always 2, one logical volume at a time).
  * A change of cell_bits re-sizes the transport workspace at the next
  * transport.  GV_EINVAL for a field out of range (nothing changed). */
 typedef struct {

@@ -8,8 +8,9 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgvgeom.so")
-SOURCES = ["gv_inst_lane_phys64.hip", "gv_inst_lane_phys32.hip", "gv_inst_lane.hip", "gv_inst_lane_nav32.hip",
-           "gv_inst_step.hip", "gv_inst_step_phys.hip", "gv_inst_lane_bool.hip", "gv_inst_query.hip", "gv_abi.hip"]
+SOURCES = ["gv_inst_lane_phys64.hip", "gv_inst_lane_phys32.hip", "gv_inst_lane.hip", "gv_inst_lane_nav64.hip",
+           "gv_inst_lane_nav32.hip", "gv_inst_step.hip", "gv_inst_step_phys.hip", "gv_inst_lane_composites.hip",
+           "gv_inst_query.hip", "gv_abi.hip"]
 ARCH = os.environ.get("GV_OFFLOAD_ARCH", "gfx950")
 
 

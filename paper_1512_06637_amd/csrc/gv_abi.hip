@@ -81,7 +81,8 @@ struct gv_geom {
   int device = -1;
   DevGeom dg{};
   int n_lv = 0, n_pv = 0, n_place = 0, max_depth = 0, world_lv = 0;
-  bool has_bool = false;  // some LV is a composite: navigation runs the kernels built with composite code
+  bool has_bool = false;     // some LV is a composite
+  int kind = kElementary;    // SolidKind: which navigation kernels run
   std::vector<int> lv_type, lv_par;
   void* dmem = nullptr;
   // nav_transport workspace (grown on demand)
@@ -842,6 +843,9 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
     g->world_lv = world;
     g->lv_type = lv_type;
     g->has_bool = std::find(lv_type.begin(), lv_type.end(), (int)kBool) != lv_type.end();
+    g->kind = g->has_bool ? kComposites
+              : std::all_of(lv_type.begin(), lv_type.end(), [](int t) { return t == kBox || t == kTubs; }) ? kBoxTubs
+                                                                                                         : kElementary;
     g->lv_par = lv_par;
     *out = g;
     t_err.clear();
@@ -914,6 +918,9 @@ int check_i32(const char* fn, const char* name, const void* p, bool nullable = f
   if (!al4(p)) return fail(GV_EINVAL, "%s: %s is not 4-byte aligned", fn, name);
   return GV_OK;
 }
+
+// The instance of a kernel for a geometry's solids.
+#define GV_KIND(kern, kind) ((kind) == kBoxTubs ? kern<kBoxTubs> : (kind) == kElementary ? kern<kElementary> : kern<kComposites>)
 
 constexpr int kBlock = 256;
 
@@ -1108,7 +1115,7 @@ extern "C" int basket_locate(gv_geom* g, int64_t n, const double* x, const doubl
   GV_TRY(check_f64(fn, "z", z));
   GV_TRY(check_i32(fn, "out_pv", out_pv));
   DeviceGuard dgd(g->device);
-  hipLaunchKernelGGL(g->has_bool ? k_locate<true> : k_locate<false>, dim3(lane_shape(g, n).grid), dim3(lane_shape(g, n).block), 0, (hipStream_t)stream, g->dg, n, x, y, z, out_pv);
+  hipLaunchKernelGGL(GV_KIND(k_locate, g->kind), dim3(lane_shape(g, n).grid), dim3(lane_shape(g, n).block), 0, (hipStream_t)stream, g->dg, n, x, y, z, out_pv);
   return launched(fn);
 }
 
@@ -1129,7 +1136,7 @@ extern "C" int basket_step(gv_geom* g, int64_t n, const double* x, const double*
   GV_TRY(check_i32(fn, "out_next_pv", out_next_pv));
   GV_TRY(check_i32(fn, "out_flags", out_flags, true));
   DeviceGuard dgd(g->device);
-  const auto kern = step_nav_kernel(g->has_bool, precision == GV_FP32_REFINE);
+  const auto kern = step_nav_kernel(g->kind, precision == GV_FP32_REFINE);
   hipLaunchKernelGGL(kern, dim3(lane_shape(g, n).grid), dim3(lane_shape(g, n).block), 0,
                      (hipStream_t)stream, g->dg, n, x, y, z, dx, dy, dz, pv, pstep, out_step, out_next_pv, out_flags);
   return launched(fn);
@@ -1147,8 +1154,7 @@ extern "C" int basket_nav_safety(gv_geom* g, int64_t n, const double* x, const d
   GV_TRY(check_i32(fn, "pv", pv));
   GV_TRY(check_f64(fn, "out", out));
   DeviceGuard dgd(g->device);
-  const auto kern = g->has_bool ? (precision == GV_FP64 ? k_nav_safety<true> : k_nav_safety_scr<true>)
-                                : (precision == GV_FP64 ? k_nav_safety<false> : k_nav_safety_scr<false>);
+  const auto kern = precision == GV_FP64 ? GV_KIND(k_nav_safety, g->kind) : GV_KIND(k_nav_safety_scr, g->kind);
   hipLaunchKernelGGL(kern, dim3(lane_shape(g, n).grid), dim3(lane_shape(g, n).block), 0,
                      (hipStream_t)stream, g->dg, n, x, y, z, pv, out);
   return launched(fn);
@@ -1165,7 +1171,7 @@ extern "C" int basket_nav_inside(gv_geom* g, int64_t n, const double* x, const d
   GV_TRY(check_i32(fn, "pv", pv));
   if (!out) return fail(GV_EINVAL, "%s: out is NULL", fn);
   DeviceGuard dgd(g->device);
-  hipLaunchKernelGGL(g->has_bool ? k_nav_inside<true> : k_nav_inside<false>, dim3(lane_shape(g, n).grid), dim3(lane_shape(g, n).block), 0, (hipStream_t)stream, g->dg, n, x, y, z, pv,
+  hipLaunchKernelGGL(GV_KIND(k_nav_inside, g->kind), dim3(lane_shape(g, n).grid), dim3(lane_shape(g, n).block), 0, (hipStream_t)stream, g->dg, n, x, y, z, pv,
                      out);
   return launched(fn);
 }
@@ -1322,7 +1328,7 @@ int basket_transport(gv_geom* g, int64_t n, const double* x, const double* y, co
   TCtl& C = g->ctl;
   hipLaunchKernelGGL(k_bt_clear, dim3(1), dim3(kBlock), 0, s, C, nl);
   GV_TRY(launched(fn));
-  hipLaunchKernelGGL(g->has_bool ? k_bt_init<true> : k_bt_init<false>, dim3(sg), dim3(kBlock), 4 * (size_t)nl, s, g->dg, n, x, y, z, dx, dy, dz, start_pv,
+  hipLaunchKernelGGL(GV_KIND(k_bt_init, g->kind), dim3(sg), dim3(kBlock), 4 * (size_t)nl, s, g->dg, n, x, y, z, dx, dy, dz, start_pv,
                      max_steps, out_pv, out_nsteps, out_flags, g->nxt_lv, cb, C);
   GV_TRY(launched(fn));
   // live track ids in bucket order (into idx[1]), then slots in that order
@@ -1336,7 +1342,7 @@ int basket_transport(gv_geom* g, int64_t n, const double* x, const double* y, co
   double* ob_step = staged ? g->ob_step : nullptr;
   int* ob_pv = staged ? g->ob_pv : nullptr;
   int8_t* ob_proc = staged && phys && out_proc ? g->ob_proc : nullptr;
-  const auto step = step_kernel(g->has_bool, g->prof_work, fp32, phys, g->tune.step_waves == 3);
+  const auto step = step_kernel(g->kind, g->prof_work, fp32, phys, g->tune.step_waves == 3);
   const unsigned step_grid = step_grid_for(g, n);
   const size_t lds_sc = 8 * (size_t)nl + 4;
   // Every step up to max_steps is enqueued at once and the call returns: a
@@ -1450,18 +1456,22 @@ int lane_transport(gv_geom* g, const LaneCtl& L, int64_t n, const double* x, con
                    const double* dx, const double* dy, const double* dz, const int32_t* start_pv, int max_steps,
                    int32_t* out_pv, double* out_step, int32_t* out_nsteps, uint32_t* out_flags, bool fp32,
                    bool phys, PhysArgs P, int8_t* out_proc, hipStream_t s, const char* fn, bool events) {
-  const int h = std::min(sort_bits(g), kSortMaxBits);
+  // tracks of a geometry with composites start in several volumes: there the
+  // order is by start volume first, then by direction
+  int h = std::min(sort_bits(g), kSortMaxBits);
   const bool sorted = h > 0;
-  const int cells = sorted ? 1 << (2 * h) : 0;
-  const Shape sh = lane_shape(g, start_pv ? cells : n);
-  hipLaunchKernelGGL(g->has_bool ? k_ls_begin<true> : k_ls_begin<false>, dim3(sh.grid), dim3(sh.block), 0, s, g->dg, n,
-                     start_pv ? (const double*)nullptr : x, y, z, L, cells);
+  const int lvs = sorted && g->has_bool && g->n_lv <= kSortMaxCells / kStartBins ? g->n_lv : 0;
+  while (lvs > 0 && ((int64_t)(lvs * kStartBins) << (2 * h)) > kSortMaxCells) --h;
+  const int cells = sorted ? std::max(lvs * kStartBins, 1) << (2 * h) : 0;
+  const Shape sh = lane_shape(g, start_pv && lvs == 0 ? cells : n);
+  hipLaunchKernelGGL(GV_KIND(k_ls_begin, g->kind), dim3(sh.grid), dim3(sh.block), 0, s, g->dg, n, x, y,
+                     z, dx, dy, dz, start_pv, lvs > 0 ? 1 : 0, L, cells);
   GV_TRY(launched(fn));
   if (!start_pv) start_pv = L.pv0;
   if (sorted) {
     const unsigned cg = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 4095) / 4096, 256));
-    hipLaunchKernelGGL(k_ls_count, dim3(cg), dim3(1024), 4 * (size_t)cells, s, n, dx, dy, dz, h,
-                       g->tune.sort_key == 2 ? 1 : 0, L);
+    hipLaunchKernelGGL(k_ls_count, dim3(cg), dim3(1024), 4 * (size_t)cells, s, g->dg, n, dx, dy, dz, start_pv,
+                       h, g->tune.sort_key == 2 ? 1 : 0, lvs, L);
     GV_TRY(launched(fn));
     hipLaunchKernelGGL(k_ls_scan, dim3(1), dim3(1024), 0, s, L, cells);
     GV_TRY(launched(fn));
@@ -1479,7 +1489,7 @@ int lane_transport(gv_geom* g, const LaneCtl& L, int64_t n, const double* x, con
   const bool stage = g->tune.lane_stage ? g->tune.lane_stage == 2 : true;
   // per-class scheduling by default (2.66 against 2.99 ms for navigation,
   // 7.6 against 9.5 ms physics-limited, on the detector workload)
-  const LaneKernel k = lane_kernel(g->has_bool, fp32, phys, waves, stage, g->tune.lane_sched != 1);
+  const LaneKernel k = lane_kernel(g->kind, fp32, phys, waves, stage, g->tune.lane_sched != 1);
   int64_t grid = g->tune.lane_grid > 0 ? g->tune.lane_grid
                                        : (int64_t)resident_blocks(g, reinterpret_cast<const void*>(k)) * g->n_cu;
   grid = std::max<int64_t>(1, std::min<int64_t>(grid, (n + 255) / 256));
@@ -1542,11 +1552,9 @@ int transport_common(const char* fn, gv_geom* g, int64_t n, const double* x, con
   DeviceGuard dgd(g->device);
   const bool fp32 = precision == GV_FP32_REFINE;
   const hipStream_t s = (hipStream_t)stream;
-  // the basket form when it is asked for (or its work counters are), and by
-  // default for geometries holding composites (their tracks start in several
-  // volumes, which a direction order mixes in every wavefront: 2.9 ms against
-  // 3.7 ms for the lane form on the composite workload); else the lane form
-  const bool basket = g->tune.transport == 1 || g->prof_work || (g->tune.transport == 0 && g->has_bool);
+  // the basket form when it is asked for (or its work counters are), else the
+  // lane form
+  const bool basket = g->tune.transport == 1 || g->prof_work;
   if (basket && n >= kBasketMin && g->n_lv <= 4096)
     return basket_transport(g, n, x, y, z, dx, dy, dz, start_pv, max_steps, out_pv, out_step, out_nsteps, out_flags,
                             fp32, phys, P, out_proc, s);

@@ -157,7 +157,7 @@ __device__ __forceinline__ int dir_cell(double dx, double dy, double dz, int cb)
 // counts of the first list (per-workgroup LDS histogram, 4 nb bytes of dynamic
 // LDS).  Tracks that start outside the world finish here with zero steps and
 // get bucket -1.
-template <bool B>
+template <int K>
 __global__ void k_bt_init(DevGeom G, int64_t n, const double* __restrict__ x, const double* __restrict__ y,
                           const double* __restrict__ z, const double* __restrict__ dx, const double* __restrict__ dy,
                           const double* __restrict__ dz, const int32_t* __restrict__ start_pv, int max_steps,
@@ -175,7 +175,7 @@ __global__ void k_bt_init(DevGeom G, int64_t n, const double* __restrict__ x, co
     if (act) {
       uint32_t fl = 0;
       V3 p = ld3(x, y, z, i);
-      int v = start_pv ? start_pv[i] : locate<B>(G, p);
+      int v = start_pv ? start_pv[i] : locate<K>(G, p);
       if (v < -1 || v >= G.n_pv) {
         v = -1;
         fl = kFlagLocateFail;
@@ -448,7 +448,7 @@ static __global__ void __launch_bounds__(1024) k_bt_scatter(const int* __restric
 // ballot and an LDS atomic per counted event); the production instance counts
 // nothing.  The kernel leaves at once when its list is empty (len_cur), so the
 // host may enqueue every step up to the bound without looking at the device.
-template <bool F32, bool PHYS, bool B, bool WK, int WV>
+template <bool F32, bool PHYS, int K, bool WK, int WV>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) k_bt_step(DevGeom G, int k, int max_steps, int cb, const int* __restrict__ idx,
                                                   const int* __restrict__ len_cur,
                                                   TRec* __restrict__ rec, const int* __restrict__ cnt_cur,
@@ -514,10 +514,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
       double st;
       bool exited = false;
       if (PHYS) {
-        st = step_physics<F32, B>(G, b, r.pv, p, d, (uint32_t)id, k, P, r.safe, &nx, &proc, &fl, w,
+        st = step_physics<F32, K>(G, b, r.pv, p, d, (uint32_t)id, k, P, r.safe, &nx, &proc, &fl, w,
                                   zfc_left(r.zfc), &exited);
       } else {
-        st = step_culled<F32, B>(G, b, r.pv, p, d, &nx, &fl, w, zfc_left(r.zfc), &exited);
+        st = step_culled<F32, K>(G, b, r.pv, p, d, &nx, &fl, w, zfc_left(r.zfc), &exited);
         p = advance(p, st, d);
       }
       // leaving pv into its mother: pv's placement index goes along (see the lane form)

@@ -1,4 +1,4 @@
-// Lane transport: navigation with FP32 screens.
+// Lane transport of elementary solids: navigation with FP32 screens.
 #include "gv_inst.h"
 
 namespace gv {

@@ -1,4 +1,4 @@
-// Lane transport: physics-limited with FP32 screens.
+// Lane transport of elementary solids: physics-limited with FP32 screens.
 #include "gv_inst.h"
 
 namespace gv {

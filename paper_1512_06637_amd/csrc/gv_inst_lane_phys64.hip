@@ -1,4 +1,4 @@
-// Lane transport: physics-limited, FP64.
+// Lane transport of elementary solids: physics-limited, FP64.
 #include "gv_inst.h"
 
 namespace gv {

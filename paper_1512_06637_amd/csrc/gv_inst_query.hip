@@ -3,11 +3,14 @@
 
 namespace gv {
 
-StepNavKernel step_nav_kernel(bool has_bool, bool fp32) {
-  if (has_bool) return fp32 ? k_step_nav<true, true> : k_step_nav<false, true>;
-  return fp32 ? k_step_nav<true, false> : k_step_nav<false, false>;
+StepNavKernel step_nav_kernel(int kind, bool fp32) {
+  if (kind == kBoxTubs) return fp32 ? k_step_nav<true, kBoxTubs> : k_step_nav<false, kBoxTubs>;
+  if (kind == kElementary) return fp32 ? k_step_nav<true, kElementary> : k_step_nav<false, kElementary>;
+  return fp32 ? k_step_nav<true, kComposites> : k_step_nav<false, kComposites>;
 }
 
-ServeKernel serve_kernel(bool has_bool) { return has_bool ? k_serve<true> : k_serve<false>; }
+ServeKernel serve_kernel(int kind) {
+  return kind == kBoxTubs ? k_serve<kBoxTubs> : kind == kElementary ? k_serve<kElementary> : k_serve<kComposites>;
+}
 
 }  // namespace gv

@@ -86,31 +86,82 @@ struct LaneCtl {
   uint32_t* queue;  // [1] next place to hand out
 };
 
-// Before a transport: zeroes the key counts and the work counter, and locates
-// the tracks whose start volume the caller does not give (x not NULL).  With the
-// point lookup inside the transport kernel instead, its code took registers
-// from the step loop (1.89 against 1.85 ms per 2^20-track detector transport);
-// here it runs at full occupancy.
-template <bool B>
-__global__ void k_ls_begin(DevGeom G, int64_t n, const double* __restrict__ x, const double* __restrict__ y,
-                           const double* __restrict__ z, LaneCtl L, int cells) {
-  for (int64_t i = gtid(); i < cells; i += gstride()) L.cnt[i] = 0u;
-  if (gtid() == 0) *L.queue = 0u;
-  if (!x) return;
-  for (int64_t i = gtid(); i < n; i += gstride()) L.pv0[i] = locate<B>(G, ld3(x, y, z, i));
+// Geometries with composites: tracks start in several volumes, and a step
+// there costs what the few daughters on its way cost (a polycone minus a cone
+// takes 20 us of a wavefront's time).  So the tracks are ordered by start
+// volume, then by what their first step will evaluate, then by direction, and
+// in each iteration the lanes of one volume step together (8 % of lanes active
+// per VALU instruction without the bins, 23 % with them; 500,009 tracks: 990
+// and 617 us; basket form 1,867 us, most of it 128 step launches for tracks
+// that take 1.7 steps).  The kernel waits on dependent instructions most of
+// its time at any register budget; 2 waves per SIMD (252 VGPRs) spill least:
+// 617 us against 763 at 3 and 920 at 4.
+//
+// Start bin of a track in an LV whose daughters are found by their boxes: 0 no
+// daughter box on its way, else which daughter's box it enters first and
+// whether it enters more than one.
+constexpr int kStartBins = 32;
+__device__ __forceinline__ uint32_t start_bin(const DevGeom& G, int pv, V3 p, V3 d) {
+  const int lv = G.pv_lv[pv], off = G.lv_dau_off[lv], cnt = G.lv_dau_cnt[lv];
+  if (G.lv_loc[lv] != kLocBox) return 0;
+  CQ X = G.pv_gxf + 12 * (size_t)pv;
+  const V3 pl = to_child_p(X, p), dl = to_child_d(X, d);
+  const V3 inv{inv_dir64(dl.x), inv_dir64(dl.y), inv_dir64(dl.z)};
+  const V3 pin{-pl.x * inv.x, -pl.y * inv.y, -pl.z * inv.z};
+  double best = GV_INF;
+  int bk = -1, hits = 0;
+  for (int k = 0; k < cnt; ++k) {
+    const double t = box_entry64(G.dau_box + 6 * (size_t)(off + k), inv, pin);
+    if (!(t < GV_INF)) continue;
+    ++hits;
+    if (t < best) {
+      best = t;
+      bk = k;
+    }
+  }
+  return bk < 0 ? 0 : 1 + 2 * (bk % 15) + (hits > 1 ? 1 : 0);
 }
 
-// Key of every track (z-axis or octahedral) and the per-key counts
+// Before a transport: zeroes the key counts and the work counter, and locates
+// the tracks whose start volume the caller does not give.  With the
+// point lookup inside the transport kernel instead, its code took registers
+// from the step loop (1.89 against 1.85 ms per 2^20-track detector transport);
+// here it runs at full occupancy.  bins: also each track's start bin, into its
+// key.
+template <int K>
+__global__ void k_ls_begin(DevGeom G, int64_t n, const double* __restrict__ x, const double* __restrict__ y,
+                           const double* __restrict__ z, const double* __restrict__ dx,
+                           const double* __restrict__ dy, const double* __restrict__ dz,
+                           const int32_t* __restrict__ start_pv, int bins, LaneCtl L, int cells) {
+  for (int64_t i = gtid(); i < cells; i += gstride()) L.cnt[i] = 0u;
+  if (gtid() == 0) *L.queue = 0u;
+  if (start_pv && !bins) return;
+  for (int64_t i = gtid(); i < n; i += gstride()) {
+    const V3 p = ld3(x, y, z, i);
+    const int pv = start_pv ? start_pv[i] : locate<K>(G, p);
+    if (!start_pv) L.pv0[i] = pv;
+    if (bins) L.key[i] = pv >= 0 && pv < G.n_pv ? start_bin(G, pv, p, ld3(dx, dy, dz, i)) : 0u;
+  }
+}
+
+// Key of every track (z-axis or octahedral cell; when lvs > 0, for tracks that
+// start in several volumes, below the logical volume it starts in and its start
+// bin, which its key holds on entry) and the per-key counts
 // (workgroup histogram in LDS, 4 cells bytes of dynamic LDS, one global
 // atomic per workgroup and key).
-static __global__ void k_ls_count(int64_t n, const double* __restrict__ dx, const double* __restrict__ dy,
-                           const double* __restrict__ dz, int h, int zaxis, LaneCtl L) {
+static __global__ void k_ls_count(DevGeom G, int64_t n, const double* __restrict__ dx, const double* __restrict__ dy,
+                                  const double* __restrict__ dz, const int32_t* __restrict__ start_pv, int h,
+                                  int zaxis, int lvs, LaneCtl L) {
   extern __shared__ uint32_t key_hist[];
-  const int cells = 1 << (2 * h);
+  const int cells = max(lvs * kStartBins, 1) << (2 * h);
   for (int c = threadIdx.x; c < cells; c += blockDim.x) key_hist[c] = 0u;
   __syncthreads();
   for (int64_t i = gtid(); i < n; i += gstride()) {
-    const uint32_t k = zaxis ? direction_key_zaxis(dx[i], dy[i], dz[i], h) : direction_key(dx[i], dy[i], dz[i], h);
+    uint32_t k = zaxis ? direction_key_zaxis(dx[i], dy[i], dz[i], h) : direction_key(dx[i], dy[i], dz[i], h);
+    if (lvs > 0) {
+      const int pv = start_pv[i];
+      if (pv >= 0 && pv < G.n_pv) k |= ((uint32_t)G.pv_lv[pv] * kStartBins + L.key[i]) << (2 * h);
+    }
     L.key[i] = k;
     atomicAdd(&key_hist[k], 1u);
   }
@@ -222,7 +273,7 @@ struct LaneStage {
 // of a lane come in runs of consecutive addresses; all lanes of a wavefront
 // that started together write their runs in the same iteration, and a full
 // run goes out in 16-byte stores (its process codes in one 8-byte store).
-template <bool F32, bool PHYS, bool B, int ST>
+template <bool F32, bool PHYS, int K, int ST>
 __device__ __forceinline__ bool lane_step(const DevGeom& G, LaneTrack& T, int lv, int pv, int max_steps,
                                           int32_t* __restrict__ out_pv, double* __restrict__ out_step,
                                           int32_t* __restrict__ out_nsteps, uint32_t* __restrict__ out_flags,
@@ -234,7 +285,7 @@ __device__ __forceinline__ bool lane_step(const DevGeom& G, LaneTrack& T, int lv
   bool exited = false;
   if (PHYS) {
     int proc;
-    st = step_physics<F32, B>(G, lv, pv, T.p, T.d, (uint32_t)T.i, T.k, P, T.safe, &nx, &proc, &T.fl, w, T.left,
+    st = step_physics<F32, K>(G, lv, pv, T.p, T.d, (uint32_t)T.i, T.k, P, T.safe, &nx, &proc, &T.fl, w, T.left,
                               &exited);
     if (ST == 0) {
       if (out_proc) out_proc[(size_t)T.i * max_steps + T.k] = (int8_t)proc;
@@ -242,7 +293,7 @@ __device__ __forceinline__ bool lane_step(const DevGeom& G, LaneTrack& T, int lv
       T.procs |= (uint64_t)(uint8_t)proc << (8 * (T.k % 8));
     }
   } else {
-    st = step_culled<F32, B>(G, lv, pv, T.p, T.d, &nx, &T.fl, w, T.left, &exited);
+    st = step_culled<F32, K>(G, lv, pv, T.p, T.d, &nx, &T.fl, w, T.left, &exited);
     T.p = advance(T.p, st, T.d);
   }
   // a track that leaves pv into its mother carries pv's placement index there
@@ -323,7 +374,7 @@ __device__ __forceinline__ bool lane_step(const DevGeom& G, LaneTrack& T, int lv
 // run the same branch separately.  Giving a lane whose track has ended the
 // next track at once, which let its new track wait for its class like any
 // other, was measured slower as well: 2.66 against 2.56 ms.)
-template <bool F32, bool PHYS, bool B, int WV, int ST, bool CLS = false>
+template <bool F32, bool PHYS, int K, int WV, int ST, bool CLS = false>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) k_lane_transport(
     DevGeom G, int64_t n, const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
     const double* __restrict__ dx, const double* __restrict__ dy, const double* __restrict__ dz,
@@ -350,7 +401,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
     }
     if (!CLS) {
       if (live)
-        while (!lane_step<F32, PHYS, B, ST>(G, T, G.pv_lv[T.pv], T.pv, max_steps, out_pv, out_step, out_nsteps,
+        while (!lane_step<F32, PHYS, K, ST>(G, T, G.pv_lv[T.pv], T.pv, max_steps, out_pv, out_step, out_nsteps,
                                             out_flags, P, out_proc, S)) {
         }
       continue;
@@ -360,7 +411,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
       if (live) {  // volume and class in one load
         const unsigned long long lc = reinterpret_cast<CQL>(G.pv_lc)[T.pv];
         lv = (int)(uint32_t)lc;
-        cl = (int)(uint32_t)(lc >> 32);
+        cl = K == kComposites ? lv : (int)(uint32_t)(lc >> 32);  // composites: each volume is a class of its own
       }
       // the class most live lanes are in (few classes are present at once;
       // on equal counts the first found)
@@ -384,23 +435,29 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
       const bool mine = live && cl == best;
       const int lead = __ffsll((unsigned long long)__ballot(mine)) - 1;
       const int lv0 = __builtin_amdgcn_readlane(lv, lead);
+      if (K == kComposites) {  // one volume at a time
+        if (mine)
+          live = !lane_step<F32, PHYS, K, ST>(G, T, lv0, T.pv, max_steps, out_pv, out_step, out_nsteps, out_flags, P,
+                                              out_proc, S);
+        continue;
+      }
       const bool uni_lv = __ballot(mine && lv != lv0) == 0;
       if (!PHYS && uni_lv) {
         const int pv0 = __builtin_amdgcn_readlane(T.pv, lead);
         if (__ballot(mine && T.pv != pv0) == 0) {
           if (mine)
-            live = !lane_step<F32, PHYS, B, ST>(G, T, lv0, pv0, max_steps, out_pv, out_step, out_nsteps, out_flags,
+            live = !lane_step<F32, PHYS, K, ST>(G, T, lv0, pv0, max_steps, out_pv, out_step, out_nsteps, out_flags,
                                                 P, out_proc, S);
         } else if (mine) {
-          live = !lane_step<F32, PHYS, B, ST>(G, T, lv0, T.pv, max_steps, out_pv, out_step, out_nsteps, out_flags, P,
+          live = !lane_step<F32, PHYS, K, ST>(G, T, lv0, T.pv, max_steps, out_pv, out_step, out_nsteps, out_flags, P,
                                               out_proc, S);
         }
       } else if (uni_lv) {
         if (mine)
-          live = !lane_step<F32, PHYS, B, ST>(G, T, lv0, T.pv, max_steps, out_pv, out_step, out_nsteps, out_flags, P,
+          live = !lane_step<F32, PHYS, K, ST>(G, T, lv0, T.pv, max_steps, out_pv, out_step, out_nsteps, out_flags, P,
                                               out_proc, S);
       } else if (mine) {
-        live = !lane_step<F32, PHYS, B, ST>(G, T, lv, T.pv, max_steps, out_pv, out_step, out_nsteps, out_flags, P,
+        live = !lane_step<F32, PHYS, K, ST>(G, T, lv, T.pv, max_steps, out_pv, out_step, out_nsteps, out_flags, P,
                                             out_proc, S);
       }
     }

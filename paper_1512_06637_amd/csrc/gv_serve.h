@@ -116,7 +116,7 @@ int server_launch(gv_server* s, int k) {
   const auto rout = runs(R.bs, [](const gv_server::Bk& b) { return std::make_pair(b.out_off, b.out_len); });
   gv::SDesc* dd = s->d_desc + (size_t)k * s->slots;
   const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((tiles + 3) / 4, 2048));
-  auto kernel = gv::serve_kernel(s->g->has_bool);
+  auto kernel = gv::serve_kernel(s->g->kind);
   if (s->graphs && rin.size() <= 2 && rout.size() <= 2) {
     // one graph launch: the round's copies and kernel as the node parameters
     gv_server::RoundGraph& G = s->rg[k];
@@ -249,7 +249,7 @@ int server_round_graph(gv_server* s, int k) {
   char* dout = s->d_out;
   void* args[] = {&dg, &cdd, &nb, &tiles, &din, &dout};
   hipKernelNodeParams kp{};
-  kp.func = reinterpret_cast<void*>(gv::serve_kernel(s->g->has_bool));
+  kp.func = reinterpret_cast<void*>(gv::serve_kernel(s->g->kind));
   kp.gridDim = dim3(1);
   kp.blockDim = dim3(kBlock);
   kp.sharedMemBytes = 0;

@@ -25,6 +25,9 @@ constexpr double kHalf = 5e-10;
 #define GV_INF __builtin_huge_val()
 
 enum SolidType { kBox = 0, kTubs = 1, kCons = 2, kSphere = 3, kTrd = 4, kPcon = 5, kBool = 6 };
+// What solids a geometry holds, as far as kernels are instantiated for it:
+// boxes and tube segments only, any elementary solids, or composites as well.
+enum SolidKind { kBoxTubs = 0, kElementary = 1, kComposites = 2 };
 enum BoolOp { kUnion = 0, kSubtraction = 1, kIntersection = 2 };
 enum { kOutside = 0, kSurface = 1, kInside = 2 };
 
@@ -928,48 +931,58 @@ struct Bool {
   }
 };
 
+// A pointer that is the same in every active lane, as a wavefront-uniform value.
+__device__ __forceinline__ CQ uniform_ptr(CQ q) {
+  const uint64_t a = (uint64_t)q;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+  return (CQ)((uint64_t)hi << 32 | lo);
+}
+
 // Out-of-line entry points of the composite code for the navigation kernels
 // (inlined there it would set their register budget for every geometry); the
 // solid-level kernels, instantiated per solid type, inline Bool directly.
-struct BoolCall {
-  __device__ __noinline__ static double sgn(CQ q, V3 p) { return Bool::sgn(q, p); }
-  __device__ __noinline__ static double safety_in(CQ q, V3 p) { return Bool::safety_in(q, p); }
-  __device__ __noinline__ static double safety_out(CQ q, V3 p) { return Bool::safety_out(q, p); }
-  __device__ __noinline__ static double dist_in(CQ q, V3 p, V3 d) { return Bool::dist_in(q, p, d); }
-  __device__ __noinline__ static double dist_out(CQ q, V3 p, V3 d) { return Bool::dist_out(q, p, d); }
+struct BoolCall {  // q is the same in every active lane
+  __device__ __noinline__ static double sgn(CQ q, V3 p) { return Bool::sgn(uniform_ptr(q), p); }
+  __device__ __noinline__ static double safety_in(CQ q, V3 p) { return Bool::safety_in(uniform_ptr(q), p); }
+  __device__ __noinline__ static double safety_out(CQ q, V3 p) { return Bool::safety_out(uniform_ptr(q), p); }
+  __device__ __noinline__ static double dist_in(CQ q, V3 p, V3 d) { return Bool::dist_in(uniform_ptr(q), p, d); }
+  __device__ __noinline__ static double dist_out(CQ q, V3 p, V3 d) { return Bool::dist_out(uniform_ptr(q), p, d); }
 };
 
-// Any solid.  B: the geometry may hold composites.  Kernels instantiated with
-// B false (geometries of elementary solids only) contain no composite code.
-template <bool B>
-__device__ __forceinline__ double solid_sgn(int type, CQ q, V3 p) {
-  if constexpr (B)
-    if (type == kBool) return BoolCall::sgn(q, p);
-  return prim_sgn(type, q, p);
+// Any solid of a geometry of kind K.  Kernels instantiated for a kind contain
+// no code of solids beyond it: the registers that code needs would bound the
+// step loops of every geometry (the mixed-type daughter loop's box test alone
+// took the detector's transport from 1.87 to 2.27 ms while it shared a kernel
+// with cones, spheres, Trds and polycones).
+// Composites run one solid at a time: the lanes whose solid is that of the first
+// active lane run it with its table as a wavefront-uniform value (scalar loads
+// of the parameters, one branch of the type switches), then the next solid's.
+// Different composites take different paths anyway, and through per-lane
+// table pointers every parameter was a gather and every branch a mask.
+template <class F>
+__device__ __forceinline__ double one_solid_at_a_time(int type, CQ q, F f) {
+  for (;;) {
+    CQ u = uniform_ptr(q);
+    if (u == q) return f(__builtin_amdgcn_readfirstlane(type), u);
+  }
 }
-template <bool B>
-__device__ __forceinline__ double solid_dist_in(int type, CQ q, V3 p, V3 d) {
-  if constexpr (B)
-    if (type == kBool) return BoolCall::dist_in(q, p, d);
-  return prim_dist_in(type, q, p, d);
-}
-template <bool B>
-__device__ __forceinline__ double solid_dist_out(int type, CQ q, V3 p, V3 d) {
-  if constexpr (B)
-    if (type == kBool) return BoolCall::dist_out(q, p, d);
-  return prim_dist_out(type, q, p, d);
-}
-template <bool B>
-__device__ __forceinline__ double solid_safety_in(int type, CQ q, V3 p) {
-  if constexpr (B)
-    if (type == kBool) return BoolCall::safety_in(q, p);
-  return prim_safety_in(type, q, p);
-}
-template <bool B>
-__device__ __forceinline__ double solid_safety_out(int type, CQ q, V3 p) {
-  if constexpr (B)
-    if (type == kBool) return BoolCall::safety_out(q, p);
-  return prim_safety_out(type, q, p);
-}
+#define GV_ANY_SOLID(name, args, ...)                                                       \
+  template <int K>                                                                          \
+  __device__ __forceinline__ double solid_##name args {                                     \
+    if constexpr (K == kComposites)                                                         \
+      return one_solid_at_a_time(type, q, [&](int t, CQ u) {                                \
+        return t == kBool ? BoolCall::name(u, __VA_ARGS__) : prim_##name(t, u, __VA_ARGS__); \
+      });                                                                                   \
+    if constexpr (K == kBoxTubs)                                                            \
+      return type == kBox ? Box::name(q, __VA_ARGS__) : Tubs::name(q, __VA_ARGS__);         \
+    return prim_##name(type, q, __VA_ARGS__);                                               \
+  }
+GV_ANY_SOLID(sgn, (int type, CQ q, V3 p), p)
+GV_ANY_SOLID(dist_in, (int type, CQ q, V3 p, V3 d), p, d)
+GV_ANY_SOLID(dist_out, (int type, CQ q, V3 p, V3 d), p, d)
+GV_ANY_SOLID(safety_in, (int type, CQ q, V3 p), p)
+GV_ANY_SOLID(safety_out, (int type, CQ q, V3 p), p)
+#undef GV_ANY_SOLID
 
 }  // namespace gv

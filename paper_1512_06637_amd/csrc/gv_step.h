@@ -133,6 +133,16 @@ __device__ __forceinline__ bool box_hit64(CQ B, V3 inv, V3 pin, double bound) {
   return !(nr > fr || fr < 0.0 || nr > bound);
 }
 
+// The parameter >= 0 at which a ray enters a padded box, +inf when it misses it.
+__device__ __forceinline__ double box_entry64(CQ B, V3 inv, V3 pin) {
+  const double ax = fma(B[0], inv.x, pin.x), bx = fma(B[3], inv.x, pin.x);
+  const double ay = fma(B[1], inv.y, pin.y), by = fma(B[4], inv.y, pin.y);
+  const double az = fma(B[2], inv.z, pin.z), bz = fma(B[5], inv.z, pin.z);
+  const double nr = fmax(fmax(fmin(ax, bx), fmin(ay, by)), fmax(fmin(az, bz), 0.0));
+  const double fr = fmin(fmin(fmax(ax, bx), fmax(ay, by)), fmax(az, bz));
+  return nr > fr ? GV_INF : nr;
+}
+
 // The same test in FP32.  The FP32 boxes are the FP64 ones widened by
 // delta = 128 u (S + |box|inf), S of the mother, u = 2^-24, which covers the
 // rounding of the point, of the direction over a parameter up to 4 S and of
@@ -434,12 +444,12 @@ __device__ __forceinline__ void daughters_phi(const DevGeom& G, int lv, int m0, 
 // left: placement index of a box daughter of lv the track has left along its
 // present line (-1: none), which the ray cannot meet again; *exited (if given)
 // says whether the step ends at the mother's exit.
-template <bool F32, bool B, class W>
+template <bool F32, int K, class W>
 __device__ __forceinline__ double step_culled(const DevGeom& G, int lv, int pv, V3 p, V3 d, int* next,
                                               uint32_t* flags, W& w, int left = -1, bool* exited = nullptr) {
   CQ X = G.pv_gxf + 12 * (size_t)pv;
   V3 pl = to_child_p(X, p), dl = to_child_d(X, d);
-  double dout = solid_dist_out<B>(G.lv_type[lv], G.par + G.lv_par[lv], pl, dl);
+  double dout = solid_dist_out<K>(G.lv_type[lv], G.par + G.lv_par[lv], pl, dl);
   uint32_t fl = *flags;
   if (dout < 0.0) {
     dout = 0.0;
@@ -467,12 +477,22 @@ __device__ __forceinline__ double step_culled(const DevGeom& G, int lv, int pv, 
     daughters_of_type<Tubs>(G, off, cnt, pl, dl, best, bestk, neg);
     w.add(kWorkPlain + kTubs, (unsigned)cnt);
   } else {
+    // mixed daughters: one whose padded box the ray misses, or enters beyond
+    // the exit or the best daughter so far, cannot be entered first (finite
+    // rays and rotations only, as in point lookups)
+    const bool cull = loc_mode(G, lv, pl) == kLocBox && dl.x * dl.x + dl.y * dl.y + dl.z * dl.z < 4.0;
+    V3 inv{}, pin{};
+    if (cull) {
+      inv = V3{inv_dir64(dl.x), inv_dir64(dl.y), inv_dir64(dl.z)};
+      pin = V3{-pl.x * inv.x, -pl.y * inv.y, -pl.z * inv.z};
+    }
     for (int k = 0; k < cnt; ++k) {
+      if (cull && !box_hit64(G.dau_box + 6 * (size_t)(off + k), inv, pin, fmin(best, dout) + kTol)) continue;
       CQ Y = G.dau_xf + 12 * (size_t)(off + k);
       const int clv = G.dau_lv[off + k];
       V3 pc = to_child_p(Y, pl), dc = to_child_d(Y, dl);
       const int ct = G.lv_type[clv];
-      double t = solid_dist_in<B>(ct, G.par + G.lv_par[clv], pc, dc);
+      double t = solid_dist_in<K>(ct, G.par + G.lv_par[clv], pc, dc);
       if (ct <= kPcon) w.add(kWorkPlain + ct);  // composites have no counter
       neg = neg || t < 0.0;
       t = fmax(t, 0.0);
@@ -496,11 +516,11 @@ __device__ __forceinline__ double step_culled(const DevGeom& G, int lv, int pv, 
 
 // ComputeStep with a physics limit: as step_culled, then the physics length
 // wins when it is below both the daughter minimum and the exit.
-template <bool F32, bool B, class W>
+template <bool F32, int K, class W>
 __device__ __forceinline__ double step_culled_limited(const DevGeom& G, int pv, V3 p, V3 d, double pstep, int* next,
                                                       uint32_t* flags, W& w) {
   int nx;
-  const double s = step_culled<F32, B>(G, G.pv_lv[pv], pv, p, d, &nx, flags, w);
+  const double s = step_culled<F32, K>(G, G.pv_lv[pv], pv, p, d, &nx, flags, w);
   // s is the daughter minimum when a daughter was chosen, else the exit
   if (pstep < s) {
     *next = pv;
@@ -525,7 +545,7 @@ struct PhysArgs {
   int shortcut;
 };
 
-template <bool F32, bool B, class W>
+template <bool F32, int K, class W>
 __device__ __forceinline__ double step_physics(const DevGeom& G, int lv, int pv, V3& p, V3 d, uint32_t track, int k,
                                                const PhysArgs& P, double& safe, int* next, int* proc,
                                                uint32_t* flags, W& w, int left = -1, bool* exited = nullptr) {
@@ -542,7 +562,7 @@ __device__ __forceinline__ double step_physics(const DevGeom& G, int lv, int pv,
     return ps;
   }
   int nx;
-  const double sg = step_culled<F32, B>(G, lv, pv, p, d, &nx, flags, w, left, exited);  // min(best daughter, exit)
+  const double sg = step_culled<F32, K>(G, lv, pv, p, d, &nx, flags, w, left, exited);  // min(best daughter, exit)
   double st;
   if (ps < sg) {
     w.add(kWorkPhys);
@@ -566,14 +586,14 @@ __device__ __forceinline__ double step_physics(const DevGeom& G, int lv, int pv,
 // when its FP32 lower bound (minus its error) exceeds both the running minimum
 // and the surface half-band by kTolerance, i.e. when the point is provably
 // outside it and it cannot lower the minimum.  Equal to nav_safety bit for bit.
-template <bool B>
+template <int K>
 __device__ __forceinline__ double nav_safety_screened(const DevGeom& G, int pv, V3 p) {
   const int lv = G.pv_lv[pv];
   const V3 pl = to_child_p(G.pv_gxf + 12 * (size_t)pv, p);
   const int t = G.lv_type[lv];
   CQ q = G.par + G.lv_par[lv];
-  if (code_of(solid_sgn<B>(t, q, pl)) != kInside) return 0.0;
-  double s = solid_safety_out<B>(t, q, pl);
+  if (code_of(solid_sgn<K>(t, q, pl)) != kInside) return 0.0;
+  double s = solid_safety_out<K>(t, q, pl);
   if (safety_indexed(G, lv, pl, s)) return fmax(s, 0.0);
   const int off = G.lv_dau_off[lv], cnt = G.lv_dau_cnt[lv], dtype = G.lv_dau_type[lv];
   const F3 p32{(float)pl.x, (float)pl.y, (float)pl.z};
@@ -591,15 +611,15 @@ __device__ __forceinline__ double nav_safety_screened(const DevGeom& G, int pv, 
     const V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(off + k), pl);
     CQ qc = G.par + G.lv_par[clv];
     const int tc = G.lv_type[clv];
-    if (code_of(solid_sgn<B>(tc, qc, pc)) != kOutside) return 0.0;
-    s = fmin(s, solid_safety_in<B>(tc, qc, pc));
+    if (code_of(solid_sgn<K>(tc, qc, pc)) != kOutside) return 0.0;
+    s = fmin(s, solid_safety_in<K>(tc, qc, pc));
   }
   return fmax(s, 0.0);
 }
 
 // --------------------------------------------------------- per-lane kernels
 // ComputeStep for every track of a basket, each lane in its own volume.
-template <bool F32, bool B>
+template <bool F32, int K>
 __global__ void k_step_nav(DevGeom G, int64_t n, const double* __restrict__ x, const double* __restrict__ y,
                            const double* __restrict__ z, const double* __restrict__ dx, const double* __restrict__ dy,
                            const double* __restrict__ dz, const int32_t* __restrict__ pv,
@@ -612,7 +632,7 @@ __global__ void k_step_nav(DevGeom G, int64_t n, const double* __restrict__ x, c
     int nx = -1;
     double st = 0.0;
     if (v >= 0 && v < G.n_pv) {
-      st = step_culled_limited<F32, B>(G, v, ld3(x, y, z, i), ld3(dx, dy, dz, i), pstep ? pstep[i] : GV_INF, &nx, &fl,
+      st = step_culled_limited<F32, K>(G, v, ld3(x, y, z, i), ld3(dx, dy, dz, i), pstep ? pstep[i] : GV_INF, &nx, &fl,
                                     w);
     } else {
       fl = kFlagLocateFail;
@@ -623,13 +643,13 @@ __global__ void k_step_nav(DevGeom G, int64_t n, const double* __restrict__ x, c
   }
 }
 
-template <bool B>
+template <int K>
 __global__ void k_nav_safety_scr(DevGeom G, int64_t n, const double* __restrict__ x, const double* __restrict__ y,
                                  const double* __restrict__ z, const int32_t* __restrict__ pv,
                                  double* __restrict__ out) {
   for (int64_t i = gtid(); i < n; i += gstride()) {
     int v = pv[i];
-    out[i] = (v >= 0 && v < G.n_pv) ? nav_safety_screened<B>(G, v, ld3(x, y, z, i)) : 0.0;
+    out[i] = (v >= 0 && v < G.n_pv) ? nav_safety_screened<K>(G, v, ld3(x, y, z, i)) : 0.0;
   }
 }
 
