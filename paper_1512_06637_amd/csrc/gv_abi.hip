@@ -844,8 +844,9 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
     g->lv_type = lv_type;
     g->has_bool = std::find(lv_type.begin(), lv_type.end(), (int)kBool) != lv_type.end();
     g->kind = g->has_bool ? kComposites
-              : std::all_of(lv_type.begin(), lv_type.end(), [](int t) { return t == kBox || t == kTubs; }) ? kBoxTubs
-                                                                                                         : kElementary;
+                             : kBoxTube;
+    for (int i = 0; i < n_lv && g->kind == kBoxTube; ++i)
+      if (!(lv_type[i] == kBox || (lv_type[i] == kTubs && par[lv_par[i] + L::TB_PHI] == 0.0))) g->kind = kElementary;
     g->lv_par = lv_par;
     *out = g;
     t_err.clear();
@@ -920,7 +921,7 @@ int check_i32(const char* fn, const char* name, const void* p, bool nullable = f
 }
 
 // The instance of a kernel for a geometry's solids.
-#define GV_KIND(kern, kind) ((kind) == kBoxTubs ? kern<kBoxTubs> : (kind) == kElementary ? kern<kElementary> : kern<kComposites>)
+#define GV_KIND(kern, kind) ((kind) == kBoxTube ? kern<kBoxTube> : (kind) == kElementary ? kern<kElementary> : kern<kComposites>)
 
 constexpr int kBlock = 256;
 

@@ -91,10 +91,18 @@ __device__ __forceinline__ int phi_sector(double a) {
   return min(kPhiSectors - 1, max(0, (int)(a * (kPhiSectors / 4.0))));
 }
 
-// Radial entries with rmin^2 <= rho^2.
+// Radial entries with rmin^2 <= rho^2 (ascending).  Four at a time while every
+// active lane is past them, then one by one until no lane is: lanes that run
+// together mostly sit between the same two tubes.
 __device__ __forceinline__ int radial_rank(CQ R2, int cnt, double rho2) {
-  int j = 0;
-  for (int m = 0; m < cnt; ++m) j += R2[2 * m] <= rho2 ? 1 : 0;
+  int m = 0;
+  while (m + 4 <= cnt && __ballot(!(R2[2 * (m + 3)] <= rho2)) == 0) m += 4;
+  int j = m;
+  for (; m < cnt; ++m) {
+    const bool past = R2[2 * m] <= rho2;
+    if (__ballot(past) == 0) break;
+    j += past ? 1 : 0;
+  }
   return j;
 }
 

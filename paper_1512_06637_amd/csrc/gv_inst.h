@@ -29,7 +29,7 @@ StepKernel step_kernel_phys(int kind, bool work, bool fp32);
 
 // The lane-transport instance: the geometry's solids, FP32 screens or not,
 // physics-limited or not, the register budget (3 or 4 waves per SIMD), output
-// staging and per-class scheduling.  Boxes and tubes have instances of their
+// staging and per-class scheduling.  Boxes and full tubes have instances of their
 // own for the default shapes (staged, per-class scheduling, 4 waves for
 // navigation and 3 for physics) and share the elementary solids' otherwise;
 // geometries with composites run one shape per precision and physics.

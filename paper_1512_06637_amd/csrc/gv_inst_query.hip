@@ -4,13 +4,13 @@
 namespace gv {
 
 StepNavKernel step_nav_kernel(int kind, bool fp32) {
-  if (kind == kBoxTubs) return fp32 ? k_step_nav<true, kBoxTubs> : k_step_nav<false, kBoxTubs>;
+  if (kind == kBoxTube) return fp32 ? k_step_nav<true, kBoxTube> : k_step_nav<false, kBoxTube>;
   if (kind == kElementary) return fp32 ? k_step_nav<true, kElementary> : k_step_nav<false, kElementary>;
   return fp32 ? k_step_nav<true, kComposites> : k_step_nav<false, kComposites>;
 }
 
 ServeKernel serve_kernel(int kind) {
-  return kind == kBoxTubs ? k_serve<kBoxTubs> : kind == kElementary ? k_serve<kElementary> : k_serve<kComposites>;
+  return kind == kBoxTube ? k_serve<kBoxTube> : kind == kElementary ? k_serve<kElementary> : k_serve<kComposites>;
 }
 
 }  // namespace gv

@@ -265,7 +265,30 @@ struct LaneStage {
   int32_t* pv;
 };
 
-// One step of a carried track; returns true when the track has ended (left
+// What a step found: its length, the next volume, the acting process (physics,
+// -1: none), and whether it ends at the mother's exit.
+struct LaneStep {
+  double st;
+  int nx, proc;
+  bool exited;
+};
+
+// One ComputeStep of a carried track in volume pv (logical volume lv).
+template <bool F32, bool PHYS, int K>
+__device__ __forceinline__ void lane_compute(const DevGeom& G, LaneTrack& T, int lv, int pv, const PhysArgs& P,
+                                             LaneStep& R) {
+  NoWork w;
+  R.exited = false;
+  if (PHYS) {
+    R.st = step_physics<F32, K>(G, lv, pv, T.p, T.d, (uint32_t)T.i, T.k, P, T.safe, &R.nx, &R.proc, &T.fl, w, T.left,
+                                &R.exited);
+  } else {
+    R.st = step_culled<F32, K>(G, lv, pv, T.p, T.d, &R.nx, &T.fl, w, T.left, &R.exited);
+    T.p = advance(T.p, R.st, T.d);
+  }
+}
+
+// Records a carried track's step; returns true when the track has ended (left
 // the world, stuck, or out of steps), after writing its count and flags.
 // With ST > 0 the step length and next volume go to the lane's LDS column
 // (and a physics step's process code to a byte of T.procs) and are written
@@ -273,38 +296,32 @@ struct LaneStage {
 // of a lane come in runs of consecutive addresses; all lanes of a wavefront
 // that started together write their runs in the same iteration, and a full
 // run goes out in 16-byte stores (its process codes in one 8-byte store).
-template <bool F32, bool PHYS, int K, int ST>
-__device__ __forceinline__ bool lane_step(const DevGeom& G, LaneTrack& T, int lv, int pv, int max_steps,
-                                          int32_t* __restrict__ out_pv, double* __restrict__ out_step,
-                                          int32_t* __restrict__ out_nsteps, uint32_t* __restrict__ out_flags,
-                                          const PhysArgs& P, int8_t* __restrict__ out_proc, LaneStage S) {
+template <bool PHYS, int ST>
+__device__ __forceinline__ bool lane_record(const DevGeom& G, LaneTrack& T, const LaneStep& R, int max_steps,
+                                            int32_t* __restrict__ out_pv, double* __restrict__ out_step,
+                                            int32_t* __restrict__ out_nsteps, uint32_t* __restrict__ out_flags,
+                                            int8_t* __restrict__ out_proc, LaneStage S) {
   static_assert(ST == 0 || ST == 8, "a staged run is 8 steps (the process codes of a run fill 64 bits)");
-  NoWork w;
-  int nx;
-  double st;
-  bool exited = false;
+  constexpr int kRun = ST > 0 ? ST : 1;
+  const int nx = R.nx;
+  const double st = R.st;
   if (PHYS) {
-    int proc;
-    st = step_physics<F32, K>(G, lv, pv, T.p, T.d, (uint32_t)T.i, T.k, P, T.safe, &nx, &proc, &T.fl, w, T.left,
-                              &exited);
     if (ST == 0) {
-      if (out_proc) out_proc[(size_t)T.i * max_steps + T.k] = (int8_t)proc;
+      if (out_proc) out_proc[(size_t)T.i * max_steps + T.k] = (int8_t)R.proc;
     } else {
-      T.procs |= (uint64_t)(uint8_t)proc << (8 * (T.k % 8));
+      T.procs |= (uint64_t)(uint8_t)R.proc << (8 * (T.k % 8));
     }
-  } else {
-    st = step_culled<F32, K>(G, lv, pv, T.p, T.d, &nx, &T.fl, w, T.left, &exited);
-    T.p = advance(T.p, st, T.d);
   }
-  // a track that leaves pv into its mother carries pv's placement index there
-  // (the line does not change, so pv is behind it); entering a daughter clears it
-  if (nx != pv) T.left = exited ? G.pv_k[pv] : -1;
+  // a track that leaves its volume into the mother carries the volume's
+  // placement index there (the line does not change, so the volume is behind
+  // it); entering a daughter clears it
+  if (nx != T.pv) T.left = R.exited ? G.pv_k[T.pv] : -1;
   if (ST == 0) {
     out_step[(size_t)T.i * max_steps + T.k] = st;
     out_pv[(size_t)T.i * (max_steps + 1) + T.k + 1] = nx;
   } else {
-    S.st[64 * (T.k % ST)] = st;
-    S.pv[64 * (T.k % ST)] = nx;
+    S.st[64 * (T.k % kRun)] = st;
+    S.pv[64 * (T.k % kRun)] = nx;
   }
   ++T.k;
   bool end = nx < 0;
@@ -319,13 +336,13 @@ __device__ __forceinline__ bool lane_step(const DevGeom& G, LaneTrack& T, int lv
     }
   }
   T.pv = nx;
-  if (ST > 0 && (end || T.k % ST == 0)) {
-    const int m = (T.k - 1) % ST + 1, k0 = T.k - m;
+  if (ST > 0 && (end || T.k % kRun == 0)) {
+    const int m = (T.k - 1) % kRun + 1, k0 = T.k - m;
     double* rs = out_step + (size_t)T.i * max_steps + k0;
     int32_t* rp = out_pv + (size_t)T.i * (max_steps + 1) + k0 + 1;
     if (m == ST) {
-      double vs[ST > 0 ? ST : 1];
-      int32_t vp[ST > 0 ? ST : 1];
+      double vs[kRun];
+      int32_t vp[kRun];
       for (int j = 0; j < ST; ++j) {
         vs[j] = S.st[64 * j];
         vp[j] = S.pv[64 * j];
@@ -399,11 +416,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
       const int64_t i = perm ? perm[j] : j;
       live = lane_begin(G, T, i, x, y, z, dx, dy, dz, start_pv, max_steps, out_pv, out_nsteps, out_flags);
     }
+    LaneStep R;
     if (!CLS) {
-      if (live)
-        while (!lane_step<F32, PHYS, K, ST>(G, T, G.pv_lv[T.pv], T.pv, max_steps, out_pv, out_step, out_nsteps,
-                                            out_flags, P, out_proc, S)) {
-        }
+      while (live) {
+        lane_compute<F32, PHYS, K>(G, T, G.pv_lv[T.pv], T.pv, P, R);
+        live = !lane_record<PHYS, ST>(G, T, R, max_steps, out_pv, out_step, out_nsteps, out_flags, out_proc, S);
+      }
       continue;
     }
     for (uint64_t lm = __ballot(live); lm; lm = __ballot(live)) {
@@ -436,30 +454,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
       const int lead = __ffsll((unsigned long long)__ballot(mine)) - 1;
       const int lv0 = __builtin_amdgcn_readlane(lv, lead);
       if (K == kComposites) {  // one volume at a time
-        if (mine)
-          live = !lane_step<F32, PHYS, K, ST>(G, T, lv0, T.pv, max_steps, out_pv, out_step, out_nsteps, out_flags, P,
-                                              out_proc, S);
-        continue;
-      }
-      const bool uni_lv = __ballot(mine && lv != lv0) == 0;
-      if (!PHYS && uni_lv) {
+        if (mine) lane_compute<F32, PHYS, K>(G, T, lv0, T.pv, P, R);
+      } else {
+        const bool uni_lv = __ballot(mine && lv != lv0) == 0;
         const int pv0 = __builtin_amdgcn_readlane(T.pv, lead);
-        if (__ballot(mine && T.pv != pv0) == 0) {
-          if (mine)
-            live = !lane_step<F32, PHYS, K, ST>(G, T, lv0, pv0, max_steps, out_pv, out_step, out_nsteps, out_flags,
-                                                P, out_proc, S);
+        if (!PHYS && uni_lv && __ballot(mine && T.pv != pv0) == 0) {
+          if (mine) lane_compute<F32, PHYS, K>(G, T, lv0, pv0, P, R);
+        } else if (uni_lv) {
+          if (mine) lane_compute<F32, PHYS, K>(G, T, lv0, T.pv, P, R);
         } else if (mine) {
-          live = !lane_step<F32, PHYS, K, ST>(G, T, lv0, T.pv, max_steps, out_pv, out_step, out_nsteps, out_flags, P,
-                                              out_proc, S);
+          lane_compute<F32, PHYS, K>(G, T, lv, T.pv, P, R);
         }
-      } else if (uni_lv) {
-        if (mine)
-          live = !lane_step<F32, PHYS, K, ST>(G, T, lv0, T.pv, max_steps, out_pv, out_step, out_nsteps, out_flags, P,
-                                              out_proc, S);
-      } else if (mine) {
-        live = !lane_step<F32, PHYS, K, ST>(G, T, lv, T.pv, max_steps, out_pv, out_step, out_nsteps, out_flags, P,
-                                            out_proc, S);
       }
+      if (mine)
+        live = !lane_record<PHYS, ST>(G, T, R, max_steps, out_pv, out_step, out_nsteps, out_flags, out_proc, S);
     }
   }
 }

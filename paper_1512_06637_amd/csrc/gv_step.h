@@ -332,7 +332,7 @@ __device__ __forceinline__ void daughters_radial(const DevGeom& G, int r0, int o
   auto eval = [&](int m) {
     const int k = K[m];
     w.add(kWorkFull + kTubs);
-    double t = Tubs::dist_in(G.par + G.dau_par[off + k], pl, dl);
+    double t = Tubs::full_dist<true>(G.par + G.dau_par[off + k], pl, dl);
     neg = neg || t < 0.0;
     t = fmax(t, 0.0);
     if (t < best || (t == best && k < bestk)) {
@@ -342,25 +342,42 @@ __device__ __forceinline__ void daughters_radial(const DevGeom& G, int r0, int o
   };
   auto beyond = [&](double t) { return t - 1e-6 - 1e-12 * t > fmin(best, dout) + kTol; };
   const bool holds = j > 0 && rho2 <= R2[2 * (j - 1) + 1];
-  if (holds && !(B >= 0.0 && R2[2 * (j - 1) + 1] - rho2 < 0.25 * kTol * B)) eval(j - 1);
-  if (!(A > 0.0)) return;  // parallel to the axis: the radius never changes
-  for (int m = j; m < cnt; ++m) {  // outward: larger root of A t^2 + 2 B t + (rho^2 - rmin^2), C < 0
-    const double C = rho2 - R2[2 * m];
-    const double sq = sqrt(B * B - A * C);
-    const double t = B <= 0.0 ? div_fast(sq - B, A) : -div_fast(C, B + sq);
-    w.add(kWorkRadBound);
-    if (beyond(t)) break;
-    eval(m);
-  }
-  if (!(B < 0.0)) return;  // moving outward: the radius only grows
-  for (int m = holds ? j - 2 : j - 1; m >= 0; --m) {  // inward: smaller root with rmax^2, C > 0
-    const double C = rho2 - R2[2 * m + 1];
-    const double disc = B * B - A * C;
-    if (disc < -1e-12 * (B * B + A * C)) break;  // misses rmax_m, hence every inner tube
-    const double t = div_fast(C, sqrt(fmax(disc, 0.0)) - B);
-    w.add(kWorkRadBound);
-    if (beyond(t)) break;
-    eval(m);
+  // one loop over the three parts of the walk, so that the tube's code is there
+  // once: the tube holding the point, then outward, then inward
+  enum { kHolding, kOutward, kInward, kEnd };
+  int part = kHolding, m = j - 1;
+  if (!holds || (B >= 0.0 && R2[2 * (j - 1) + 1] - rho2 < 0.25 * kTol * B)) part = A > 0.0 ? kOutward : kEnd, m = j;
+  while (part != kEnd) {
+    bool go = true;
+    if (part == kOutward) {  // larger root of A t^2 + 2 B t + (rho^2 - rmin^2), C < 0
+      go = m < cnt;
+      if (go) {
+        const double C = rho2 - R2[2 * m];
+        const double sq = sqrt(B * B - A * C);
+        w.add(kWorkRadBound);
+        go = !beyond(B <= 0.0 ? div_fast(sq - B, A) : -div_fast(C, B + sq));
+      }
+    } else if (part == kInward) {  // smaller root with rmax^2, C > 0
+      go = m >= 0;
+      if (go) {
+        const double C = rho2 - R2[2 * m + 1];
+        const double disc = B * B - A * C;
+        go = !(disc < -1e-12 * (B * B + A * C));  // else misses rmax_m, hence every inner tube
+        if (go) {
+          w.add(kWorkRadBound);
+          go = !beyond(div_fast(C, sqrt(fmax(disc, 0.0)) - B));
+        }
+      }
+    }
+    if (go) {
+      eval(m);
+      if (part == kHolding) part = A > 0.0 ? kOutward : kEnd, m = j;  // parallel to the axis: the radius never changes
+      else m += part == kOutward ? 1 : -1;
+    } else if (part == kOutward && B < 0.0) {
+      part = kInward, m = holds ? j - 2 : j - 1;
+    } else {  // moving outward, the radius only grows
+      part = kEnd;
+    }
   }
 }
 
@@ -460,21 +477,22 @@ __device__ __forceinline__ double step_culled(const DevGeom& G, int lv, int pv, 
   const int off = G.lv_dau_off[lv], cnt = G.lv_dau_cnt[lv], dtype = G.lv_dau_type[lv];
   bool neg = false;
   const int rad = G.lv_rad[lv], phs = G.lv_phi[lv];
+  using Tube = std::conditional_t<K == kBoxTube, FullTubs, Tubs>;
   if (rad >= 0) {
     daughters_radial(G, rad, off, cnt, pl, dl, dout, best, bestk, neg, w);
   } else if (phs >= 0 && dtype == kBox) {
     daughters_phi<Box, F32>(G, lv, phs, off, cnt, pl, dl, dout, best, bestk, neg, w, left);
   } else if (phs >= 0 && dtype == kTubs) {
-    daughters_phi<Tubs, F32>(G, lv, phs, off, cnt, pl, dl, dout, best, bestk, neg, w, -1);
+    daughters_phi<Tube, F32>(G, lv, phs, off, cnt, pl, dl, dout, best, bestk, neg, w, -1);
   } else if (dtype == kBox && cnt >= kCullMin) {
     daughters_culled<Box, F32>(G, lv, off, cnt, pl, dl, dout, best, bestk, neg, w, left);
   } else if (dtype == kTubs && cnt >= kCullMin) {
-    daughters_culled<Tubs, F32>(G, lv, off, cnt, pl, dl, dout, best, bestk, neg, w, -1);
+    daughters_culled<Tube, F32>(G, lv, off, cnt, pl, dl, dout, best, bestk, neg, w, -1);
   } else if (dtype == kBox) {
     daughters_of_type<Box>(G, off, cnt, pl, dl, best, bestk, neg);
     w.add(kWorkPlain + kBox, (unsigned)cnt);
   } else if (dtype == kTubs) {
-    daughters_of_type<Tubs>(G, off, cnt, pl, dl, best, bestk, neg);
+    daughters_of_type<Tube>(G, off, cnt, pl, dl, best, bestk, neg);
     w.add(kWorkPlain + kTubs, (unsigned)cnt);
   } else {
     // mixed daughters: one whose padded box the ray misses, or enters beyond
