@@ -298,7 +298,7 @@ bool derive(int type, const double* q, int nq, std::vector<double>& out, std::st
 }
 
 struct HostTree {
-  std::vector<int> pv_lv, pv_parent, pv_child_off, pv_child;
+  std::vector<int> pv_lv, pv_parent;
   std::vector<double> pv_gxf;
   int max_depth = 0;
 };
@@ -434,6 +434,29 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
       dau_lv[k] = rd_i32(b, o);
       if (dau_lv[k] < 0 || dau_lv[k] >= n_lv) return fail(GV_EFORMAT, "geom_load: placement %d child", k);
       for (int j = 0; j < 12; ++j) dau_xf[12 * (size_t)k + j] = rd_f64(b, o + 8 + 8 * (size_t)j);
+    }
+    // the tables below keep what depends on the mother with each placement:
+    // volumes that share placements get copies of their own
+    std::vector<int> owner(n_place, -1);
+    bool shared = false;
+    for (int i = 0; i < n_lv; ++i)
+      for (int k = lv_doff[i]; k < lv_doff[i] + lv_dcnt[i]; ++k) {
+        shared = shared || owner[k] >= 0;
+        owner[k] = i;
+      }
+    if (shared) {
+      std::vector<int> lv2;
+      std::vector<double> xf2;
+      for (int i = 0; i < n_lv; ++i) {
+        const int o = lv_doff[i];
+        lv_doff[i] = (int)lv2.size();
+        lv2.insert(lv2.end(), dau_lv.begin() + o, dau_lv.begin() + o + lv_dcnt[i]);
+        xf2.insert(xf2.end(), dau_xf.begin() + 12 * (size_t)o, dau_xf.begin() + 12 * (size_t)(o + lv_dcnt[i]));
+        if (lv2.size() > (size_t)kMaxPv) return fail(GV_EFORMAT, "geom_load: too many placements");
+      }
+      dau_lv.swap(lv2);
+      dau_xf.swap(xf2);
+      n_place = (int)dau_lv.size();
     }
     // one solid type for all daughters of an LV lets the daughter loop run a
     // single solid's code
@@ -700,8 +723,6 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
     HostTree T;
     T.pv_lv.resize(npv);
     T.pv_parent.resize(npv);
-    T.pv_child_off.resize(npv);
-    T.pv_child.resize(npv > 0 ? npv - 1 : 0);
     T.pv_gxf.resize((size_t)npv * 12);
     std::vector<int> pv_k(npv, -1);
     T.max_depth = height[world];
@@ -710,15 +731,13 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
       int pv, lv, next_k;
     };
     std::vector<Frame> stack;
-    int next_id = 0, child_fill = 0;
+    int next_id = 0;
     const double ident[12] = {1, 0, 0, 0, 1, 0, 0, 0, 1, 0, 0, 0};
     auto open = [&](int lv, int parent, const double* gxf) {
       int me = next_id++;
       T.pv_lv[me] = lv;
       T.pv_parent[me] = parent;
       std::memcpy(&T.pv_gxf[12 * (size_t)me], gxf, 12 * sizeof(double));
-      T.pv_child_off[me] = child_fill;
-      child_fill += lv_dcnt[lv];
       stack.push_back(Frame{me, lv, 0});
     };
     open(world, -1, ident);
@@ -731,18 +750,27 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
       int k = f.next_k++;
       int pl = lv_doff[f.lv] + k;
       int parent = f.pv;
-      T.pv_child[T.pv_child_off[parent] + k] = next_id;
       pv_k[next_id] = k;
       double g[12];
       compose(&T.pv_gxf[12 * (size_t)parent], &dau_xf[12 * (size_t)pl], g);
       open(dau_lv[pl], parent, g);
     }
 
-    std::vector<int> pv_lc(2 * (size_t)npv);
-    for (long i = 0; i < npv; ++i) {
-      pv_lc[2 * i] = T.pv_lv[i];
-      pv_lc[2 * i + 1] = lv_class[T.pv_lv[i]];
+    std::vector<LvRec> lvr(n_lv);
+    for (int i = 0; i < n_lv; ++i)
+      lvr[i] = LvRec{lv_type[i], lv_par[i], lv_doff[i], lv_dcnt[i], lv_dtype[i], lv_rad[i], lv_phi[i], lv_loc[i]};
+    // placed volumes are numbered in DFS pre-order, so a daughter's number
+    // follows its mother's by the sizes of the subtrees placed before it
+    std::vector<DauRec> daur(n_place, DauRec{0, 0, 0, 0});
+    for (int i = 0; i < n_lv; ++i) {
+      long delta = 1;
+      for (int k = lv_doff[i]; k < lv_doff[i] + lv_dcnt[i]; ++k) {
+        daur[k] = DauRec{dau_lv[k], dau_par[k], dau_ident[k], (int)delta};
+        delta += std::max(0L, subtree[dau_lv[k]]);  // -1: not reached from the world
+      }
     }
+    std::vector<PvRec> pvr(npv);
+    for (long i = 0; i < npv; ++i) pvr[i] = PvRec{T.pv_lv[i], lv_class[T.pv_lv[i]], T.pv_parent[i], pv_k[i]};
 
     // one device allocation, 256-byte aligned sub-arrays
     struct Part {
@@ -751,22 +779,23 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
       size_t off;
     };
     std::vector<Part> parts = {
-        {lv_type.data(), lv_type.size() * 4, 0},   {lv_par.data(), lv_par.size() * 4, 0},
-        {lv_doff.data(), lv_doff.size() * 4, 0},   {lv_dcnt.data(), lv_dcnt.size() * 4, 0},
-        {par.data(), par.size() * 8, 0},           {dau_xf.data(), dau_xf.size() * 8, 0},
-        {dau_lv.data(), dau_lv.size() * 4, 0},     {T.pv_lv.data(), T.pv_lv.size() * 4, 0},
-        {T.pv_parent.data(), T.pv_parent.size() * 4, 0}, {T.pv_gxf.data(), T.pv_gxf.size() * 8, 0},
-        {T.pv_child_off.data(), T.pv_child_off.size() * 4, 0}, {T.pv_child.data(), T.pv_child.size() * 4, 0},
-        {lv_dtype.data(), lv_dtype.size() * 4, 0}, {dau_par.data(), dau_par.size() * 4, 0},
-        {dau_box.data(), dau_box.size() * 8, 0},   {lv_scr.data(), lv_scr.size() * 4, 0},
-        {dau_box32.data(), dau_box32.size() * 4, 0}, {dau_scr32.data(), dau_scr32.size() * 4, 0},
-        {dau_ident.data(), dau_ident.size() * 4, 0}, {lv_grp.data(), lv_grp.size() * 4, 0},
-        {grp_box.data(), grp_box.size() * 8, 0},     {grp_box32.data(), grp_box32.size() * 4, 0},
-        {lv_rad.data(), lv_rad.size() * 4, 0},       {rad_r2.data(), rad_r2.size() * 8, 0},
-        {rad_k.data(), rad_k.size() * 4, 0},         {lv_phi.data(), lv_phi.size() * 4, 0},
-        {phi_mask.data(), phi_mask.size() * 8, 0},   {nullptr, 5 * 8, 0},
-        {lv_class.data(), lv_class.size() * 4, 0},   {pv_k.data(), pv_k.size() * 4, 0},
-        {pv_lc.data(), pv_lc.size() * 4, 0},         {lv_loc.data(), lv_loc.size() * 4, 0}};
+        {lvr.data(), lvr.size() * 32, 0},
+        {par.data(), par.size() * 8, 0},
+        {dau_xf.data(), dau_xf.size() * 8, 0},
+        {daur.data(), daur.size() * 16, 0},
+        {pvr.data(), pvr.size() * 16, 0},
+        {T.pv_gxf.data(), T.pv_gxf.size() * 8, 0},
+        {dau_box.data(), dau_box.size() * 8, 0},
+        {lv_scr.data(), lv_scr.size() * 4, 0},
+        {dau_box32.data(), dau_box32.size() * 4, 0},
+        {dau_scr32.data(), dau_scr32.size() * 4, 0},
+        {lv_grp.data(), lv_grp.size() * 4, 0},
+        {grp_box.data(), grp_box.size() * 8, 0},
+        {grp_box32.data(), grp_box32.size() * 4, 0},
+        {rad_r2.data(), rad_r2.size() * 8, 0},
+        {rad_k.data(), rad_k.size() * 4, 0},
+        {phi_mask.data(), phi_mask.size() * 8, 0},
+        {nullptr, 5 * 8, 0}};
     size_t total = 0;
     for (auto& p : parts) {
       p.off = total;
@@ -804,38 +833,23 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
     D.n_lv = n_lv;
     D.n_pv = (int)npv;
     D.n_place = n_place;
-    D.lv_type = (CQI)(base + parts[0].off);
-    D.lv_par = (CQI)(base + parts[1].off);
-    D.lv_dau_off = (CQI)(base + parts[2].off);
-    D.lv_dau_cnt = (CQI)(base + parts[3].off);
-    D.par = (CQ)(base + parts[4].off);
-    D.dau_xf = (CQ)(base + parts[5].off);
-    D.dau_lv = (CQI)(base + parts[6].off);
-    D.pv_lv = (CQI)(base + parts[7].off);
-    D.pv_parent = (CQI)(base + parts[8].off);
-    D.pv_gxf = (CQ)(base + parts[9].off);
-    D.pv_child_off = (CQI)(base + parts[10].off);
-    D.pv_child = (CQI)(base + parts[11].off);
-    D.lv_dau_type = (CQI)(base + parts[12].off);
-    D.dau_par = (CQI)(base + parts[13].off);
-    D.dau_box = (CQ)(base + parts[14].off);
-    D.lv_scr = (CQF)(base + parts[15].off);
-    D.dau_box32 = (CQF)(base + parts[16].off);
-    D.dau_scr32 = (CQF)(base + parts[17].off);
-    D.dau_ident = (CQI)(base + parts[18].off);
-    D.lv_grp = (CQI)(base + parts[19].off);
-    D.grp_box = (CQ)(base + parts[20].off);
-    D.grp_box32 = (CQF)(base + parts[21].off);
-    D.lv_rad = (CQI)(base + parts[22].off);
-    D.rad_r2 = (CQ)(base + parts[23].off);
-    D.rad_k = (CQI)(base + parts[24].off);
-    D.lv_phi = (CQI)(base + parts[25].off);
-    D.phi_mask = (CQL)(base + parts[26].off);
-    g->pcon_work = (unsigned long long*)(base + parts[27].off);  // zeroed by the upload
-    D.lv_class = (CQI)(base + parts[28].off);
-    D.pv_k = (CQI)(base + parts[29].off);
-    D.pv_lc = (CQI)(base + parts[30].off);
-    D.lv_loc = (CQI)(base + parts[31].off);
+    D.lv_rec = (CQ4)(base + parts[0].off);
+    D.par = (CQ)(base + parts[1].off);
+    D.dau_xf = (CQ)(base + parts[2].off);
+    D.dau_rec = (CQ4)(base + parts[3].off);
+    D.pv_rec = (CQ4)(base + parts[4].off);
+    D.pv_gxf = (CQ)(base + parts[5].off);
+    D.dau_box = (CQ)(base + parts[6].off);
+    D.lv_scr = (CQF)(base + parts[7].off);
+    D.dau_box32 = (CQF)(base + parts[8].off);
+    D.dau_scr32 = (CQF)(base + parts[9].off);
+    D.lv_grp = (CQI)(base + parts[10].off);
+    D.grp_box = (CQ)(base + parts[11].off);
+    D.grp_box32 = (CQF)(base + parts[12].off);
+    D.rad_r2 = (CQ)(base + parts[13].off);
+    D.rad_k = (CQI)(base + parts[14].off);
+    D.phi_mask = (CQL)(base + parts[15].off);
+    g->pcon_work = (unsigned long long*)(base + parts[16].off);  // zeroed by the upload
     g->n_lv = n_lv;
     g->n_pv = (int)npv;
     g->n_place = n_place;

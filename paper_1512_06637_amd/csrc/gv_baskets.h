@@ -185,7 +185,7 @@ __global__ void k_bt_init(DevGeom G, int64_t n, const double* __restrict__ x, co
         out_nsteps[i] = 0;
         out_flags[i] = fl;
       } else {
-        bk = G.pv_lv[v] << cb | dir_cell(dx[i], dy[i], dz[i], cb);
+        bk = pv_rec(G, v).lv << cb | dir_cell(dx[i], dy[i], dz[i], cb);
       }
       key[i] = bk;
     }
@@ -521,7 +521,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
         p = advance(p, st, d);
       }
       // leaving pv into its mother: pv's placement index goes along (see the lane form)
-      const int left = nx != r.pv ? (exited ? G.pv_k[r.pv] : -1) : zfc_left(r.zfc);
+      const int left = nx != r.pv ? (exited ? pv_rec(G, r.pv).k : -1) : zfc_left(r.zfc);
       if (ob_step) {  // staged by slot, moved to the rows at the end
         ob_step[(size_t)k * cap + sl] = st;
         ob_pv[(size_t)k * cap + sl] = nx;
@@ -554,7 +554,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
         r.pv = nx;
         r.zfc = zfc_pack(zr, fl, left, zfc_cc(r.zfc));
         rec[sl] = r;
-        nlv_out = G.pv_lv[nx] << cb | zfc_cc(r.zfc);
+        nlv_out = pv_rec(G, nx).lv << cb | zfc_cc(r.zfc);
       }
       nxt_lv[e] = nlv_out;
     }

@@ -8,55 +8,74 @@
 
 namespace gv {
 
+// What a step reads of a logical volume, a placement and a placed volume, each
+// in one aligned record: the fields used to be arrays of their own, and a step
+// waited for seven loads of its volume, then for the daughter's, the parent's
+// and the child's one after another.
+struct LvRec {
+  int type, par;    // solid type and offset of its parameters in DevGeom::par
+  int off, cnt;     // first daughter placement and number of daughters
+  int dtype;        // solid type shared by all daughters, -1 if mixed or none
+  int rad, phi;     // first entry of its radial list / first phi mask, -1 without
+  int loc;          // how point lookups reach the daughters (kLoc*)
+};
+struct DauRec {
+  int lv, par;      // child volume, offset of its solid's parameters
+  int ident;        // 1 when the placement is the identity (R = I, t = 0)
+  int delta;        // placed volume of this daughter minus its mother's
+};
+struct PvRec {
+  int lv, cls;      // logical volume, step class: branch of the step code (daughter access mode x 8 + solid type)
+  int parent, k;    // placed mother (-1: none), placement index among its daughters (-1: the world)
+};
+
 // All arrays live in HBM; geom_load fills them once.  Transforms are 12
 // doubles: R row-major then t, with x_mother = R x_child + t.
 constexpr int kPhiSectors = 256;
 
 struct DevGeom {
   int n_lv, n_pv, n_place;
-  CQI lv_type;       // [n_lv]
-  CQI lv_par;        // [n_lv] offset into par
-  CQI lv_dau_off;    // [n_lv] first daughter placement
-  CQI lv_dau_cnt;    // [n_lv]
-  CQI lv_dau_type;   // [n_lv] solid type shared by all daughters, -1 if mixed or none
+  CQ4 lv_rec;        // [n_lv][2] records of LvRec, one 32-byte load
   CQ par;            // derived solid parameters
   CQ dau_xf;         // [n_place][12] placement transform, LV frame
-  CQI dau_lv;        // [n_place]
-  CQI dau_par;       // [n_place] offset of the child solid's parameters in par
+  CQ4 dau_rec;       // [n_place] records of DauRec, one 16-byte load
   CQ dau_box;        // [n_place][6] child's bounding box in the mother frame (lo xyz, hi xyz), padded
-  CQI pv_lv;         // [n_pv]
-  CQI pv_parent;     // [n_pv]
+  CQ4 pv_rec;        // [n_pv] records of PvRec, one 16-byte load
   CQ pv_gxf;         // [n_pv][12] composed world <- PV transform
-  CQI pv_child_off;  // [n_pv] children of a PV follow their LV's placement order
-  CQI pv_child;      // [n_pv]
   // FP32 screen tables (daughter culling in FP32 with FP64 refinement)
   CQF lv_scr;        // [n_lv] S: max |coordinate| of a point of the LV's solid + 1 mm
   CQF dau_box32;     // [n_place][8] dau_box widened by 128 u (S(mother) + |box|inf), rounded outward; 2 unused
   CQF dau_scr32;     // [n_place][16] R (9), t (3), child a b c (box: dx dy dz; tube: rmin rmax dz), e
   // daughter groups: 8 consecutive daughters of an LV with >= 16 daughters
-  CQI dau_ident;     // [n_place] 1 when the placement is the identity (R = I, t = 0)
   CQI lv_grp;        // [n_lv] index of the LV's first group box, -1 without groups
   CQ grp_box;        // [n_grp][6] union of the group's padded daughter boxes (lo xyz, hi xyz)
   CQF grp_box32;     // [n_grp][8] union of the group's FP32 boxes; 2 unused
   // radial order: an LV whose daughters are identity-placed full tubes with
   // disjoint radial ranges lists them by radius
-  CQI lv_rad;        // [n_lv] first entry of the LV's radial list, -1 without one
   CQ rad_r2;         // [n_rad][2] rmin^2, rmax^2 in radial order
   CQI rad_k;         // [n_rad] daughter index (placement order) of each entry
   // phi sectors: an LV whose (<= 64) daughters lie around the z axis, each
   // within less than a half turn, has kPhiSectors masks of the daughters
   // whose angular extent (widened) meets each sector of pseudo-angle
-  CQI lv_phi;        // [n_lv] first mask of the LV, -1 without sectors
   CQL phi_mask;      // [n_phi_lv][kPhiSectors]
   // materials for physics-limited steps (geom_set_materials); n_mat 0 if unset
   int n_mat, n_proc;
   CQ mat_rate;       // [n_mat][n_proc] n sigma = 1 / mean free path, 1/mm
   CQI lv_mat;        // [n_lv] material of each LV
-  CQI lv_class;      // [n_lv] step class: branch of the step code (daughter access mode x 8 + solid type)
-  CQI pv_k;          // [n_pv] placement index of each PV among its parent's daughters (-1: the world)
-  CQI lv_loc;        // [n_lv] how point lookups reach the daughters (kLoc*)
-  CQI pv_lc;         // [2 n_pv] logical volume and step class of each PV (one 8-byte load)
 };
+
+__device__ __forceinline__ LvRec lv_rec(const DevGeom& G, int lv) {
+  const Int4 a = G.lv_rec[2 * (size_t)lv], b = G.lv_rec[2 * (size_t)lv + 1];
+  return LvRec{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+}
+__device__ __forceinline__ DauRec dau_rec(const DevGeom& G, int k) {
+  const Int4 a = G.dau_rec[k];
+  return DauRec{a.x, a.y, a.z, a.w};
+}
+__device__ __forceinline__ PvRec pv_rec(const DevGeom& G, int pv) {
+  const Int4 a = G.pv_rec[pv];
+  return PvRec{a.x, a.y, a.z, a.w};
+}
 
 __device__ __forceinline__ V3 ld3(const double* x, const double* y, const double* z, int64_t i) {
   return V3{x[i], y[i], z[i]};
@@ -83,8 +102,8 @@ enum { kLocPlain = 0, kLocRadial = 1, kLocPhi = 2, kLocBox = 3 };
 
 // The access mode for a point: the indexes take finite coordinates only (a NaN
 // or infinity goes through every daughter's own code).
-__device__ __forceinline__ int loc_mode(const DevGeom& G, int lv, V3 p) {
-  return p.x * p.x + p.y * p.y + p.z * p.z < 1e200 ? G.lv_loc[lv] : kLocPlain;
+__device__ __forceinline__ int loc_mode(const LvRec& v, V3 p) {
+  return p.x * p.x + p.y * p.y + p.z * p.z < 1e200 ? v.loc : kLocPlain;
 }
 
 __device__ __forceinline__ int phi_sector(double a) {
@@ -115,17 +134,17 @@ __device__ __forceinline__ int radial_rank(CQ R2, int cnt, double rho2) {
 // us per 300,007 points spread over it), the indexes two or three (13 us, most
 // of it the call).
 template <int K>
-__device__ __forceinline__ int first_daughter(const DevGeom& G, int lv, V3 pl) {
-  const int off = G.lv_dau_off[lv], cnt = G.lv_dau_cnt[lv];
+__device__ __forceinline__ int first_daughter(const DevGeom& G, const LvRec& v, V3 pl) {
+  const int off = v.off, cnt = v.cnt;
   if (cnt == 0) return -1;
-  int mode = loc_mode(G, lv, pl);
+  const int mode = loc_mode(v, pl);
   auto holds = [&](int k) {
-    const int clv = G.dau_lv[off + k];
+    const DauRec d = dau_rec(G, off + k);
     const V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(off + k), pl);
-    return code_of(solid_sgn<K>(G.lv_type[clv], G.par + G.lv_par[clv], pc)) != kOutside;
+    return code_of(solid_sgn<K>(lv_rec(G, d.lv).type, G.par + d.par, pc)) != kOutside;
   };
   if (mode == kLocRadial) {
-    const int r0 = G.lv_rad[lv];
+    const int r0 = v.rad;
     CQ R2 = G.rad_r2 + 2 * (size_t)r0;
     CQI order = G.rad_k + r0;
     const double rho2 = pl.x * pl.x + pl.y * pl.y;
@@ -133,19 +152,19 @@ __device__ __forceinline__ int first_daughter(const DevGeom& G, int lv, V3 pl) {
     int best = cnt;
     auto test = [&](int m) {
       const int k = order[m];
-      if (k < best && code_of(Tubs::sgn(G.par + G.dau_par[off + k], pl)) != kOutside) best = k;
+      if (k < best && code_of(Tubs::sgn(G.par + dau_rec(G, off + k).par, pl)) != kOutside) best = k;
     };
     for (int m = j - 1; m >= 0 && rho2 <= fma(R2[2 * m + 1], 1.0 + 1e-8, 1e-8); --m) test(m);
     for (int m = j; m < cnt && rho2 >= fma(R2[2 * m], 1.0 - 1e-8, -1e-8); ++m) test(m);
     return best < cnt ? best : -1;
   }
   if (mode == kLocPhi && fabs(pl.x) + fabs(pl.y) > 1e-6) {
-    uint64_t cand = (G.phi_mask + (size_t)G.lv_phi[lv])[phi_sector(pseudo_angle_fast(pl.x, pl.y))];
-    const int type = G.lv_dau_type[lv];
+    uint64_t cand = (G.phi_mask + (size_t)v.phi)[phi_sector(pseudo_angle_fast(pl.x, pl.y))];
+    const int type = v.dtype;
     while (cand) {
       const int k = __builtin_ctzll(cand);
       cand &= cand - 1;
-      CQ q = G.par + G.dau_par[off + k];
+      CQ q = G.par + dau_rec(G, off + k).par;
       const V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(off + k), pl);
       if (code_of(type == kBox ? Box::sgn(q, pc) : Tubs::sgn(q, pc)) != kOutside) return k;
     }
@@ -163,16 +182,17 @@ __device__ __forceinline__ int first_daughter(const DevGeom& G, int lv, V3 pl) {
 
 template <int K>
 __device__ __forceinline__ int locate(const DevGeom& G, V3 p) {
-  int lv = G.pv_lv[0];
-  if (code_of(solid_sgn<K>(G.lv_type[lv], G.par + G.lv_par[lv], p)) == kOutside) return -1;
+  LvRec v = lv_rec(G, pv_rec(G, 0).lv);
+  if (code_of(solid_sgn<K>(v.type, G.par + v.par, p)) == kOutside) return -1;
   int pv = 0;
   V3 pl = p;
   for (;;) {
-    const int k = first_daughter<K>(G, lv, pl);
+    const int k = first_daughter<K>(G, v, pl);
     if (k < 0) return pv;
-    pl = to_child_p(G.dau_xf + 12 * (size_t)(G.lv_dau_off[lv] + k), pl);
-    pv = G.pv_child[G.pv_child_off[pv] + k];
-    lv = G.pv_lv[pv];
+    const DauRec d = dau_rec(G, v.off + k);
+    pl = to_child_p(G.dau_xf + 12 * (size_t)(v.off + k), pl);
+    pv += d.delta;
+    v = lv_rec(G, d.lv);
   }
 }
 
@@ -187,30 +207,30 @@ __device__ __forceinline__ int locate(const DevGeom& G, V3 p) {
 // over sqrt(3)), an arc of at most pi/2 sin(angle) in pseudo-angle.  kTolerance
 // on top of s keeps rounding of the bounds from mattering.  In the detector two
 // or three daughters instead of 20 or 64 (71 against 16 us per 200,003 points).
-__device__ __forceinline__ bool safety_indexed(const DevGeom& G, int lv, V3 pl, double& s) {
-  const int mode = loc_mode(G, lv, pl);
-  if (mode != kLocRadial && !(mode == kLocPhi && G.lv_dau_type[lv] == kBox)) return false;
-  const int off = G.lv_dau_off[lv], cnt = G.lv_dau_cnt[lv];
+__device__ __forceinline__ bool safety_indexed(const DevGeom& G, const LvRec& v, V3 pl, double& s) {
+  const int mode = loc_mode(v, pl);
+  if (mode != kLocRadial && !(mode == kLocPhi && v.dtype == kBox)) return false;
+  const int off = v.off, cnt = v.cnt;
   const double rho2 = pl.x * pl.x + pl.y * pl.y, r = sqrt(rho2);
   auto limit = [&] { return fmax(s, kHalf) + kTol; };
   if (mode == kLocRadial) {
-    const int r0 = G.lv_rad[lv];
+    const int r0 = v.rad;
     CQI order = G.rad_k + r0;
     const int j = radial_rank(G.rad_r2 + 2 * (size_t)r0, cnt, rho2);
     auto eval = [&](CQ q) { s = code_of(Tubs::sgn(q, pl)) == kOutside ? fmin(s, Tubs::safety_in(q, pl)) : 0.0; };
     for (int m = j - 1; m >= 0; --m) {
-      CQ q = G.par + G.dau_par[off + order[m]];
+      CQ q = G.par + dau_rec(G, off + order[m]).par;
       if (r - q[L::TB_RMAX] > limit()) break;
       eval(q);
     }
     for (int m = j; m < cnt; ++m) {
-      CQ q = G.par + G.dau_par[off + order[m]];
+      CQ q = G.par + dau_rec(G, off + order[m]).par;
       if (q[L::TB_RMIN] - r > limit()) break;
       eval(q);
     }
     return true;
   }
-  CQL M = G.phi_mask + (size_t)G.lv_phi[lv];
+  CQL M = G.phi_mask + (size_t)v.phi;
   const uint64_t all = cnt == 64 ? ~0ull : (1ull << cnt) - 1;
   const bool off_axis = fabs(pl.x) + fabs(pl.y) > 1e-6;
   const double a = off_axis ? pseudo_angle_fast(pl.x, pl.y) : 0.0;
@@ -220,7 +240,7 @@ __device__ __forceinline__ bool safety_indexed(const DevGeom& G, int lv, V3 pl, 
     while (cand) {
       const int k = __builtin_ctzll(cand);
       cand &= cand - 1;
-      CQ q = G.par + G.dau_par[off + k];
+      CQ q = G.par + dau_rec(G, off + k).par;
       const V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(off + k), pl);
       s = code_of(Box::sgn(q, pc)) == kOutside ? fmin(s, Box::safety_in(q, pc)) : 0.0;
     }
@@ -243,19 +263,17 @@ __device__ __forceinline__ bool safety_indexed(const DevGeom& G, int lv, V3 pl, 
 
 template <int K>
 __device__ __forceinline__ double nav_safety(const DevGeom& G, int pv, V3 p) {
-  int lv = G.pv_lv[pv];
+  const LvRec v = lv_rec(G, pv_rec(G, pv).lv);
   V3 pl = to_child_p(G.pv_gxf + 12 * (size_t)pv, p);
-  int t = G.lv_type[lv];
-  CQ q = G.par + G.lv_par[lv];
-  if (code_of(solid_sgn<K>(t, q, pl)) != kInside) return 0.0;
-  double s = solid_safety_out<K>(t, q, pl);
-  if (safety_indexed(G, lv, pl, s)) return fmax(s, 0.0);
-  int off = G.lv_dau_off[lv], cnt = G.lv_dau_cnt[lv];
-  for (int k = 0; k < cnt; ++k) {
-    int clv = G.dau_lv[off + k];
-    V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(off + k), pl);
-    CQ qc = G.par + G.lv_par[clv];
-    int tc = G.lv_type[clv];
+  CQ q = G.par + v.par;
+  if (code_of(solid_sgn<K>(v.type, q, pl)) != kInside) return 0.0;
+  double s = solid_safety_out<K>(v.type, q, pl);
+  if (safety_indexed(G, v, pl, s)) return fmax(s, 0.0);
+  for (int k = 0; k < v.cnt; ++k) {
+    const DauRec d = dau_rec(G, v.off + k);
+    V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(v.off + k), pl);
+    CQ qc = G.par + d.par;
+    int tc = lv_rec(G, d.lv).type;
     if (code_of(solid_sgn<K>(tc, qc, pc)) != kOutside) return 0.0;
     s = fmin(s, solid_safety_in<K>(tc, qc, pc));
   }

@@ -271,9 +271,9 @@ __global__ void k_nav_inside(DevGeom G, int64_t n, const double* __restrict__ x,
       out[i] = (int8_t)kOutside;
       continue;
     }
-    int lv = G.pv_lv[v];
+    const LvRec m = lv_rec(G, pv_rec(G, v).lv);
     V3 pl = to_child_p(G.pv_gxf + 12 * (size_t)v, ld3(x, y, z, i));
-    out[i] = (int8_t)code_of(solid_sgn<K>(G.lv_type[lv], G.par + G.lv_par[lv], pl));
+    out[i] = (int8_t)code_of(solid_sgn<K>(m.type, G.par + m.par, pl));
   }
 }
 

@@ -102,16 +102,16 @@ struct LaneCtl {
 // whether it enters more than one.
 constexpr int kStartBins = 32;
 __device__ __forceinline__ uint32_t start_bin(const DevGeom& G, int pv, V3 p, V3 d) {
-  const int lv = G.pv_lv[pv], off = G.lv_dau_off[lv], cnt = G.lv_dau_cnt[lv];
-  if (G.lv_loc[lv] != kLocBox) return 0;
+  const LvRec v = lv_rec(G, pv_rec(G, pv).lv);
+  if (v.loc != kLocBox) return 0;
   CQ X = G.pv_gxf + 12 * (size_t)pv;
   const V3 pl = to_child_p(X, p), dl = to_child_d(X, d);
   const V3 inv{inv_dir64(dl.x), inv_dir64(dl.y), inv_dir64(dl.z)};
   const V3 pin{-pl.x * inv.x, -pl.y * inv.y, -pl.z * inv.z};
   double best = GV_INF;
   int bk = -1, hits = 0;
-  for (int k = 0; k < cnt; ++k) {
-    const double t = box_entry64(G.dau_box + 6 * (size_t)(off + k), inv, pin);
+  for (int k = 0; k < v.cnt; ++k) {
+    const double t = box_entry64(G.dau_box + 6 * (size_t)(v.off + k), inv, pin);
     if (!(t < GV_INF)) continue;
     ++hits;
     if (t < best) {
@@ -160,7 +160,7 @@ static __global__ void k_ls_count(DevGeom G, int64_t n, const double* __restrict
     uint32_t k = zaxis ? direction_key_zaxis(dx[i], dy[i], dz[i], h) : direction_key(dx[i], dy[i], dz[i], h);
     if (lvs > 0) {
       const int pv = start_pv[i];
-      if (pv >= 0 && pv < G.n_pv) k |= ((uint32_t)G.pv_lv[pv] * kStartBins + L.key[i]) << (2 * h);
+      if (pv >= 0 && pv < G.n_pv) k |= ((uint32_t)pv_rec(G, pv).lv * kStartBins + L.key[i]) << (2 * h);
     }
     L.key[i] = k;
     atomicAdd(&key_hist[k], 1u);
@@ -315,7 +315,7 @@ __device__ __forceinline__ bool lane_record(const DevGeom& G, LaneTrack& T, cons
   // a track that leaves its volume into the mother carries the volume's
   // placement index there (the line does not change, so the volume is behind
   // it); entering a daughter clears it
-  if (nx != T.pv) T.left = R.exited ? G.pv_k[T.pv] : -1;
+  if (nx != T.pv) T.left = R.exited ? pv_rec(G, T.pv).k : -1;
   if (ST == 0) {
     out_step[(size_t)T.i * max_steps + T.k] = st;
     out_pv[(size_t)T.i * (max_steps + 1) + T.k + 1] = nx;
@@ -419,7 +419,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
     LaneStep R;
     if (!CLS) {
       while (live) {
-        lane_compute<F32, PHYS, K>(G, T, G.pv_lv[T.pv], T.pv, P, R);
+        lane_compute<F32, PHYS, K>(G, T, pv_rec(G, T.pv).lv, T.pv, P, R);
         live = !lane_record<PHYS, ST>(G, T, R, max_steps, out_pv, out_step, out_nsteps, out_flags, out_proc, S);
       }
       continue;
@@ -427,9 +427,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
     for (uint64_t lm = __ballot(live); lm; lm = __ballot(live)) {
       int lv = -1, cl = -1;
       if (live) {  // volume and class in one load
-        const unsigned long long lc = reinterpret_cast<CQL>(G.pv_lc)[T.pv];
-        lv = (int)(uint32_t)lc;
-        cl = K == kComposites ? lv : (int)(uint32_t)(lc >> 32);  // composites: each volume is a class of its own
+        const PvRec v = pv_rec(G, T.pv);
+        lv = v.lv;
+        cl = K == kComposites ? lv : v.cls;  // composites: each volume is a class of its own
       }
       // the class most live lanes are in (few classes are present at once;
       // on equal counts the first found)

@@ -82,9 +82,9 @@ __global__ void __launch_bounds__(256) k_serve(DevGeom G, const SDesc* __restric
       } else {
         int8_t c = (int8_t)kOutside;
         if (ok) {
-          const int lv = G.pv_lv[v];
+          const LvRec m = lv_rec(G, pv_rec(G, v).lv);
           const V3 pl = to_child_p(G.pv_gxf + 12 * (size_t)v, p);
-          c = (int8_t)code_of(solid_sgn<K>(G.lv_type[lv], G.par + G.lv_par[lv], pl));
+          c = (int8_t)code_of(solid_sgn<K>(m.type, G.par + m.par, pl));
         }
         ((int8_t*)O)[i] = c;
       }

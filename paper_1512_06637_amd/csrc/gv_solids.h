@@ -33,7 +33,7 @@ enum { kOutside = 0, kSurface = 1, kInside = 2 };
 
 // ---- derived parameter layouts (filled on the host by geom_load) ----------
 // box   : dx dy dz
-// tubs  : rmin rmax dz phimode ns[2] ne[2] us[2] ue[2] rmin^2 rmax^2
+// tubs  : rmin rmax dz phimode rmin^2 rmax^2 ns[2] ne[2] us[2] ue[2]
 // cons  : rmin1 rmax1 rmin2 rmax2 dz phimode ns[2] ne[2] us[2] ue[2] ao bo co ai bi ci inner
 // sphere: rmin rmax rmin^2 rmax^2
 // trd   : dx1 dx2 dy1 dy2 dz x0 tx cx y0 ty cy
@@ -46,7 +46,7 @@ enum { kOutside = 0, kSurface = 1, kInside = 2 };
 // phimode: 0 full circle, 1 wedge <= pi (intersection of two half-spaces),
 //          2 wedge > pi (union of two half-spaces).
 namespace L {
-enum { TB_RMIN = 0, TB_RMAX, TB_DZ, TB_PHI, TB_NS, TB_NE = 6, TB_US = 8, TB_UE = 10, TB_RMIN2 = 12, TB_RMAX2, TB_N };
+enum { TB_RMIN = 0, TB_RMAX, TB_DZ, TB_PHI, TB_RMIN2, TB_RMAX2, TB_NS, TB_NE = 8, TB_US = 10, TB_UE = 12, TB_N = 14 };
 enum { CN_RMIN1 = 0, CN_RMAX1, CN_RMIN2, CN_RMAX2, CN_DZ, CN_PHI, CN_NS, CN_NE = 8, CN_US = 10, CN_UE = 12,
        CN_AO = 14, CN_BO, CN_CO, CN_AI, CN_BI, CN_CI, CN_INNER, CN_N };
 enum { SP_RMIN = 0, SP_RMAX, SP_RMIN2, SP_RMAX2, SP_N };
@@ -66,6 +66,8 @@ typedef const __attribute__((address_space(4))) double* CQ;
 typedef const __attribute__((address_space(4))) int* CQI;
 typedef const __attribute__((address_space(4))) float* CQF;
 typedef const __attribute__((address_space(4))) unsigned long long* CQL;
+typedef int Int4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(4))) Int4* CQ4;
 
 // Pseudo-angle of (x, y) around the z axis: a monotone map of the polar angle
 // [0, 2 pi) onto [0, 4), one unit per quadrant, with a half turn adding

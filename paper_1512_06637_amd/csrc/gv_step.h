@@ -69,7 +69,7 @@ __device__ __forceinline__ Placement load_placement(const DevGeom& G, int k) {
   CQ Y = G.dau_xf + 12 * (size_t)k;
 #pragma unroll
   for (int j = 0; j < 12; ++j) P.R[j] = Y[j];
-  P.par = G.dau_par[k];
+  P.par = dau_rec(G, k).par;
   return P;
 }
 
@@ -272,8 +272,9 @@ __device__ __forceinline__ void daughters_culled(const DevGeom& G, int lv, int o
       cand &= cand - 1;
       const int pk = off + c0 + k;
       CQ Y = G.dau_xf + 12 * (size_t)pk;
-      CQ q = G.par + G.dau_par[pk];
-      const bool ident = G.dau_ident[pk] != 0;  // then the child frame is the mother's
+      const DauRec dr = dau_rec(G, pk);
+      CQ q = G.par + dr.par;
+      const bool ident = dr.ident != 0;  // then the child frame is the mother's
       const double thr = fmin(best, dout) + kTol;
       w.add(kWorkBound + S::kType);
       V3 pc = pl;
@@ -332,7 +333,7 @@ __device__ __forceinline__ void daughters_radial(const DevGeom& G, int r0, int o
   auto eval = [&](int m) {
     const int k = K[m];
     w.add(kWorkFull + kTubs);
-    double t = Tubs::full_dist<true>(G.par + G.dau_par[off + k], pl, dl);
+    double t = Tubs::full_dist<true>(G.par + dau_rec(G, off + k).par, pl, dl);
     neg = neg || t < 0.0;
     t = fmax(t, 0.0);
     if (t < best || (t == best && k < bestk)) {
@@ -430,8 +431,9 @@ __device__ __forceinline__ void daughters_phi(const DevGeom& G, int lv, int m0, 
     cand &= cand - 1;
     const int pk = off + k;
     CQ Y = G.dau_xf + 12 * (size_t)pk;
-    CQ q = G.par + G.dau_par[pk];
-    const bool ident = G.dau_ident[pk] != 0;
+    const DauRec dr = dau_rec(G, pk);
+    CQ q = G.par + dr.par;
+    const bool ident = dr.ident != 0;
     const double thr = fmin(best, dout) + kTol;
     w.add(kWorkBound + S::kType);
     V3 pc = pl;
@@ -466,7 +468,8 @@ __device__ __forceinline__ double step_culled(const DevGeom& G, int lv, int pv, 
                                               uint32_t* flags, W& w, int left = -1, bool* exited = nullptr) {
   CQ X = G.pv_gxf + 12 * (size_t)pv;
   V3 pl = to_child_p(X, p), dl = to_child_d(X, d);
-  double dout = solid_dist_out<K>(G.lv_type[lv], G.par + G.lv_par[lv], pl, dl);
+  const LvRec v = lv_rec(G, lv);
+  double dout = solid_dist_out<K>(v.type, G.par + v.par, pl, dl);
   uint32_t fl = *flags;
   if (dout < 0.0) {
     dout = 0.0;
@@ -474,9 +477,8 @@ __device__ __forceinline__ double step_culled(const DevGeom& G, int lv, int pv, 
   }
   double best = GV_INF;
   int bestk = -1;
-  const int off = G.lv_dau_off[lv], cnt = G.lv_dau_cnt[lv], dtype = G.lv_dau_type[lv];
+  const int off = v.off, cnt = v.cnt, dtype = v.dtype, rad = v.rad, phs = v.phi;
   bool neg = false;
-  const int rad = G.lv_rad[lv], phs = G.lv_phi[lv];
   using Tube = std::conditional_t<K == kBoxTube, FullTubs, Tubs>;
   if (rad >= 0) {
     daughters_radial(G, rad, off, cnt, pl, dl, dout, best, bestk, neg, w);
@@ -498,7 +500,7 @@ __device__ __forceinline__ double step_culled(const DevGeom& G, int lv, int pv, 
     // mixed daughters: one whose padded box the ray misses, or enters beyond
     // the exit or the best daughter so far, cannot be entered first (finite
     // rays and rotations only, as in point lookups)
-    const bool cull = loc_mode(G, lv, pl) == kLocBox && dl.x * dl.x + dl.y * dl.y + dl.z * dl.z < 4.0;
+    const bool cull = loc_mode(v, pl) == kLocBox && dl.x * dl.x + dl.y * dl.y + dl.z * dl.z < 4.0;
     V3 inv{}, pin{};
     if (cull) {
       inv = V3{inv_dir64(dl.x), inv_dir64(dl.y), inv_dir64(dl.z)};
@@ -507,10 +509,10 @@ __device__ __forceinline__ double step_culled(const DevGeom& G, int lv, int pv, 
     for (int k = 0; k < cnt; ++k) {
       if (cull && !box_hit64(G.dau_box + 6 * (size_t)(off + k), inv, pin, fmin(best, dout) + kTol)) continue;
       CQ Y = G.dau_xf + 12 * (size_t)(off + k);
-      const int clv = G.dau_lv[off + k];
+      const DauRec dr = dau_rec(G, off + k);
       V3 pc = to_child_p(Y, pl), dc = to_child_d(Y, dl);
-      const int ct = G.lv_type[clv];
-      double t = solid_dist_in<K>(ct, G.par + G.lv_par[clv], pc, dc);
+      const int ct = lv_rec(G, dr.lv).type;
+      double t = solid_dist_in<K>(ct, G.par + dr.par, pc, dc);
       if (ct <= kPcon) w.add(kWorkPlain + ct);  // composites have no counter
       neg = neg || t < 0.0;
       t = fmax(t, 0.0);
@@ -523,11 +525,11 @@ __device__ __forceinline__ double step_culled(const DevGeom& G, int lv, int pv, 
   if (neg) fl |= kFlagLocateFail;
   *flags = fl;
   if (bestk >= 0 && best <= dout) {
-    *next = G.pv_child[G.pv_child_off[pv] + bestk];
+    *next = pv + dau_rec(G, off + bestk).delta;
     if (exited) *exited = false;
     return best;
   }
-  *next = G.pv_parent[pv];
+  *next = pv_rec(G, pv).parent;
   if (exited) *exited = true;
   return dout;
 }
@@ -538,7 +540,7 @@ template <bool F32, int K, class W>
 __device__ __forceinline__ double step_culled_limited(const DevGeom& G, int pv, V3 p, V3 d, double pstep, int* next,
                                                       uint32_t* flags, W& w) {
   int nx;
-  const double s = step_culled<F32, K>(G, G.pv_lv[pv], pv, p, d, &nx, flags, w);
+  const double s = step_culled<F32, K>(G, pv_rec(G, pv).lv, pv, p, d, &nx, flags, w);
   // s is the daughter minimum when a daughter was chosen, else the exit
   if (pstep < s) {
     *next = pv;
@@ -606,14 +608,13 @@ __device__ __forceinline__ double step_physics(const DevGeom& G, int lv, int pv,
 // outside it and it cannot lower the minimum.  Equal to nav_safety bit for bit.
 template <int K>
 __device__ __forceinline__ double nav_safety_screened(const DevGeom& G, int pv, V3 p) {
-  const int lv = G.pv_lv[pv];
+  const LvRec v = lv_rec(G, pv_rec(G, pv).lv);
   const V3 pl = to_child_p(G.pv_gxf + 12 * (size_t)pv, p);
-  const int t = G.lv_type[lv];
-  CQ q = G.par + G.lv_par[lv];
-  if (code_of(solid_sgn<K>(t, q, pl)) != kInside) return 0.0;
-  double s = solid_safety_out<K>(t, q, pl);
-  if (safety_indexed(G, lv, pl, s)) return fmax(s, 0.0);
-  const int off = G.lv_dau_off[lv], cnt = G.lv_dau_cnt[lv], dtype = G.lv_dau_type[lv];
+  CQ q = G.par + v.par;
+  if (code_of(solid_sgn<K>(v.type, q, pl)) != kInside) return 0.0;
+  double s = solid_safety_out<K>(v.type, q, pl);
+  if (safety_indexed(G, v, pl, s)) return fmax(s, 0.0);
+  const int off = v.off, cnt = v.cnt, dtype = v.dtype;
   const F3 p32{(float)pl.x, (float)pl.y, (float)pl.z};
   const float pmax = max3f(fabsf(p32.x), fabsf(p32.y), fabsf(p32.z));
   const bool scr = dtype == kBox || dtype == kTubs;
@@ -625,10 +626,10 @@ __device__ __forceinline__ double nav_safety_screened(const DevGeom& G, int pv, 
       const float t32 = (float)(fmax(s, kHalf) + kTol);
       if (lb > fmaf(4.0f * kU32, t32, t32)) continue;
     }
-    const int clv = G.dau_lv[off + k];
+    const DauRec dr = dau_rec(G, off + k);
     const V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(off + k), pl);
-    CQ qc = G.par + G.lv_par[clv];
-    const int tc = G.lv_type[clv];
+    CQ qc = G.par + dr.par;
+    const int tc = lv_rec(G, dr.lv).type;
     if (code_of(solid_sgn<K>(tc, qc, pc)) != kOutside) return 0.0;
     s = fmin(s, solid_safety_in<K>(tc, qc, pc));
   }

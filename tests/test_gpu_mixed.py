@@ -99,3 +99,30 @@ def test_start_volumes_out_of_range():
     good = (pv >= 0) & (pv < 10)
     assert np.array_equal(p0, np.where(good, pv, -1)) and (ns[~good] == 0).all() and (ns[good] > 0).all()
     assert np.array_equal(fl[~good], np.where(pv[~good] == -1, 0, 4))
+
+
+def test_shared_placements():
+    """Volumes whose placement ranges overlap in the blob (the same range, and
+    a part of it) against the same geometry with ranges of their own."""
+    import struct
+    import torch
+    import paper_1512_06637_amd as G
+    e = np.eye(3)
+    kids = [(4, W.rot_z(0.4 * k), np.array([25.0 * (k - 1.5), 10.0 * (k % 2) - 5.0, 0.0])) for k in range(4)]
+    lvs = [W.LV(W.box(300.0, 60.0, 60.0), [(1, e, [-180.0, 0.0, 0.0]), (2, e, [0.0, 0.0, 0.0]), (3, e, [180.0, 0.0, 0.0])]),
+           W.LV(W.box(60.0, 40.0, 40.0), kids), W.LV(W.tubs(0.0, 59.0, 40.0), kids), W.LV(W.box(60.0, 40.0, 40.0), kids[1:]),
+           W.LV(W.box(5.0, 4.0, 20.0), [(5, e, [0.0, 0.0, 1.0])]), W.LV(W.tubs(1.0, 3.0, 10.0), [])]
+    own = W.make_blob(lvs)
+    shared = bytearray(own)
+    for lv, (off, cnt) in ((1, (3, 4)), (2, (3, 4)), (3, (4, 3))):
+        struct.pack_into("<2i", shared, 32 + 32 * lv + 12, off, cnt)
+    t = W.uniform_world_tracks((300.0, 60.0, 60.0), 9001, 5)
+    a = [cuda(v) for v in t.arrays()]
+    got = []
+    for blob in (own, bytes(shared)):
+        with G.Geometry(blob) as g:
+            pv = g.locate(*a[:3])
+            got.append((g.n_pv, pv, g.transport(*a), g.nav_safety(*a[:3], pv)))
+    assert got[0][0] == got[1][0] and torch.equal(got[0][1], got[1][1]) and torch.equal(got[0][3], got[1][3])
+    assert transport_bits_equal(got[0][2], got[1][2])
+    assert (host(got[0][1]) > 8).sum() > 100
