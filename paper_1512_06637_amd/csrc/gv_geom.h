@@ -106,6 +106,9 @@ __device__ __forceinline__ int loc_mode(const LvRec& v, V3 p) {
   return p.x * p.x + p.y * p.y + p.z * p.z < 1e200 ? v.loc : kLocPlain;
 }
 
+__device__ __forceinline__ int phi_sector32(float a) {
+  return min(kPhiSectors - 1, max(0, (int)(a * (kPhiSectors / 4.0f))));
+}
 __device__ __forceinline__ int phi_sector(double a) {
   return min(kPhiSectors - 1, max(0, (int)(a * (kPhiSectors / 4.0))));
 }

@@ -330,7 +330,7 @@ __device__ __forceinline__ void daughters_radial(const DevGeom& G, int r0, int o
   const double A = dl.x * dl.x + dl.y * dl.y, B = pl.x * dl.x + pl.y * dl.y;
   w.add(kWorkRadial);
   const int j = radial_rank(R2, cnt, rho2);
-  auto eval = [&](int m) {
+  auto eval = [&](int m) -> bool {  // whether the ray meets the tube
     const int k = K[m];
     w.add(kWorkFull + kTubs);
     double t = Tubs::full_dist<true>(G.par + dau_rec(G, off + k).par, pl, dl);
@@ -340,6 +340,7 @@ __device__ __forceinline__ void daughters_radial(const DevGeom& G, int r0, int o
       best = t;
       bestk = k;
     }
+    return t < GV_INF;
   };
   auto beyond = [&](double t) { return t - 1e-6 - 1e-12 * t > fmin(best, dout) + kTol; };
   const bool holds = j > 0 && rho2 <= R2[2 * (j - 1) + 1];
@@ -352,9 +353,9 @@ __device__ __forceinline__ void daughters_radial(const DevGeom& G, int r0, int o
     bool go = true;
     if (part == kOutward) {  // larger root of A t^2 + 2 B t + (rho^2 - rmin^2), C < 0
       go = m < cnt;
-      if (go) {
+      if (go && m > j) {  // the first is evaluated at once
         const double C = rho2 - R2[2 * m];
-        const double sq = sqrt(B * B - A * C);
+        const double sq = sqrt_fast(B * B - A * C);
         w.add(kWorkRadBound);
         go = !beyond(B <= 0.0 ? div_fast(sq - B, A) : -div_fast(C, B + sq));
       }
@@ -371,8 +372,14 @@ __device__ __forceinline__ void daughters_radial(const DevGeom& G, int r0, int o
       }
     }
     if (go) {
-      eval(m);
-      if (part == kHolding) part = A > 0.0 ? kOutward : kEnd, m = j;  // parallel to the axis: the radius never changes
+      // A ray moving outward that enters a tube enters the tubes around it
+      // later, by at least the gap to the next (10 um or more are asked for,
+      // far above the rounding of the distances): the walk ends without
+      // their crossing bounds, on three of four world steps.
+      const bool met = eval(m);
+      const double r2 = R2[2 * m + 1];
+      if (met && B >= 0.0 && (m + 1 >= cnt || R2[2 * (m + 1)] > r2 + fma(2e-8, r2, 2e-5 * fmax(1.0, fabs(pl.x) + fabs(pl.y))))) part = kEnd;
+      else if (part == kHolding) part = A > 0.0 ? kOutward : kEnd, m = j;  // parallel to the axis: the radius never changes
       else m += part == kOutward ? 1 : -1;
     } else if (part == kOutward && B < 0.0) {
       part = kInward, m = holds ? j - 2 : j - 1;
@@ -395,23 +402,29 @@ __device__ __forceinline__ void daughters_phi(const DevGeom& G, int lv, int m0, 
                                               double dout, double& best, int& bestk, bool& neg, W& w, int left) {
   const double T = dout + kTol;
   const double A = dl.x * dl.x + dl.y * dl.y;
-  const double tc = A > 0.0 ? fmin(fmax(-div_fast(pl.x * dl.x + pl.y * dl.y, A), 0.0), T) : 0.0;
+  const double Bxy = pl.x * dl.x + pl.y * dl.y;
+  double tc = 0.0;  // closest to the axis: where the ray starts, unless it moves inward
+  if (Bxy < 0.0 && A > 0.0) tc = fmin(-div_fast(Bxy, A), T);
   const double cx = pl.x + tc * dl.x, cy = pl.y + tc * dl.y;
   const double guard = 1e-3 * (fmax(fmax(fabs(pl.x), fabs(pl.y)), fabs(pl.z)) + 1.0);
-  if (!(cx * cx + cy * cy > guard * guard) || !(T < GV_INF)) {
+  // the sectors of both ends in FP32 (angles within 1e-6, masks widened by 1e-4)
+  const float x0 = (float)pl.x, y0 = (float)pl.y;
+  const float x1 = (float)(pl.x + T * dl.x), y1 = (float)(pl.y + T * dl.y);
+  const float s0 = fabsf(x0) + fabsf(y0), s1 = fabsf(x1) + fabsf(y1);
+  if (!(cx * cx + cy * cy > guard * guard) || !(s0 < 1e30f && s1 < 1e30f)) {
     daughters_culled<S, F32>(G, lv, off, cnt, pl, dl, dout, best, bestk, neg, w, left);
     return;
   }
   w.add(kWorkPhi);
-  const double a0 = pseudo_angle_fast(pl.x, pl.y), a1 = pseudo_angle_fast(pl.x + T * dl.x, pl.y + T * dl.y);
   const bool ccw = pl.x * dl.y - pl.y * dl.x >= 0.0;
-  const int s1 = phi_sector(ccw ? a1 : a0);
+  const int c0 = phi_sector32(pseudo_angle32(x0, y0, s0)), c1 = phi_sector32(pseudo_angle32(x1, y1, s1));
+  const int last = ccw ? c1 : c0;
   CQL M = G.phi_mask + (size_t)m0;
   uint64_t cand = 0;
-  for (int s = phi_sector(ccw ? a0 : a1);; s = (s + 1) & (kPhiSectors - 1)) {
+  for (int s = ccw ? c0 : c1;; s = (s + 1) & (kPhiSectors - 1)) {
     cand |= M[s];
     w.add(kWorkPhiSec);
-    if (s == s1) break;
+    if (s == last) break;
   }
   if (S::kType == kBox && left >= 0) cand &= ~(1ull << left);
   // FP32 screen of the bound (as in the culled loop): only when every active
