@@ -1521,9 +1521,12 @@ int lane_transport(gv_geom* g, const LaneCtl& L, int64_t n, const double* x, con
     g->prof_used += 2;
     (void)hipEventRecord(pe[0], s);
   }
-  hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(256), 0, s, g->dg, n, x, y, z, dx, dy, dz, start_pv,
-                     sorted ? (const int32_t*)L.perm : (const int32_t*)nullptr, L.queue, max_steps, out_pv, out_step,
-                     out_nsteps, out_flags, P, out_proc);
+  using D = GIn<double>;
+  const LaneArgs A{g->dg, n, (D)x, (D)y, (D)z, (D)dx, (D)dy, (D)dz, (GIn<int32_t>)start_pv,
+                   (GIn<int32_t>)(sorted ? L.perm : nullptr), (GOut<uint32_t>)L.queue, (GOut<int32_t>)out_pv,
+                   (GOut<double>)out_step, (GOut<int32_t>)out_nsteps, (GOut<uint32_t>)out_flags,
+                   (GOut<int8_t>)out_proc, P, max_steps};
+  hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(256), 0, s, A);
   GV_TRY(launched(fn));
   if (pe) (void)hipEventRecord(pe[1], s);
   return GV_OK;

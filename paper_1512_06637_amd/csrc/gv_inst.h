@@ -11,9 +11,7 @@ namespace gv {
 using StepKernel = void (*)(DevGeom, int, int, int, const int*, const int*, TRec*, const int*, int*, uint32_t*, int*,
                             TCtl, int32_t*, double*, int32_t*, uint32_t*, const int*, double*, int*, int64_t,
                             PhysArgs, int8_t*, int8_t*);
-using LaneKernel = void (*)(DevGeom, int64_t, const double*, const double*, const double*, const double*,
-                            const double*, const double*, const int32_t*, const int32_t*, uint32_t*, int, int32_t*,
-                            double*, int32_t*, uint32_t*, PhysArgs, int8_t*);
+using LaneKernel = void (*)(LaneArgs);
 using StepNavKernel = void (*)(DevGeom, int64_t, const double*, const double*, const double*, const double*,
                                const double*, const double*, const int32_t*, const double*, double*, int32_t*,
                                uint32_t*);

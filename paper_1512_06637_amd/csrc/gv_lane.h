@@ -225,33 +225,59 @@ struct LaneTrack {
   uint64_t procs;  // physics, staged outputs: the process codes of the run, byte k % 8 for step k
 };
 
+// The arguments of a lane transport.  The kernels read them where they need
+// them, through a pointer that the compiler cannot see through (lane_args), so
+// that it loads them again instead of holding 60 scalar registers of pointers
+// through the step loop, where they were spilled to vector registers.
+template <class T>
+using GIn = const __attribute__((address_space(1))) T*;
+template <class T>
+using GOut = __attribute__((address_space(1))) T*;
+struct LaneArgs {
+  DevGeom G;
+  int64_t n;
+  GIn<double> x, y, z, dx, dy, dz;
+  GIn<int32_t> start_pv, perm;
+  GOut<uint32_t> queue;
+  GOut<int32_t> out_pv;
+  GOut<double> out_step;
+  GOut<int32_t> out_nsteps;
+  GOut<uint32_t> out_flags;
+  GOut<int8_t> out_proc;
+  PhysArgs P;
+  int max_steps;
+};
+typedef const __attribute__((address_space(4))) LaneArgs* CLA;
+__device__ __forceinline__ CLA lane_args() {
+  CLA a = (CLA)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  return a;
+}
+
+__device__ __forceinline__ const DevGeom& geom_of(CLA a) { return *(const DevGeom*)&a->G; }
+
 // Starts track i: its volume and entry 0 of its sequence.  Returns false (and
 // writes the track's zero count and flags) when it starts outside the world.
-__device__ __forceinline__ bool lane_begin(const DevGeom& G, LaneTrack& T, int64_t i, const double* __restrict__ x,
-                                           const double* __restrict__ y, const double* __restrict__ z,
-                                           const double* __restrict__ dx, const double* __restrict__ dy,
-                                           const double* __restrict__ dz, const int32_t* __restrict__ start_pv,
-                                           int max_steps, int32_t* __restrict__ out_pv,
-                                           int32_t* __restrict__ out_nsteps, uint32_t* __restrict__ out_flags) {
+__device__ __forceinline__ bool lane_begin(CLA a, LaneTrack& T, int64_t i) {
   T.i = i;
-  T.p = ld3(x, y, z, i);
-  T.d = ld3(dx, dy, dz, i);
+  T.p = V3{a->x[i], a->y[i], a->z[i]};
+  T.d = V3{a->dx[i], a->dy[i], a->dz[i]};
   T.fl = 0u;
   T.k = 0;
   T.zero_run = 0;
   T.left = -1;
   T.safe = 0.0;
   T.procs = 0;
-  int pv = start_pv[i];
-  if (pv < -1 || pv >= G.n_pv) {
+  int pv = a->start_pv[i];
+  if (pv < -1 || pv >= a->G.n_pv) {
     pv = -1;
     T.fl = kFlagLocateFail;
   }
   T.pv = pv;
-  out_pv[(size_t)i * (max_steps + 1)] = pv;
+  a->out_pv[(size_t)i * (a->max_steps + 1)] = pv;
   if (pv < 0) {
-    out_nsteps[i] = 0;
-    out_flags[i] = T.fl;
+    a->out_nsteps[i] = 0;
+    a->out_flags[i] = T.fl;
     return false;
   }
   return true;
@@ -297,17 +323,14 @@ __device__ __forceinline__ void lane_compute(const DevGeom& G, LaneTrack& T, int
 // that started together write their runs in the same iteration, and a full
 // run goes out in 16-byte stores (its process codes in one 8-byte store).
 template <bool PHYS, int ST>
-__device__ __forceinline__ bool lane_record(const DevGeom& G, LaneTrack& T, const LaneStep& R, int max_steps,
-                                            int32_t* __restrict__ out_pv, double* __restrict__ out_step,
-                                            int32_t* __restrict__ out_nsteps, uint32_t* __restrict__ out_flags,
-                                            int8_t* __restrict__ out_proc, LaneStage S) {
+__device__ __forceinline__ bool lane_record(CLA a, LaneTrack& T, const LaneStep& R, LaneStage S) {
   static_assert(ST == 0 || ST == 8, "a staged run is 8 steps (the process codes of a run fill 64 bits)");
   constexpr int kRun = ST > 0 ? ST : 1;
   const int nx = R.nx;
   const double st = R.st;
   if (PHYS) {
     if (ST == 0) {
-      if (out_proc) out_proc[(size_t)T.i * max_steps + T.k] = (int8_t)R.proc;
+      if (a->out_proc) a->out_proc[(size_t)T.i * a->max_steps + T.k] = (int8_t)R.proc;
     } else {
       T.procs |= (uint64_t)(uint8_t)R.proc << (8 * (T.k % 8));
     }
@@ -315,10 +338,10 @@ __device__ __forceinline__ bool lane_record(const DevGeom& G, LaneTrack& T, cons
   // a track that leaves its volume into the mother carries the volume's
   // placement index there (the line does not change, so the volume is behind
   // it); entering a daughter clears it
-  if (nx != T.pv) T.left = R.exited ? pv_rec(G, T.pv).k : -1;
+  if (nx != T.pv) T.left = R.exited ? pv_rec(geom_of(a), T.pv).k : -1;
   if (ST == 0) {
-    out_step[(size_t)T.i * max_steps + T.k] = st;
-    out_pv[(size_t)T.i * (max_steps + 1) + T.k + 1] = nx;
+    a->out_step[(size_t)T.i * a->max_steps + T.k] = st;
+    a->out_pv[(size_t)T.i * (a->max_steps + 1) + T.k + 1] = nx;
   } else {
     S.st[64 * (T.k % kRun)] = st;
     S.pv[64 * (T.k % kRun)] = nx;
@@ -330,7 +353,7 @@ __device__ __forceinline__ bool lane_record(const DevGeom& G, LaneTrack& T, cons
     if (T.zero_run >= 8) {
       T.fl |= kFlagStuck;
       end = true;
-    } else if (T.k == max_steps) {
+    } else if (T.k == a->max_steps) {
       T.fl |= kFlagOverflow;
       end = true;
     }
@@ -338,8 +361,8 @@ __device__ __forceinline__ bool lane_record(const DevGeom& G, LaneTrack& T, cons
   T.pv = nx;
   if (ST > 0 && (end || T.k % kRun == 0)) {
     const int m = (T.k - 1) % kRun + 1, k0 = T.k - m;
-    double* rs = out_step + (size_t)T.i * max_steps + k0;
-    int32_t* rp = out_pv + (size_t)T.i * (max_steps + 1) + k0 + 1;
+    double* rs = (double*)a->out_step + (size_t)T.i * a->max_steps + k0;
+    int32_t* rp = (int32_t*)a->out_pv + (size_t)T.i * (a->max_steps + 1) + k0 + 1;
     if (m == ST) {
       double vs[kRun];
       int32_t vp[kRun];
@@ -356,8 +379,8 @@ __device__ __forceinline__ bool lane_record(const DevGeom& G, LaneTrack& T, cons
       }
     }
     if (PHYS) {
-      if (out_proc) {
-        int8_t* rq = out_proc + (size_t)T.i * max_steps + k0;
+      if (a->out_proc) {
+        int8_t* rq = (int8_t*)a->out_proc + (size_t)T.i * a->max_steps + k0;
         if (m == ST) {
           __builtin_memcpy(rq, &T.procs, 8);
         } else {
@@ -368,8 +391,8 @@ __device__ __forceinline__ bool lane_record(const DevGeom& G, LaneTrack& T, cons
     }
   }
   if (end) {
-    out_nsteps[T.i] = T.k;
-    out_flags[T.i] = T.fl;
+    a->out_nsteps[T.i] = T.k;
+    a->out_flags[T.i] = T.fl;
   }
   return end;
 }
@@ -392,12 +415,7 @@ __device__ __forceinline__ bool lane_record(const DevGeom& G, LaneTrack& T, cons
 // next track at once, which let its new track wait for its class like any
 // other, was measured slower as well: 2.66 against 2.56 ms.)
 template <bool F32, bool PHYS, int K, int WV, int ST, bool CLS = false>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) k_lane_transport(
-    DevGeom G, int64_t n, const double* __restrict__ x, const double* __restrict__ y, const double* __restrict__ z,
-    const double* __restrict__ dx, const double* __restrict__ dy, const double* __restrict__ dz,
-    const int32_t* __restrict__ start_pv, const int32_t* __restrict__ perm, uint32_t* __restrict__ queue,
-    int max_steps, int32_t* __restrict__ out_pv, double* __restrict__ out_step, int32_t* __restrict__ out_nsteps,
-    uint32_t* __restrict__ out_flags, PhysArgs P, int8_t* __restrict__ out_proc) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) k_lane_transport(LaneArgs) {
   constexpr int kStage = ST > 0 ? 4 * ST * 64 : 1;  // 4 wavefronts per workgroup
   __shared__ double stage_st[kStage];
   __shared__ int32_t stage_pv[kStage];
@@ -406,25 +424,28 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
   const LaneStage S{stage_st + wbase, stage_pv + wbase};
   LaneTrack T;
   for (;;) {
+    CLA a = lane_args();
     uint32_t b = 0;
-    if (lane == 0) b = atomicAdd(queue, 64u);
+    if (lane == 0) b = atomicAdd((uint32_t*)a->queue, 64u);
     const int64_t base = (int64_t)__shfl(b, 0);
-    if (base >= n) break;
+    if (base >= a->n) break;
     const int64_t j = base + lane;
     bool live = false;
-    if (j < n) {
-      const int64_t i = perm ? perm[j] : j;
-      live = lane_begin(G, T, i, x, y, z, dx, dy, dz, start_pv, max_steps, out_pv, out_nsteps, out_flags);
-    }
+    if (j < a->n) live = lane_begin(a, T, a->perm ? a->perm[j] : j);
     LaneStep R;
     if (!CLS) {
       while (live) {
-        lane_compute<F32, PHYS, K>(G, T, pv_rec(G, T.pv).lv, T.pv, P, R);
-        live = !lane_record<PHYS, ST>(G, T, R, max_steps, out_pv, out_step, out_nsteps, out_flags, out_proc, S);
+        a = lane_args();
+        const DevGeom& G = geom_of(a);
+        lane_compute<F32, PHYS, K>(G, T, pv_rec(G, T.pv).lv, T.pv, PhysArgs{a->P.seed, a->P.shortcut}, R);
+        live = !lane_record<PHYS, ST>(a, T, R, S);
       }
       continue;
     }
     for (uint64_t lm = __ballot(live); lm; lm = __ballot(live)) {
+      a = lane_args();
+      const DevGeom& G = geom_of(a);
+      const PhysArgs P{a->P.seed, a->P.shortcut};
       int lv = -1, cl = -1;
       if (live) {  // volume and class in one load
         const PvRec v = pv_rec(G, T.pv);
@@ -467,7 +488,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
         }
       }
       if (mine)
-        live = !lane_record<PHYS, ST>(G, T, R, max_steps, out_pv, out_step, out_nsteps, out_flags, out_proc, S);
+        live = !lane_record<PHYS, ST>(a, T, R, S);
     }
   }
 }
