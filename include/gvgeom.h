@@ -299,8 +299,8 @@ int gv_probe_fma64(double* out, int64_t n_lanes, int32_t iters, void* stream);
  *                 volume in the regrouping key (default 2; ignored when
  *                 volumes x cells would exceed 4,096);
  *   solid_block   threads per workgroup of the one-lane-per-track kernels
- *                 (solid-level queries, basket_step/_locate/_nav_*, small
- *                 transports), a multiple of 64 in 64..1024 (default 256);
+ *                 (solid-level queries, basket_locate/_nav_*), a multiple of
+ *                 64 in 64..1024 (default 256);
  *   solid_grid    at most this many workgroups for those kernels (each lane
  *                 then loops over several tracks), >= 1 (default: one lane
  *                 per track);

@@ -596,6 +596,12 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
         ok = qa[L::TB_RMAX] < by_r[m].first;
       }
       if (!ok) continue;
+      // a leading entry holds the largest z half-length
+      double zmax = 0;
+      for (auto& e : by_r) zmax = std::max(zmax, par[lv_par[dau_lv[o + e.second]] + L::TB_DZ]);
+      rad_r2.push_back(zmax);
+      rad_r2.push_back(0.0);
+      rad_k.push_back(-1);
       lv_rad[i] = (int)rad_k.size();
       for (auto& e : by_r) {
         const double* q = par.data() + lv_par[dau_lv[o + e.second]];
@@ -657,7 +663,12 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
       }
       if (!ok) continue;
       lv_phi[i] = (int)phi_mask.size();
-      phi_mask.insert(phi_mask.end(), m.begin(), m.end());
+      for (int l = 0; l < kPhiLevels; ++l) {
+        phi_mask.insert(phi_mask.end(), m.begin(), m.end());
+        std::vector<unsigned long long> up(kPhiSectors);
+        for (int s = 0; s < kPhiSectors; ++s) up[s] = m[s] | m[(s + (1 << l)) % kPhiSectors];
+        m.swap(up);
+      }
     }
     // step class of each LV: the branch its steps take in the step code (the
     // mother's solid type and how the daughters are reached), for the lane
@@ -769,6 +780,11 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
         delta += std::max(0L, subtree[dau_lv[k]]);  // -1: not reached from the world
       }
     }
+    std::vector<int> lv_slot(n_lv), by_class(n_lv);
+    for (int i = 0; i < n_lv; ++i) by_class[i] = i;
+    std::stable_sort(by_class.begin(), by_class.end(), [&](int u, int v) { return lv_class[u] < lv_class[v]; });
+    for (int i = 0; i < n_lv; ++i)
+      lv_slot[by_class[i]] = n_lv <= kLvSlots ? i : (int)((int64_t)i * kLvSlots / n_lv);
     std::vector<PvRec> pvr(npv);
     for (long i = 0; i < npv; ++i) pvr[i] = PvRec{T.pv_lv[i], lv_class[T.pv_lv[i]], T.pv_parent[i], pv_k[i]};
 
@@ -795,6 +811,7 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
         {rad_r2.data(), rad_r2.size() * 8, 0},
         {rad_k.data(), rad_k.size() * 4, 0},
         {phi_mask.data(), phi_mask.size() * 8, 0},
+        {lv_slot.data(), lv_slot.size() * 4, 0},
         {nullptr, 5 * 8, 0}};
     size_t total = 0;
     for (auto& p : parts) {
@@ -849,7 +866,8 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
     D.rad_r2 = (CQ)(base + parts[13].off);
     D.rad_k = (CQI)(base + parts[14].off);
     D.phi_mask = (CQL)(base + parts[15].off);
-    g->pcon_work = (unsigned long long*)(base + parts[16].off);  // zeroed by the upload
+    D.lv_slot = (CQI)(base + parts[16].off);
+    g->pcon_work = (unsigned long long*)(base + parts[17].off);  // zeroed by the upload
     g->n_lv = n_lv;
     g->n_pv = (int)npv;
     g->n_place = n_place;
@@ -1151,9 +1169,9 @@ extern "C" int basket_step(gv_geom* g, int64_t n, const double* x, const double*
   GV_TRY(check_i32(fn, "out_next_pv", out_next_pv));
   GV_TRY(check_i32(fn, "out_flags", out_flags, true));
   DeviceGuard dgd(g->device);
-  const auto kern = step_nav_kernel(g->kind, precision == GV_FP32_REFINE);
-  hipLaunchKernelGGL(kern, dim3(lane_shape(g, n).grid), dim3(lane_shape(g, n).block), 0,
-                     (hipStream_t)stream, g->dg, n, x, y, z, dx, dy, dz, pv, pstep, out_step, out_next_pv, out_flags);
+  hipLaunchKernelGGL(step_nav_kernel(g->kind, precision == GV_FP32_REFINE), dim3((unsigned)((n + kStepTile - 1) / kStepTile)),
+                     dim3(kStepTile), 0, (hipStream_t)stream, g->dg, n, x, y, z, dx, dy, dz, pv, pstep, out_step,
+                     out_next_pv, out_flags);
   return launched(fn);
 }
 

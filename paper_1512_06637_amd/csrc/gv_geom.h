@@ -31,10 +31,12 @@ struct PvRec {
 
 // All arrays live in HBM; geom_load fills them once.  Transforms are 12
 // doubles: R row-major then t, with x_mother = R x_child + t.
-constexpr int kPhiSectors = 256;
+constexpr int kPhiSectors = 256, kPhiLevels = 8;
+constexpr int kLvSlots = 1024;  // slots of the LVs in the regrouped kernels
 
 struct DevGeom {
   int n_lv, n_pv, n_place;
+  CQI lv_slot;       // [n_lv] place of each LV in order of step class, then number (scaled into kLvSlots)
   CQ4 lv_rec;        // [n_lv][2] records of LvRec, one 32-byte load
   CQ par;            // derived solid parameters
   CQ dau_xf;         // [n_place][12] placement transform, LV frame
@@ -52,12 +54,12 @@ struct DevGeom {
   CQF grp_box32;     // [n_grp][8] union of the group's FP32 boxes; 2 unused
   // radial order: an LV whose daughters are identity-placed full tubes with
   // disjoint radial ranges lists them by radius
-  CQ rad_r2;         // [n_rad][2] rmin^2, rmax^2 in radial order
+  CQ rad_r2;         // [n_rad][2] rmin^2, rmax^2 in radial order; before an LV's first: its largest z half-length, 0
   CQI rad_k;         // [n_rad] daughter index (placement order) of each entry
   // phi sectors: an LV whose (<= 64) daughters lie around the z axis, each
   // within less than a half turn, has kPhiSectors masks of the daughters
   // whose angular extent (widened) meets each sector of pseudo-angle
-  CQL phi_mask;      // [n_phi_lv][kPhiSectors]
+  CQL phi_mask;      // [n_phi_lv][kPhiLevels][kPhiSectors]: at level l the union of the 2^l masks from each sector on
   // materials for physics-limited steps (geom_set_materials); n_mat 0 if unset
   int n_mat, n_proc;
   CQ mat_rate;       // [n_mat][n_proc] n sigma = 1 / mean free path, 1/mm
@@ -111,6 +113,15 @@ __device__ __forceinline__ int phi_sector32(float a) {
 }
 __device__ __forceinline__ int phi_sector(double a) {
   return min(kPhiSectors - 1, max(0, (int)(a * (kPhiSectors / 4.0))));
+}
+
+// Union of the masks of sectors first..last, going up around the circle: two
+// runs of the largest power of two that fits.  (Read one by one, a track moving
+// along a layer waited for up to 128 masks, one after another.)
+__device__ __forceinline__ uint64_t phi_range(CQL M, int first, int last) {
+  const int n = ((last - first) & (kPhiSectors - 1)) + 1, l = min(kPhiLevels - 1, 31 - __clz(n));
+  CQL R = M + l * kPhiSectors;
+  return R[first] | R[(last + 1 - (1 << l)) & (kPhiSectors - 1)];
 }
 
 // Radial entries with rmin^2 <= rho^2 (ascending).  Four at a time while every
@@ -251,11 +262,7 @@ __device__ __forceinline__ bool safety_indexed(const DevGeom& G, const LvRec& v,
     const double w = 1.5707964 * 1.7320509 * limit() * rcp_fast(r) + 1e-6;  // pi/2 sin(angle)
     if (w < 0.5) {
       const double b0 = a - w, b1 = a + w;
-      const int s1 = phi_sector(b1 >= 4.0 ? b1 - 4.0 : b1);
-      for (int c = phi_sector(b0 < 0.0 ? b0 + 4.0 : b0);; c = (c + 1) & (kPhiSectors - 1)) {
-        cand |= M[c];
-        if (c == s1) break;
-      }
+      cand = phi_range(M, phi_sector(b0 < 0.0 ? b0 + 4.0 : b0), phi_sector(b1 >= 4.0 ? b1 - 4.0 : b1));
     } else {
       cand = all;
     }

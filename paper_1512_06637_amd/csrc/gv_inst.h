@@ -38,7 +38,7 @@ LaneKernel lane_kernel_phys64(int waves, bool stage, bool cls);
 LaneKernel lane_kernel_phys32(int waves, bool stage, bool cls);
 LaneKernel lane_kernel_composites(bool fp32, bool phys);
 
-// ComputeStep with each lane in its own volume, and the serving round.
+// ComputeStep of a basket, and the serving round.
 StepNavKernel step_nav_kernel(int kind, bool fp32);
 ServeKernel serve_kernel(int kind);
 

@@ -39,7 +39,6 @@ __global__ void __launch_bounds__(256) k_serve(DevGeom G, const SDesc* __restric
   const int lane = __lane_id();
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / 64;
   const int64_t nwaves = (int64_t)gridDim.x * blockDim.x / 64;
-  NoWork w;
   for (int64_t t = wave; t < ntiles; t += nwaves) {
     int lo = 0, hi = nb - 1;  // largest b with t0[b] <= t
     while (lo < hi) {
@@ -59,15 +58,9 @@ __global__ void __launch_bounds__(256) k_serve(DevGeom G, const SDesc* __restric
       const V3 d{X[3 * n + i], X[4 * n + i], X[5 * n + i]};
       const double ps = X[6 * n + i];
       const int v = ((const int32_t*)(X + 7 * n))[i];
-      uint32_t fl = 0;
-      int nx = -1;
-      double st = 0.0;
-      if (v >= 0 && v < G.n_pv) {
-        st = prec == 0 ? step_culled_limited<false, K>(G, v, p, d, ps, &nx, &fl, w)
-                       : step_culled_limited<true, K>(G, v, p, d, ps, &nx, &fl, w);
-      } else {
-        fl = kFlagLocateFail;
-      }
+      uint32_t fl;
+      int nx;
+      const double st = prec == 0 ? step_query<false, K>(G, v, p, d, ps, &nx, &fl) : step_query<true, K>(G, v, p, d, ps, &nx, &fl);
       double* os = (double*)O;
       int32_t* on = (int32_t*)(os + n);
       uint32_t* of = (uint32_t*)(on + n);

@@ -321,7 +321,7 @@ constexpr int kCullMin = 8;  // LVs with fewer daughters run the plain loop
 // within kTolerance / 2 of rmax (not inside), so the tube's DistanceToIn would
 // return +inf.  Equal distances keep the lowest placement index, as the plain
 // loop does.
-template <class W>
+template <bool ENDS, class W>
 __device__ __forceinline__ void daughters_radial(const DevGeom& G, int r0, int off, int cnt, V3 pl, V3 dl,
                                                  double dout, double& best, int& bestk, bool& neg, W& w) {
   CQ R2 = G.rad_r2 + 2 * (size_t)r0;
@@ -342,7 +342,23 @@ __device__ __forceinline__ void daughters_radial(const DevGeom& G, int r0, int o
     }
     return t < GV_INF;
   };
-  auto beyond = [&](double t) { return t - 1e-6 - 1e-12 * t > fmin(best, dout) + kTol; };
+  // ENDS: no tube is entered after the ray has left the longest one's z range
+  // for good.  For single steps of tracks anywhere (one beyond the tubes' ends
+  // evaluated them all while its wavefront waited: 2^20 steps 121 against 109
+  // us); transports from the middle meet it too seldom to pay for the test
+  // (2.03 against 2.04 ms per 400,003 physics-limited tracks).
+  double far = dout;
+  if (ENDS) {
+    const double zmax = R2[-2];
+    if (dl.z != 0.0) {
+      const double tz = (copysign(zmax, dl.z) - pl.z) * rcp_fast(dl.z);
+      if (tz < -1e-3) return;
+      far = fmin(dout, tz + 1e-6);
+    } else if (fabs(pl.z) > zmax + 1e-3) {
+      return;
+    }
+  }
+  auto beyond = [&](double t) { return t - 1e-6 - 1e-12 * t > fmin(best, far) + kTol; };
   const bool holds = j > 0 && rho2 <= R2[2 * (j - 1) + 1];
   // one loop over the three parts of the walk, so that the tube's code is there
   // once: the tube holding the point, then outward, then inward
@@ -376,7 +392,9 @@ __device__ __forceinline__ void daughters_radial(const DevGeom& G, int r0, int o
       // later, by at least the gap to the next (10 um or more are asked for,
       // far above the rounding of the distances): the walk ends without
       // their crossing bounds, on three of four world steps.
-      const bool met = eval(m);
+      // lanes at the same tube read its table as scalars
+      const int mu = __builtin_amdgcn_readfirstlane(m);
+      const bool met = __ballot(m != mu) == 0 ? eval(mu) : eval(m);
       const double r2 = R2[2 * m + 1];
       if (met && B >= 0.0 && (m + 1 >= cnt || R2[2 * (m + 1)] > r2 + fma(2e-8, r2, 2e-5 * fmax(1.0, fabs(pl.x) + fabs(pl.y))))) part = kEnd;
       else if (part == kHolding) part = A > 0.0 ? kOutward : kEnd, m = j;  // parallel to the axis: the radius never changes
@@ -392,8 +410,8 @@ __device__ __forceinline__ void daughters_radial(const DevGeom& G, int r0, int o
 // Daughters by phi sector: the ray's segment [0, exit + kTolerance] seen from
 // the z axis sweeps an angle of less than a half turn (it does not pass within
 // 1e-3 (|p|inf + 1) mm of the axis, else the culled loop runs instead); the
-// union of the masks of the sectors it sweeps holds every daughter whose
-// extent it can meet, and those candidates go through the SafetyToIn bound
+// union of the masks of the sectors it sweeps (phi_range) holds every daughter
+// whose extent it can meet, and those candidates go through the SafetyToIn bound
 // and DistanceToIn in index order, as in the culled loop's second pass.
 // left: the index of a box daughter the ray has left (-1: none); a straight
 // ray leaves a convex solid once, so it is not a candidate.
@@ -418,14 +436,9 @@ __device__ __forceinline__ void daughters_phi(const DevGeom& G, int lv, int m0, 
   w.add(kWorkPhi);
   const bool ccw = pl.x * dl.y - pl.y * dl.x >= 0.0;
   const int c0 = phi_sector32(pseudo_angle32(x0, y0, s0)), c1 = phi_sector32(pseudo_angle32(x1, y1, s1));
-  const int last = ccw ? c1 : c0;
   CQL M = G.phi_mask + (size_t)m0;
-  uint64_t cand = 0;
-  for (int s = ccw ? c0 : c1;; s = (s + 1) & (kPhiSectors - 1)) {
-    cand |= M[s];
-    w.add(kWorkPhiSec);
-    if (s == last) break;
-  }
+  uint64_t cand = phi_range(M, ccw ? c0 : c1, ccw ? c1 : c0);
+  w.add(kWorkPhiSec, 2);
   if (S::kType == kBox && left >= 0) cand &= ~(1ull << left);
   // FP32 screen of the bound (as in the culled loop): only when every active
   // lane's point and exit lie in the range the FP32 margins cover
@@ -476,7 +489,7 @@ __device__ __forceinline__ void daughters_phi(const DevGeom& G, int lv, int m0, 
 // left: placement index of a box daughter of lv the track has left along its
 // present line (-1: none), which the ray cannot meet again; *exited (if given)
 // says whether the step ends at the mother's exit.
-template <bool F32, int K, class W>
+template <bool F32, int K, bool ENDS = false, class W>
 __device__ __forceinline__ double step_culled(const DevGeom& G, int lv, int pv, V3 p, V3 d, int* next,
                                               uint32_t* flags, W& w, int left = -1, bool* exited = nullptr) {
   CQ X = G.pv_gxf + 12 * (size_t)pv;
@@ -494,7 +507,7 @@ __device__ __forceinline__ double step_culled(const DevGeom& G, int lv, int pv, 
   bool neg = false;
   using Tube = std::conditional_t<K == kBoxTube, FullTubs, Tubs>;
   if (rad >= 0) {
-    daughters_radial(G, rad, off, cnt, pl, dl, dout, best, bestk, neg, w);
+    daughters_radial<ENDS>(G, rad, off, cnt, pl, dl, dout, best, bestk, neg, w);
   } else if (phs >= 0 && dtype == kBox) {
     daughters_phi<Box, F32>(G, lv, phs, off, cnt, pl, dl, dout, best, bestk, neg, w, left);
   } else if (phs >= 0 && dtype == kTubs) {
@@ -550,10 +563,10 @@ __device__ __forceinline__ double step_culled(const DevGeom& G, int lv, int pv, 
 // ComputeStep with a physics limit: as step_culled, then the physics length
 // wins when it is below both the daughter minimum and the exit.
 template <bool F32, int K, class W>
-__device__ __forceinline__ double step_culled_limited(const DevGeom& G, int pv, V3 p, V3 d, double pstep, int* next,
-                                                      uint32_t* flags, W& w) {
+__device__ __forceinline__ double step_culled_limited(const DevGeom& G, int lv, int pv, V3 p, V3 d, double pstep,
+                                                      int* next, uint32_t* flags, W& w) {
   int nx;
-  const double s = step_culled<F32, K>(G, pv_rec(G, pv).lv, pv, p, d, &nx, flags, w);
+  const double s = step_culled<F32, K, true>(G, lv, pv, p, d, &nx, flags, w);
   // s is the daughter minimum when a daughter was chosen, else the exit
   if (pstep < s) {
     *next = pv;
@@ -649,30 +662,102 @@ __device__ __forceinline__ double nav_safety_screened(const DevGeom& G, int pv, 
   return fmax(s, 0.0);
 }
 
-// --------------------------------------------------------- per-lane kernels
-// ComputeStep for every track of a basket, each lane in its own volume.
-template <bool F32, int K>
-__global__ void k_step_nav(DevGeom G, int64_t n, const double* __restrict__ x, const double* __restrict__ y,
-                           const double* __restrict__ z, const double* __restrict__ dx, const double* __restrict__ dy,
-                           const double* __restrict__ dz, const int32_t* __restrict__ pv,
-                           const double* __restrict__ pstep, double* __restrict__ out_step,
-                           int32_t* __restrict__ out_next, uint32_t* __restrict__ out_flags) {
-  NoWork w;
-  for (int64_t i = gtid(); i < n; i += gstride()) {
-    int v = pv[i];
-    uint32_t fl = 0;
-    int nx = -1;
-    double st = 0.0;
-    if (v >= 0 && v < G.n_pv) {
-      st = step_culled_limited<F32, K>(G, v, ld3(x, y, z, i), ld3(dx, dy, dz, i), pstep ? pstep[i] : GV_INF, &nx, &fl,
-                                    w);
-    } else {
-      fl = kFlagLocateFail;
-    }
-    out_step[i] = st;
-    out_next[i] = nx;
-    if (out_flags) out_flags[i] = fl;
+// ----------------------------------------------------- regrouped step kernels
+// A basket's tracks sit in any volume.  Taken 64 at a time as they come, a
+// wavefront runs the step code of the world, of the layers and of the modules one
+// after another with 18 % of its lanes active.  So a workgroup takes a tile of
+// tracks and its wavefronts take them ordered by their volumes' slots (LVs in
+// order of step class, then number; counting sort in LDS): most wavefronts then
+// run one class, many one volume, whose tables come as scalars.  The order within
+// a slot is that of LDS atomics, which no output depends on.
+// Tiles of 256 tracks: of larger ones a workgroup takes several rounds, one
+// after another, and the basket has fewer workgroups (2^20 tracks 121 / 118 / 118
+// / 152 us with 256 / 512 / 1024 / 2048, 2^18 tracks 47 / 67 / 81 / 113 us).
+constexpr int kStepTile = 256;
+
+struct StepGroup {
+  uint32_t place[kLvSlots];   // counts, then first places of the slots
+  uint32_t part[4];
+  uint16_t list[kStepTile];   // the tile's tracks in slot order
+};
+
+// Orders the m (<= kStepTile) tracks of a tile, pv pointing at its first; a
+// workgroup of kStepTile threads.  Tracks without a valid volume go to slot 0.
+__device__ __forceinline__ void step_regroup(const DevGeom& G, const int32_t* __restrict__ pv, int m, StepGroup& S) {
+  const int t = threadIdx.x, slots = min(G.n_lv, kLvSlots);
+  for (int c = t; c < slots; c += kStepTile) S.place[c] = 0u;
+  __syncthreads();
+  int slot = 0;
+  uint32_t rank = 0;
+  if (t < m) {
+    const int v = pv[t];
+    if (v >= 0 && v < G.n_pv) slot = G.lv_slot[pv_rec(G, v).lv];
+    rank = atomicAdd(&S.place[slot], 1u);
   }
+  __syncthreads();
+  // exclusive scan of the counts, kPer slots a thread
+  constexpr int kPer = kLvSlots / kStepTile;
+  uint32_t c[kPer], sum = 0;
+  for (int q = 0; q < kPer; ++q) {
+    const int k = kPer * t + q;
+    c[q] = k < slots ? S.place[k] : 0u;
+    sum += c[q];
+  }
+  uint32_t inc = sum;
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t u = __shfl_up(inc, o);
+    if ((int)__lane_id() >= o) inc += u;
+  }
+  if (__lane_id() == 63) S.part[t / 64] = inc;
+  __syncthreads();
+  uint32_t run = inc - sum;
+  for (int w = 0; w < t / 64; ++w) run += S.part[w];
+  for (int q = 0; q < kPer; ++q) {
+    const int k = kPer * t + q;
+    if (k < slots) S.place[k] = run;
+    run += c[q];
+  }
+  __syncthreads();
+  if (t < m) S.list[S.place[slot] + rank] = (uint16_t)t;
+  __syncthreads();
+}
+
+// ComputeStep of one track; lanes that share a logical volume run it with that
+// volume as a wavefront-uniform value.
+template <bool F32, int K>
+__device__ __forceinline__ double step_query(const DevGeom& G, int v, V3 p, V3 d, double ps, int* next, uint32_t* flags) {
+  NoWork w;
+  *next = -1;
+  *flags = 0u;
+  if (!(v >= 0 && v < G.n_pv)) {
+    *flags = kFlagLocateFail;
+    return 0.0;
+  }
+  const int lv = pv_rec(G, v).lv, lv0 = __builtin_amdgcn_readfirstlane(lv);
+  if (__ballot(lv != lv0) == 0) return step_culled_limited<F32, K>(G, lv0, v, p, d, ps, next, flags, w);
+  return step_culled_limited<F32, K>(G, lv, v, p, d, ps, next, flags, w);
+}
+
+// ComputeStep for every track of a basket, a tile per workgroup.
+template <bool F32, int K>
+__global__ void __launch_bounds__(kStepTile) k_step_nav(DevGeom G, int64_t n, const double* __restrict__ x,
+                                                        const double* __restrict__ y, const double* __restrict__ z,
+                                                        const double* __restrict__ dx, const double* __restrict__ dy,
+                                                        const double* __restrict__ dz, const int32_t* __restrict__ pv,
+                                                        const double* __restrict__ pstep,
+                                                        double* __restrict__ out_step, int32_t* __restrict__ out_next,
+                                                        uint32_t* __restrict__ out_flags) {
+  __shared__ StepGroup S;
+  const int64_t base = (int64_t)blockIdx.x * kStepTile;
+  const int m = (int)min((int64_t)kStepTile, n - base);
+  step_regroup(G, pv + base, m, S);
+  if ((int)threadIdx.x >= m) return;
+  const int64_t i = base + S.list[threadIdx.x];
+  int nx;
+  uint32_t fl;
+  out_step[i] = step_query<F32, K>(G, pv[i], ld3(x, y, z, i), ld3(dx, dy, dz, i), pstep ? pstep[i] : GV_INF, &nx, &fl);
+  out_next[i] = nx;
+  if (out_flags) out_flags[i] = fl;
 }
 
 template <int K>
