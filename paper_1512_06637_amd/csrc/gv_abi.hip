@@ -1007,11 +1007,22 @@ int check_nav_precision(const char* fn, int32_t precision) {
   return GV_OK;
 }
 
-// Workgroups of the compacting polycone kernel: 4 wavefronts of 4 x 64 tracks
-// each (on 2^20 full-set tracks, DistanceToIn 56.6 / 45.2 / 43.2 / 49.9 /
-// 70.7 us at 1 / 2 / 4 / 8 / 16 chunks of 64 per wavefront: fewer leave the
-// queues short of 64 rays, more leave too few wavefronts to hide latency).
-unsigned pcon_grid(int64_t n) { return (unsigned)std::max<int64_t>(1, (n + 1023) / 1024); }
+// Workgroups of the compacting polycone kernel, 4 wavefronts each: one chunk of
+// 64 tracks per wavefront until 1,024 workgroups fill the chip, then more per
+// wavefront, at most four.  Fewer chunks than that leave the queues short of 64
+// rays (2^20 tracks, all four answers: 92 / 78 / 73 / 86 us at 1 / 2 / 4 / 6),
+// more on a chip that is not full make a serial chain of walks (65,536 tracks
+// and below: 24 us at one, 31 at two, 45 at four).
+static_assert(kMaxNz <= Pcon::kMaxPlanes, "the sections of a polycone fit its kernel's table");
+unsigned pcon_grid(int64_t n) {
+  return (unsigned)std::max<int64_t>(1, std::min((n + 255) / 256, std::max<int64_t>(1024, (n + 1023) / 1024)));
+}
+
+// DistanceToOut has half of its rays walk, so that one lane per track is as
+// good until the chip is full several times over: 18.9 against 18.1 us on 2^18
+// tracks (9.0 against 9.7 on 301), 28.9 against 27.3 on 2^19, 44.7 against 40.5
+// on 2^20 and 156 against 110 on 2^22.
+constexpr int64_t kPconOutCompact = 1 << 19;
 
 // With GV_PROF_WORK, a polycone query is followed by the kernel that counts
 // its walk's work (profiling only; the query's outputs are untouched).
@@ -1086,9 +1097,12 @@ extern "C" int basket_distance(gv_geom* g, int32_t lv, int32_t dir, int64_t n, c
   CQ q = g->dg.par + g->lv_par[lv];
   hipStream_t s = (hipStream_t)stream;
   const Shape sh = lane_shape(g, n);
-  if (g->lv_type[lv] == kPcon && dir == GV_TO_IN) {
+  if (g->lv_type[lv] == kPcon && dir == GV_TO_OUT && n >= kPconOutCompact) {
+    hipLaunchKernelGGL(k_pcon_compact<1>, dim3(pcon_grid(n)), dim3(256), 0, s, q, n, x, y, z, dx, dy, dz, nullptr,
+                       nullptr, nullptr, out);
+  } else if (g->lv_type[lv] == kPcon && dir == GV_TO_IN) {
     // walking rays compacted per wavefront (43 against 53 us on 2^20 full-set
-    // tracks; DistanceToOut, where half of the rays walk, gains nothing)
+    // tracks before the sections were in LDS, 37 since)
     hipLaunchKernelGGL(k_pcon_compact<0>, dim3(pcon_grid(n)), dim3(256), 0, s, q, n, x, y, z, dx, dy, dz, nullptr,
                        nullptr, out, nullptr);
   } else if (dir == GV_TO_IN) {
@@ -1126,7 +1140,8 @@ extern "C" int basket_solid_all(gv_geom* g, int32_t lv, int64_t n, const double*
 #define CALL(S)                                                                                          \
   hipLaunchKernelGGL(k_solid_all<S>, dim3(sh.grid), dim3(sh.block), 0, s, q, n, x, y, z, dx, dy, dz, out_inside, \
                      out_safety, out_dist_in, out_dist_out)
-  if (g->lv_type[lv] == kPcon) {  // walking rays compacted per wavefront (85 against 111 us)
+  if (g->lv_type[lv] == kPcon) {  // walking rays compacted per wavefront (85 against 111 us,
+                                     // 72 with the sections in LDS)
     hipLaunchKernelGGL(k_pcon_compact<2>, dim3(pcon_grid(n)), dim3(256), 0, s, q, n, x, y, z, dx, dy, dz, out_inside,
                        out_safety, out_dist_in, out_dist_out);
   } else {

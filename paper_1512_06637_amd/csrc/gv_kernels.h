@@ -19,6 +19,13 @@ __global__ void k_inside(CQ q, int64_t n, const double* __restrict__ x,
 
 template <class S>
 __device__ __forceinline__ double safety_value(CQ q, V3 p, int side, int c) {
+  if constexpr (S::kType == kPcon) {
+    // both safeties are the distance to the boundary: computed once, not in the
+    // two branches below, which nearly every wavefront takes both of
+    const bool wrong = side == 1 ? c == kInside : side == 2 && c == kOutside;
+    if (wrong) return -1.0;
+    return c == kSurface ? 0.0 : fmax(S::safety_in(q, p), 0.0);
+  }
   if (side == 1) {  // SafetyToIn
     if (c == kInside) return -1.0;
     if (c == kSurface) return 0.0;
@@ -85,10 +92,10 @@ __global__ void k_solid_all(CQ q, int64_t n, const double* __restrict__ x,
 // steps as in Pcon::dist_in / dist_out (inside test, bounding-cylinder
 // interval, walk), so the values are those of the one-lane-per-track kernels.
 // KIND 0: DistanceToIn into o_din; 2: all four answers (k_solid_all's
-// outputs, any of them NULL); 1: DistanceToOut into o_dout (not launched: half
-// of the rays walk there, and compacting them measured no faster than the
-// one-lane-per-track kernel).  Each wavefront takes 64 tracks at a time,
-// grid-stride.
+// outputs, any of them NULL); 1: DistanceToOut into o_dout (large baskets).
+// Bound by the walks' VALU work and their chain of section after section, not
+// by memory (all four answers of 2^20 tracks: 72 us, 16 of them traffic; 82
+// before the sections lay in LDS and the boundary was evaluated once).
 struct PconQueue {
   int64_t* idx;   // [128] queued tracks
   double* t0;     // [128] DistanceToIn walks: the bounding-cylinder interval
@@ -115,8 +122,8 @@ __device__ __forceinline__ void pcon_push(PconQueue& Q, bool take, int64_t i, do
 
 // Walks the first min(n, 64) queued rays (all of them when all), one per lane,
 // and drops them from the queue.
-template <bool IN>
-__device__ __forceinline__ void pcon_walk(CQ q, PconQueue& Q, bool all, const double* __restrict__ x,
+template <bool IN, class V>
+__device__ __forceinline__ void pcon_walk(const V& v, PconQueue& Q, bool all, const double* __restrict__ x,
                                           const double* __restrict__ y, const double* __restrict__ z,
                                           const double* __restrict__ dx, const double* __restrict__ dy,
                                           const double* __restrict__ dz, double* __restrict__ out) {
@@ -125,7 +132,7 @@ __device__ __forceinline__ void pcon_walk(CQ q, PconQueue& Q, bool all, const do
     if (lane < Q.n) {
       const int64_t j = Q.idx[lane];
       const V3 p = ld3(x, y, z, j), d = ld3(dx, dy, dz, j);
-      out[j] = IN ? Pcon::walk(q, p, d, true, nullptr, Q.t0[lane], Q.t1[lane]) : Pcon::walk(q, p, d, false);
+      out[j] = IN ? Pcon::walk(v, p, d, true, nullptr, Q.t0[lane], Q.t1[lane]) : Pcon::walk(v, p, d, false);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -153,6 +160,15 @@ __global__ void __launch_bounds__(256) k_pcon_compact(CQ q, int64_t n, const dou
                                                       double* __restrict__ o_dout) {
   __shared__ int64_t s_in[4][128], s_out[4][128];
   __shared__ double s_t0[4][128], s_t1[4][128];
+  // the sections in LDS: a lane reads those of the section it is in, which as
+  // gathers from the tables were the longest part of a walk's steps (2^20
+  // tracks: DistanceToIn 42.6 to 37 us)
+  __shared__ double tab[Pcon::kSections * Pcon::kMaxPlanes];
+  const int nz = (int)q[0];
+  for (int k = threadIdx.x; k < 8 * nz - 5; k += 256) tab[k] = q[1 + k];
+  __syncthreads();
+  const auto v = Pcon::sections<const __attribute__((address_space(3))) double*>(
+      nz, (const __attribute__((address_space(3))) double*)tab);
   const int w = threadIdx.x / 64, lane = __lane_id();
   const bool want_in = KIND == 0 || (KIND == 2 && o_din);
   const bool want_out = KIND == 1 || (KIND == 2 && o_dout);
@@ -164,7 +180,7 @@ __global__ void __launch_bounds__(256) k_pcon_compact(CQ q, int64_t n, const dou
     double t0 = 0.0, t1 = 0.0;
     if (i < n) {
       const V3 p = ld3(x, y, z, i), d = ld3(dx, dy, dz, i);
-      const double sg = Pcon::sgn(q, p);
+      const double sg = Pcon::sgn_of(v, p);
       const int c = code_of(sg);
       if (KIND == 2 && o_in) o_in[i] = (int8_t)c;
       if (KIND == 2 && o_saf) o_saf[i] = safety_value<Pcon>(q, p, 0, c);
@@ -191,15 +207,15 @@ __global__ void __launch_bounds__(256) k_pcon_compact(CQ q, int64_t n, const dou
     }
     if (want_in) {
       pcon_push(Qi, walk_in, i, t0, t1);
-      pcon_walk<true>(q, Qi, false, x, y, z, dx, dy, dz, o_din);
+      pcon_walk<true>(v, Qi, false, x, y, z, dx, dy, dz, o_din);
     }
     if (want_out) {
       pcon_push(Qo, walk_out, i, 0.0, 0.0);
-      pcon_walk<false>(q, Qo, false, x, y, z, dx, dy, dz, o_dout);
+      pcon_walk<false>(v, Qo, false, x, y, z, dx, dy, dz, o_dout);
     }
   }
-  if (want_in) pcon_walk<true>(q, Qi, true, x, y, z, dx, dy, dz, o_din);
-  if (want_out) pcon_walk<false>(q, Qo, true, x, y, z, dx, dy, dz, o_dout);
+  if (want_in) pcon_walk<true>(v, Qi, true, x, y, z, dx, dy, dz, o_din);
+  if (want_out) pcon_walk<false>(v, Qo, true, x, y, z, dx, dy, dz, o_dout);
 }
 
 // Work of the polycone distance queries (profiling only, no outputs): per
@@ -228,14 +244,14 @@ static __global__ void k_pcon_work(CQ q, int dir, int64_t n, const double* __res
         ++c[2];
       } else {
         int ns = 0;
-        (void)Pcon::walk<true>(q, p, d, true, &ns, fmax(B.lo, 0.0), B.hi);
+        (void)Pcon::walk<true>(Pcon::view(q), p, d, true, &ns, fmax(B.lo, 0.0), B.hi);
         c[0] += ns;
         ++c[3];
       }
     }
     if (dir != 0 && code != kOutside) {
       int ns = 0;
-      (void)Pcon::walk<true>(q, p, d, false, &ns);
+      (void)Pcon::walk<true>(Pcon::view(q), p, d, false, &ns);
       c[1] += ns;
       ++c[4];
     }

@@ -675,22 +675,35 @@ struct Trd {
 // ================================================================= POLYCONE
 struct Pcon {
   static constexpr int kType = kPcon;
-  struct View {
+  // The sections, in the geometry's tables or in a copy of them (kSections
+  // doubles per plane from z on) in LDS.
+  static constexpr int kMaxPlanes = 64, kSections = 8;
+  template <class P>
+  struct Sections {
     int nz;
-    CQ z, rmin, rmax, bo, co, bi, ci, inner, ilo, ili, icap;
+    P z, rmin, rmax, bo, co, bi, ci, inner;
+  };
+  template <class P>
+  __device__ static __forceinline__ Sections<P> sections(int nz, P z) {
+    Sections<P> v;
+    v.nz = nz;
+    v.z = z;
+    v.rmin = v.z + nz;
+    v.rmax = v.rmin + nz;
+    v.bo = v.rmax + nz;
+    v.co = v.bo + (nz - 1);
+    v.bi = v.co + (nz - 1);
+    v.ci = v.bi + (nz - 1);
+    v.inner = v.ci + (nz - 1);
+    return v;
+  }
+  struct View : Sections<CQ> {
+    CQ ilo, ili, icap;
     double rbound;
   };
   __device__ static __forceinline__ View view(CQ q) {
     View v;
-    v.nz = (int)q[0];
-    v.z = q + 1;
-    v.rmin = v.z + v.nz;
-    v.rmax = v.rmin + v.nz;
-    v.bo = v.rmax + v.nz;
-    v.co = v.bo + (v.nz - 1);
-    v.bi = v.co + (v.nz - 1);
-    v.ci = v.bi + (v.nz - 1);
-    v.inner = v.ci + (v.nz - 1);
+    static_cast<Sections<CQ>&>(v) = sections<CQ>((int)q[0], q + 1);
     v.ilo = v.inner + (v.nz - 1);
     v.ili = v.ilo + (v.nz - 1);
     v.icap = v.ili + (v.nz - 1);
@@ -698,14 +711,16 @@ struct Pcon {
     return v;
   }
   // largest j with z_j <= z, clamped to [0, nz-2]
-  __device__ static __forceinline__ int section(const View& v, double z) {
+  template <class V>
+  __device__ static __forceinline__ int section(const V& v, double z) {
     int j = 0;
     for (int k = 1; k + 1 < v.nz; ++k)
       if (v.z[k] <= z) j = k;
     return j;
   }
-  __device__ static __forceinline__ double sgn(CQ q, V3 p) {
-    View v = view(q);
+  __device__ static __forceinline__ double sgn(CQ q, V3 p) { return sgn_of(view(q), p); }
+  template <class V>
+  __device__ static __forceinline__ double sgn_of(const V& v, V3 p) {
     int j = section(v, p.z);
     double r = sqrt(p.x * p.x + p.y * p.y);
     double zl = p.z - v.z[j];
@@ -756,10 +771,13 @@ struct Pcon {
   // stopping at the first section that starts beyond t1.  CNT: *nsec counts
   // the sections whose cone intersections are computed (the work measurement
   // of the profiling kernel; never in production).
-  template <bool CNT = false>
-  __device__ static double walk(CQ q, V3 p, V3 d, bool want_in, int* nsec = nullptr, double t0 = 0.0,
-                                double t1 = GV_INF) {
-    View v = view(q);
+  // A section whose slab the ray crosses outside its larger radius (the
+  // smallest r^2 over the slab, beyond a margin far above the rounding of the
+  // cone's discriminant) has no piece and is passed without solving its cone;
+  // one without an inner cone has its interval as its only piece.
+  template <bool CNT = false, class V>
+  __device__ static __forceinline__ double walk(const V& v, V3 p, V3 d, bool want_in, int* nsec = nullptr,
+                                                double t0 = 0.0, double t1 = GV_INF) {
     int j0 = section(v, t0 > 0.0 ? p.z + t0 * d.z : p.z), j1, step;
     if (d.z > 0.0) {
       j1 = v.nz - 2;
@@ -775,20 +793,36 @@ struct Pcon {
       step = 1;
       if (j0 > 0 && p.z == v.z[j0]) j0 = j0 - 1;
     }
+    const double rho2 = p.x * p.x + p.y * p.y;
+    const double A = d.x * d.x + d.y * d.y, B = p.x * d.x + p.y * d.y;
+    const double tc = A > 0.0 ? -div_fast(B, A) : 0.0;  // nearest the axis
+    // no section is passed where the squares of the cone's solution overflow
+    const double slack = A < 1e150 && rho2 < 1e150 ? fma(1e-12, rho2, 1e-6) : GV_INF;
     double cl = GV_INF, ch = -GV_INF;  // current merged piece
     bool have = false;
     for (int j = j0;; j += step) {
-      Iv S = zrange(p.z, d.z, v.z[j], v.z[j + 1]);
+      const double zlo = v.z[j], zhi = v.z[j + 1];
+      Iv S = zrange(p.z, d.z, zlo, zhi);
       if (S.lo > t1) break;  // beyond the part of the ray that can hold pieces
       if (have && S.lo > ch) {  // no piece of this or a later section joins the current one
         if (!want_in) return cl <= kTol ? fmax(ch, 0.0) : 0.0;
         if (ch - cl >= kTol) return cl;
       }
+      const double ro = v.rmax[j], rm = fmax(ro, v.rmax[j + 1]);
+      const double tm = fmin(fmax(tc, fmax(S.lo, 0.0)), S.hi);
+      if (fma(tm, fma(tm, A, 2.0 * B), rho2) > fma(rm * rm, 1.0 + 1e-6, slack)) {
+        if (j == j1) break;
+        continue;
+      }
       if (CNT) ++*nsec;
-      Iv A = cone_interior(v.rmax[j], v.bo[j], v.z[j], S, p, d);
-      Iv X = v.inner[j] != 0.0 ? cone_interior(v.rmin[j], v.bi[j], v.z[j], S, p, d) : iv_none();
+      Iv C = cone_interior(ro, v.bo[j], zlo, S, p, d);
       Pieces P;
-      pieces_of(A, X, iv_none(), P);
+      if (v.inner[j] != 0.0) {
+        pieces_of(C, cone_interior(v.rmin[j], v.bi[j], zlo, S, p, d), iv_none(), P);
+      } else {
+        P.p0 = P.p1 = iv_none();
+        P.p2 = clip0(C);
+      }
       Iv pk[3] = {P.p0, P.p1, P.p2};
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -826,11 +860,11 @@ struct Pcon {
     if (sgn(q, p) < -kHalf) return -1.0;
     const Iv B = bound_iv(view(q), p, d);
     if (misses(B)) return GV_INF;
-    return walk(q, p, d, true, nullptr, fmax(B.lo, 0.0), B.hi);
+    return walk(view(q), p, d, true, nullptr, fmax(B.lo, 0.0), B.hi);
   }
   __device__ static double dist_out(CQ q, V3 p, V3 d) {
     if (sgn(q, p) > kHalf) return -1.0;
-    return walk(q, p, d, false);
+    return walk(view(q), p, d, false);
   }
 };
 
