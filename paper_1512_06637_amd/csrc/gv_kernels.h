@@ -63,12 +63,30 @@ __global__ void k_distance(CQ q, int64_t n, const double* __restrict__ x,
   }
 }
 
+// DistanceToIn and DistanceToOut of a point on either side from one evaluation
+// of the ray's pieces (the side tests of dist_in and dist_out are the caller's).
+template <class S>
+__device__ __forceinline__ void both_distances(CQ q, V3 p, V3 d, double& in, double& out) {
+  if constexpr (S::kType == kTrd) {
+    double lo, hi;
+    const bool hit = S::interval(q, p, d, lo, hi);
+    in = hit ? S::entry_at(lo, hi) : GV_INF;
+    out = hit ? S::exit_at(lo, hi) : 0.0;
+  } else {
+    Pieces P;
+    S::pieces(q, p, d, P);
+    in = first_entry(P);
+    out = exit_of(P);
+  }
+}
+
 // All four answers with one read of the basket.  Only the distance that is
 // defined on the point's side is computed; the other is the -1 sentinel.  Solids
 // that answer both from the same pieces of the ray have them computed once: in
 // the two branches nearly every wavefront computed them twice, with 26 of 64
 // lanes active (2^20 tracks: a hollow 270-degree tube 25.4 to 17.5 us with 15.5
-// of traffic, a cone 26 to 18, a spherical shell 17.8 to 14.7).
+// of traffic, a cone 26 to 18, a spherical shell 17.8 to 14.7, a Trd 18.6 to 15.1;
+// a full tube 22 in its closed form, which has two branches, and 16 this way).
 template <class S>
 __global__ void k_solid_all(CQ q, int64_t n, const double* __restrict__ x,
                             const double* __restrict__ y, const double* __restrict__ z, const double* __restrict__ dx,
@@ -79,22 +97,15 @@ __global__ void k_solid_all(CQ q, int64_t n, const double* __restrict__ x,
     int c = code_of(S::sgn(q, p));
     if (o_in) o_in[i] = (int8_t)c;
     if (o_saf) o_saf[i] = safety_value<S>(q, p, 0, c);
-    if constexpr (S::kType == kTubs || S::kType == kCons || S::kType == kSphere) {
-      if (S::kType != kTubs || (int)q[L::TB_PHI]) {
-        double in = -1.0, out = -1.0;
-        if ((o_din && c != kInside) || (o_dout && c != kOutside)) {
-          Pieces P;
-          S::pieces(q, p, d, P);
-          if (c != kInside) in = first_entry(P);
-          if (c != kOutside) out = exit_of(P);
-        }
-        if (o_din) o_din[i] = in;
-        if (o_dout) o_dout[i] = out;
-        continue;
-      }
+    if constexpr (S::kType == kTubs || S::kType == kCons || S::kType == kSphere || S::kType == kTrd) {
+      double in = 0.0, out = 0.0;
+      if ((o_din && c != kInside) || (o_dout && c != kOutside)) both_distances<S>(q, p, d, in, out);
+      if (o_din) o_din[i] = c == kInside ? -1.0 : in;
+      if (o_dout) o_dout[i] = c == kOutside ? -1.0 : out;
+    } else {
+      if (o_din) o_din[i] = c == kInside ? -1.0 : S::dist_in(q, p, d);
+      if (o_dout) o_dout[i] = c == kOutside ? -1.0 : S::dist_out(q, p, d);
     }
-    if (o_din) o_din[i] = c == kInside ? -1.0 : S::dist_in(q, p, d);
-    if (o_dout) o_dout[i] = c == kOutside ? -1.0 : S::dist_out(q, p, d);
   }
 }
 

@@ -447,12 +447,13 @@ struct Tubs {
   // written out for one allowed interval [lo, hi] and at most one excluded one
   // X, value for value.  A ray moving away from the axis (B >= 0) from within
   // the outer cylinder needs one root of each cylinder: with q = -(B + sqrt D)
-  // < 0 the smaller roots are < 0 and clipped, and the larger is C / q.  The square root of the radius is taken only for points within
-  // the band of a cylinder or beyond it: C <= rmax kHalf / 2 puts r at most
-  // kHalf / 4 above rmax, C >= -rmin kHalf / 2 at most as far below rmin
-  // (rounding included while rmax < 1e5 mm).  A tube's exit took 300 of a layer
-  // step's VALU instructions through the interval algebra; the detector
-  // transport of 2^20 tracks went from 1.84 to 1.66 ms.
+  // < 0 the smaller roots are < 0 and clipped, and the larger is C / q.  The
+  // square root of the radius is taken only for points within the band of a
+  // cylinder or beyond it: C <= rmax kHalf / 2 puts r at most kHalf / 4 above
+  // rmax, C >= -rmin kHalf / 2 at most as far below rmin (rounding included
+  // while rmax < 1e5 mm).  A tube's exit took 300 of a layer step's VALU
+  // instructions through the interval algebra; the detector transport of 2^20
+  // tracks went from 1.84 to 1.66 ms.
   template <bool IN>
   __device__ static __forceinline__ double full_dist(CQ q, V3 p, V3 d) {
 #pragma clang fp contract(off)
@@ -657,18 +658,20 @@ struct Trd {
     }
     return true;
   }
+  __device__ static __forceinline__ double entry_at(double lo, double hi) {
+    lo = fmax(lo, 0.0);
+    return (hi - lo >= kTol) ? lo : GV_INF;
+  }
+  __device__ static __forceinline__ double exit_at(double lo, double hi) { return (lo <= kTol) ? fmax(hi, 0.0) : 0.0; }
   __device__ static __forceinline__ double dist_in(CQ q, V3 p, V3 d) {
     if (sgn(q, p) < -kHalf) return -1.0;
     double lo, hi;
-    if (!interval(q, p, d, lo, hi)) return GV_INF;
-    lo = fmax(lo, 0.0);
-    return (hi - lo >= kTol) ? lo : GV_INF;
+    return interval(q, p, d, lo, hi) ? entry_at(lo, hi) : GV_INF;
   }
   __device__ static __forceinline__ double dist_out(CQ q, V3 p, V3 d) {
     if (sgn(q, p) > kHalf) return -1.0;
     double lo, hi;
-    if (!interval(q, p, d, lo, hi)) return 0.0;
-    return (lo <= kTol) ? fmax(hi, 0.0) : 0.0;
+    return interval(q, p, d, lo, hi) ? exit_at(lo, hi) : 0.0;
   }
 };
 

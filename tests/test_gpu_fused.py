@@ -1,5 +1,5 @@
 """The fused query where one evaluation of the ray's pieces answers both
-distances (tube segments with phi faces, cones, spherical shells) against the
+distances (tubes, cones, spherical shells, Trds) against the
 oracle, for every choice of outputs, at the edges of a wavefront.
 
 Bar: 1e-12 max(|ref|, 1 mm), sentinels exact, on tracks the oracle does not
@@ -21,6 +21,7 @@ SOLIDS = {
     "cone 5 rad": W.cons(0.0, 8.0, 0.0, 12.0, 25.0, 1.0, 5.0),
     "shell": W.sphere(10.0, 30.0),
     "ball": W.sphere(0.0, 30.0),
+    "trd": W.trd(10.0, 20.0, 15.0, 25.0, 30.0),
 }
 
 
