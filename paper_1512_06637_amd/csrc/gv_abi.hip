@@ -1531,12 +1531,13 @@ int lane_transport(gv_geom* g, const LaneCtl& L, int64_t n, const double* x, con
     GV_TRY(launched(fn));
   }
   // defaults: staged outputs; 4 waves per SIMD for navigation, 3 for
-  // physics-limited steps (more live state per lane: 9.6 ms at 3 against
-  // 11.5 ms at 4 on the detector workload)
+  // physics-limited steps (more live state per lane: 400,003 detector tracks
+  // 2.04 ms at 3 against 3.44 at 4; navigation of 2^20 tracks 1.31 ms at 4
+  // against 1.50 at 3)
   const int waves = g->tune.lane_waves ? g->tune.lane_waves : (phys ? 3 : 4);
   const bool stage = g->tune.lane_stage ? g->tune.lane_stage == 2 : true;
-  // per-class scheduling by default (2.66 against 2.99 ms for navigation,
-  // 7.6 against 9.5 ms physics-limited, on the detector workload)
+  // per-class scheduling by default (2^20 detector tracks 1.31 against 2.21 ms
+  // for navigation, 400,003 physics-limited 2.04 against 2.48 ms)
   const LaneKernel k = lane_kernel(g->kind, fp32, phys, waves, stage, g->tune.lane_sched != 1);
   int64_t grid = g->tune.lane_grid > 0 ? g->tune.lane_grid
                                        : (int64_t)resident_blocks(g, reinterpret_cast<const void*>(k)) * g->n_cu;

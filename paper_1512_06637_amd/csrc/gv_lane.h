@@ -92,8 +92,8 @@ struct LaneCtl {
 // volume, then by what their first step will evaluate, then by direction, and
 // in each iteration the lanes of one volume step together (8 % of lanes active
 // per VALU instruction without the bins, 23 % with them; 500,009 tracks: 990
-// and 617 us; basket form 1,867 us, most of it 128 step launches for tracks
-// that take 1.7 steps).  The kernel waits on dependent instructions most of
+// and 617 us when the bins came; basket form 1,867 us, most of it 128 step
+// launches for tracks that take 1.7 steps).  The kernel waits on dependent instructions most of
 // its time at any register budget; 2 waves per SIMD (252 VGPRs) spill least:
 // 617 us against 763 at 3 and 920 at 4.
 //
@@ -125,7 +125,8 @@ __device__ __forceinline__ uint32_t start_bin(const DevGeom& G, int pv, V3 p, V3
 // Before a transport: zeroes the key counts and the work counter, and locates
 // the tracks whose start volume the caller does not give.  With the
 // point lookup inside the transport kernel instead, its code took registers
-// from the step loop (1.89 against 1.85 ms per 2^20-track detector transport);
+// from the step loop (1.89 against 1.85 ms per 2^20-track detector transport,
+// measured before the tubes' closed form);
 // here it runs at full occupancy.  bins: also each track's start bin, into its
 // key.
 template <int K>

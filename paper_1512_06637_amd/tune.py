@@ -31,7 +31,7 @@ CACHE = os.path.join(HERE, "tuned.json")
 
 # candidate values per knob (0 / -1 = the library default)
 LANE_FORM_SPACE = {
-    "transport": [0],  # the default form: lane, basket for geometries holding composites
+    "transport": [0],  # the default form: lane
     "sort_bits": [-1, 0, 5, 6],
     "sort_key": [0, 2],
     "lane_waves": [0, 3],  # 0: 4 waves per SIMD for navigation, 3 for physics-limited steps (the field serves both)
