@@ -429,15 +429,19 @@ struct Tubs {
     phi_intervals(q, L::TB_NS, L::TB_NE, (int)q[L::TB_PHI], p, d, allow, excl);
     pieces_of(iv_and(A, allow), X1, excl, P);
   }
+  // FULL: full tubes in closed form (composites' parts go without: both forms
+  // side by side spill there)
+  template <bool FULL = true>
   __device__ static __forceinline__ double dist_in(CQ q, V3 p, V3 d) {
-    if ((int)q[L::TB_PHI] == 0) return full_dist<true>(q, p, d);
+    if (FULL && (int)q[L::TB_PHI] == 0) return full_dist<true>(q, p, d);
     if (sgn(q, p) < -kHalf) return -1.0;
     Pieces P;
     pieces(q, p, d, P);
     return first_entry(P);
   }
+  template <bool FULL = true>
   __device__ static __forceinline__ double dist_out(CQ q, V3 p, V3 d) {
-    if ((int)q[L::TB_PHI] == 0) return full_dist<false>(q, p, d);
+    if (FULL && (int)q[L::TB_PHI] == 0) return full_dist<false>(q, p, d);
     if (sgn(q, p) > kHalf) return -1.0;
     Pieces P;
     pieces(q, p, d, P);
@@ -774,11 +778,14 @@ struct Pcon {
   // stopping at the first section that starts beyond t1.  CNT: *nsec counts
   // the sections whose cone intersections are computed (the work measurement
   // of the profiling kernel; never in production).
-  // A section whose slab the ray crosses outside its larger radius (the
+  // PASS: a section whose slab the ray crosses outside its larger radius (the
   // smallest r^2 over the slab, beyond a margin far above the rounding of the
   // cone's discriminant) has no piece and is passed without solving its cone;
-  // one without an inner cone has its interval as its only piece.
-  template <bool CNT = false, class V>
+  // one without an inner cone has its interval as its only piece.  The values
+  // are the same; the test's state costs kernels that hold other solids beside
+  // the polycone more in spills than it saves (fused query of two united boxes,
+  // 2^20 tracks: 89 us with it, 49 without).
+  template <bool CNT = false, bool PASS = true, class V>
   __device__ static __forceinline__ double walk(const V& v, V3 p, V3 d, bool want_in, int* nsec = nullptr,
                                                 double t0 = 0.0, double t1 = GV_INF) {
     int j0 = section(v, t0 > 0.0 ? p.z + t0 * d.z : p.z), j1, step;
@@ -813,18 +820,19 @@ struct Pcon {
       }
       const double ro = v.rmax[j], rm = fmax(ro, v.rmax[j + 1]);
       const double tm = fmin(fmax(tc, fmax(S.lo, 0.0)), S.hi);
-      if (fma(tm, fma(tm, A, 2.0 * B), rho2) > fma(rm * rm, 1.0 + 1e-6, slack)) {
+      if (PASS && fma(tm, fma(tm, A, 2.0 * B), rho2) > fma(rm * rm, 1.0 + 1e-6, slack)) {
         if (j == j1) break;
         continue;
       }
       if (CNT) ++*nsec;
       Iv C = cone_interior(ro, v.bo[j], zlo, S, p, d);
       Pieces P;
-      if (v.inner[j] != 0.0) {
-        pieces_of(C, cone_interior(v.rmin[j], v.bi[j], zlo, S, p, d), iv_none(), P);
-      } else {
+      if (PASS && v.inner[j] == 0.0) {
         P.p0 = P.p1 = iv_none();
         P.p2 = clip0(C);
+      } else {
+        const Iv X = v.inner[j] != 0.0 ? cone_interior(v.rmin[j], v.bi[j], zlo, S, p, d) : iv_none();
+        pieces_of(C, X, iv_none(), P);
       }
       Iv pk[3] = {P.p0, P.p1, P.p2};
 #pragma unroll
@@ -859,15 +867,17 @@ struct Pcon {
     return iv_and(cyl_interior(rb * rb, p, d), zrange(p.z, d.z, v.z[0] - 1e-6, v.z[v.nz - 1] + 1e-6));
   }
   __device__ static __forceinline__ bool misses(Iv B) { return !(B.hi >= fmax(B.lo, 0.0)); }
-  __device__ static double dist_in(CQ q, V3 p, V3 d) {
+  template <bool PASS = true>
+  __device__ static __forceinline__ double dist_in(CQ q, V3 p, V3 d) {
     if (sgn(q, p) < -kHalf) return -1.0;
     const Iv B = bound_iv(view(q), p, d);
     if (misses(B)) return GV_INF;
-    return walk(view(q), p, d, true, nullptr, fmax(B.lo, 0.0), B.hi);
+    return walk<false, PASS>(view(q), p, d, true, nullptr, fmax(B.lo, 0.0), B.hi);
   }
-  __device__ static double dist_out(CQ q, V3 p, V3 d) {
+  template <bool PASS = true>
+  __device__ static __forceinline__ double dist_out(CQ q, V3 p, V3 d) {
     if (sgn(q, p) > kHalf) return -1.0;
-    return walk(view(q), p, d, false);
+    return walk<false, PASS>(view(q), p, d, false);
   }
 };
 
@@ -883,24 +893,26 @@ __device__ __forceinline__ double prim_sgn(int type, CQ q, V3 p) {
     default: return Pcon::sgn(q, p);
   }
 }
+template <bool FULL = true>
 __device__ __forceinline__ double prim_dist_in(int type, CQ q, V3 p, V3 d) {
   switch (type) {
     case kBox: return Box::dist_in(q, p, d);
-    case kTubs: return Tubs::dist_in(q, p, d);
+    case kTubs: return Tubs::dist_in<FULL>(q, p, d);
     case kCons: return Cons::dist_in(q, p, d);
     case kSphere: return Sphere::dist_in(q, p, d);
     case kTrd: return Trd::dist_in(q, p, d);
-    default: return Pcon::dist_in(q, p, d);
+    default: return Pcon::dist_in<false>(q, p, d);
   }
 }
+template <bool FULL = true>
 __device__ __forceinline__ double prim_dist_out(int type, CQ q, V3 p, V3 d) {
   switch (type) {
     case kBox: return Box::dist_out(q, p, d);
-    case kTubs: return Tubs::dist_out(q, p, d);
+    case kTubs: return Tubs::dist_out<FULL>(q, p, d);
     case kCons: return Cons::dist_out(q, p, d);
     case kSphere: return Sphere::dist_out(q, p, d);
     case kTrd: return Trd::dist_out(q, p, d);
-    default: return Pcon::dist_out(q, p, d);
+    default: return Pcon::dist_out<false>(q, p, d);
   }
 }
 __device__ __forceinline__ double prim_safety_in(int type, CQ q, V3 p) {
@@ -957,7 +969,7 @@ struct Bool {
   }
   // entry of a part: 0 when the point is inside it or enters it at once
   __device__ static __forceinline__ double entry(int type, CQ q, V3 p, V3 d) {
-    return fmax(prim_dist_in(type, q, p, d), 0.0);
+    return fmax(prim_dist_in<false>(type, q, p, d), 0.0);
   }
   // t + s for t >= 0, s > 0, but at least the next double above t: a part's
   // distance below the resolution of t (a point within rounding of a
@@ -1025,18 +1037,18 @@ struct Bool {
           t = ahead(t, fmax(ea, ec));
           continue;
         }
-        run = fmin(prim_dist_out(A, a, x, d), prim_dist_out(C, c, xc, dc));
+        run = fmin(prim_dist_out<false>(A, a, x, d), prim_dist_out<false>(C, c, xc, dc));
       } else {
         if (ea > 0.0) {
           t = ahead(t, ea);
           continue;
         }
-        const double xcv = prim_dist_out(C, c, xc, dc);
+        const double xcv = prim_dist_out<false>(C, c, xc, dc);
         if (xcv > 0.0) {  // inside C: skip to its exit
           t = ahead(t, xcv);
           continue;
         }
-        run = fmin(prim_dist_out(A, a, x, d), entry(C, c, xc, dc));
+        run = fmin(prim_dist_out<false>(A, a, x, d), entry(C, c, xc, dc));
       }
       if (run >= kTol) return t;
       t = ahead(t, run);
@@ -1049,12 +1061,12 @@ struct Bool {
     const int A = ta(q), C = tc(q), o = op(q);
     CQ a = qa(q), c = qc(q);
     const V3 pc = to_c(q, p), dc = rt(q, d);
-    if (o == kIntersection) return fmax(fmin(prim_dist_out(A, a, p, d), prim_dist_out(C, c, pc, dc)), 0.0);
-    if (o == kSubtraction) return fmax(fmin(prim_dist_out(A, a, p, d), entry(C, c, pc, dc)), 0.0);
+    if (o == kIntersection) return fmax(fmin(prim_dist_out<false>(A, a, p, d), prim_dist_out<false>(C, c, pc, dc)), 0.0);
+    if (o == kSubtraction) return fmax(fmin(prim_dist_out<false>(A, a, p, d), entry(C, c, pc, dc)), 0.0);
     double t = 0.0;
     for (int it = 0; it < kMaxIter; ++it) {
       const V3 x = at(p, d, t), xc = at(pc, dc, t);
-      const double m = fmax(prim_dist_out(A, a, x, d), prim_dist_out(C, c, xc, dc));
+      const double m = fmax(prim_dist_out<false>(A, a, x, d), prim_dist_out<false>(C, c, xc, dc));
       if (m > 0.0) {  // still inside a part: go to the farther exit
         t = ahead(t, m);
         continue;
