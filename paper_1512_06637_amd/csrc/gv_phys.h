@@ -49,7 +49,12 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32
 
 // u in (0, 1): the first two output words as a 64-bit integer, its top 53
 // bits, centred in their 2^-53 interval.
-__device__ __forceinline__ double uniform_of(uint64_t w) { return ((double)(w >> 11) + 0.5) * 0x1p-53; }
+__host__ __device__ inline double uniform_of(uint64_t w) { return ((double)(w >> 11) + 0.5) * 0x1p-53; }
+// The same number in FP32, to one part in 2^24 from 2^-54 up: the 11 low bits go
+// and the centre of the interval comes in before the rounding.
+__host__ __device__ inline float uniform32(uint32_t hi, uint32_t lo) {
+  return fmaf((float)((lo & ~0x7FFu) | 0x400u), 0x1p-64f, (float)hi * 0x1p-32f);
+}
 __device__ __forceinline__ double length_of(uint64_t w, double rate) { return -log(uniform_of(w)) / rate; }
 
 // Shortest sampled interaction length of the processes of material `mat`
@@ -57,7 +62,7 @@ __device__ __forceinline__ double length_of(uint64_t w, double rate) { return -l
 // equal lengths); +inf and -1 when no process acts.
 // Only the winner's logarithm and division are taken in FP64.  The others are
 // ruled out in FP32: with L = -log2(u), the hardware logarithm of u rounded to
-// FP32 is off by at most 1.2e-7 L (every float in [2^-33, 1) checked) plus 1.9e-7
+// FP32 is off by at most 1.2e-7 L (every float in [2^-54, 1) checked) plus 1.9e-7
 // for the rounding of u, and the product with 1/rate by a few 6e-8 of itself,
 // inside the margins 1e-6 L + 4e-7 below.  Two processes whose intervals overlap
 // are compared by their FP64 lengths (about one step in 1e5), so the choice and
@@ -75,8 +80,7 @@ __device__ __forceinline__ double physics_length(CQ rate, int n_proc, int mat, u
     uint32_t c[4] = {track, step, (uint32_t)i, 0u};
     philox4x32_10(c, (uint32_t)seed, (uint32_t)(seed >> 32));
     const uint64_t w = ((uint64_t)c[0] << 32) | c[1];
-    const float u = fmaxf(fmaf((float)c[1], 0x1p-64f, (float)c[0] * 0x1p-32f), 0x1p-54f);
-    const float l = -__builtin_amdgcn_logf(u), e = fmaf(l, 1e-6f, 4e-7f), inv = __builtin_amdgcn_rcpf((float)r);
+    const float l = -__builtin_amdgcn_logf(uniform32(c[0], c[1])), e = fmaf(l, 1e-6f, 4e-7f), inv = __builtin_amdgcn_rcpf((float)r);
     const bool sane = r > 1e-30 && r < 1e30;
     const float lo = sane ? (l - e) * inv : 0.0f, hi = sane ? (l + e) * inv : __builtin_huge_valf();
     bool take = bp < 0 || hi < blo;
