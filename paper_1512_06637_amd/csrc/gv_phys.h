@@ -22,8 +22,13 @@ __device__ __forceinline__ uint64_t mul_wide(uint32_t a, uint32_t b) {
   asm("v_mad_u64_u32 %0, %1, %2, %3, 0" : "=v"(p), "=s"(carry) : "v"(a), "s"(b));
   return p;
 }
+// One instruction on gfx950 (the compiler makes two of it).
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+#ifdef __gfx950__
   return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+#else
+  return a ^ b ^ c;
+#endif
 }
 
 // Philox4x32 with 10 rounds.  A round multiplies words 0 and 2 by the two
