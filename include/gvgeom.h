@@ -284,8 +284,8 @@ int gv_probe_fma64(double* out, int64_t n_lanes, int32_t iters, void* stream);
  *
  * The transports have two forms.  The lane form (default) orders the tracks
  * once by a direction key (counting sort into 2^sort_bits x 2^sort_bits
- * direction cells; for geometries with composites by start volume and the
- * daughters on the track's way first, with fewer cells), then one
+ * direction cells; for geometries with composites first by start volume and the
+ * daughters on the track's way, where those are composites, with fewer cells), then one
  * persistent kernel carries each track in one lane from its start to its end,
  * wavefronts taking 64 places of the order at a time from an atomic counter.
  * The basket form (Sec. II.A baskets of tracks in the same volume) regroups
@@ -324,7 +324,8 @@ int gv_probe_fma64(double* out, int64_t n_lanes, int32_t iters, void* stream);
  *                 class (solid type and daughter access) most of the
  *                 wavefront's live lanes are in take a step, the others wait,
  *                 so lanes that fell behind catch up (default 2; geometries
- *                 with composites always 2, one logical volume at a time).
+ *                 with composites always 2, composites and the volumes that
+ *                 hold them each a class of its own).
  * A change of cell_bits re-sizes the transport workspace at the next
  * transport.  GV_EINVAL for a field out of range (nothing changed). */
 typedef struct {

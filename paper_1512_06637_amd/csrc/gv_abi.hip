@@ -83,6 +83,7 @@ struct gv_geom {
   int n_lv = 0, n_pv = 0, n_place = 0, max_depth = 0, world_lv = 0;
   bool has_bool = false;     // some LV is a composite
   int kind = kElementary;    // SolidKind: which navigation kernels run
+  int n_groups = 0;          // start groups of the transports' order (0: by direction alone)
   std::vector<int> lv_type, lv_par;
   void* dmem = nullptr;
   // nav_transport workspace (grown on demand)
@@ -684,7 +685,11 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
       else if (dt == kBox || dt == kTubs) mode = dt == kBox ? 6 : 7;
       else mode = 8;
       lv_class[i] = mode * 8 + lv_type[i];
+      bool own = lv_type[i] == kBool;
+      for (int k = lv_doff[i]; k < lv_doff[i] + lv_dcnt[i] && !own; ++k) own = lv_type[dau_lv[k]] == kBool;
+      if (own) lv_class[i] = i == world ? kOwnClass : kOwnClass + 1 + i;
     }
+    static_assert(8 * 8 + 7 < kOwnClass, "classes of composites lie above the others");
     // how point lookups reach an LV's daughters; placements that are not
     // rotations keep the loop over every daughter
     std::vector<int> lv_loc(n_lv, kLocPlain);
@@ -702,6 +707,23 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
       if (lv_rad[i] >= 0) lv_loc[i] = kLocRadial;
       else if (lv_phi[i] >= 0) lv_loc[i] = kLocPhi;
       else lv_loc[i] = kLocBox;
+    }
+    // start groups of the transports' order (geometries with composites):
+    // group 0 for volumes without composites, then the others, as far as their
+    // cells fit; one group each, or none, when they do not
+    std::vector<int> lv_key(2 * (size_t)n_lv);
+    int n_groups = 0;
+    for (int bins = 1; bins >= 0; --bins) {
+      int64_t groups = 1;
+      for (int i = 0; i < n_lv; ++i) {
+        const bool own = lv_class[i] >= kOwnClass;
+        const int m = bins && own && lv_loc[i] == kLocBox ? 1 + 2 * std::min(lv_dcnt[i], kStartBoxes) : 1;
+        lv_key[2 * i] = own ? (int)std::min<int64_t>(groups, kSortMaxCells) : 0;
+        lv_key[2 * i + 1] = m;
+        if (own) groups += m;
+      }
+      n_groups = groups > 1 && groups <= kSortMaxCells ? (int)groups : 0;
+      if (n_groups > 0) break;
     }
     // count the tree first (depth and size limits also reject cycles)
     std::vector<long> subtree(n_lv, -1);
@@ -812,6 +834,7 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
         {rad_k.data(), rad_k.size() * 4, 0},
         {phi_mask.data(), phi_mask.size() * 8, 0},
         {lv_slot.data(), lv_slot.size() * 4, 0},
+        {lv_key.data(), lv_key.size() * 4, 0},
         {nullptr, 5 * 8, 0}};
     size_t total = 0;
     for (auto& p : parts) {
@@ -867,7 +890,9 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
     D.rad_k = (CQI)(base + parts[14].off);
     D.phi_mask = (CQL)(base + parts[15].off);
     D.lv_slot = (CQI)(base + parts[16].off);
-    g->pcon_work = (unsigned long long*)(base + parts[17].off);  // zeroed by the upload
+    D.lv_key = (CQI)(base + parts[17].off);
+    g->pcon_work = (unsigned long long*)(base + parts[18].off);  // zeroed by the upload
+    g->n_groups = n_groups;
     g->n_lv = n_lv;
     g->n_pv = (int)npv;
     g->n_place = n_place;
@@ -1505,21 +1530,21 @@ int lane_transport(gv_geom* g, const LaneCtl& L, int64_t n, const double* x, con
                    int32_t* out_pv, double* out_step, int32_t* out_nsteps, uint32_t* out_flags, bool fp32,
                    bool phys, PhysArgs P, int8_t* out_proc, hipStream_t s, const char* fn, bool events) {
   // tracks of a geometry with composites start in several volumes: there the
-  // order is by start volume first, then by direction
+  // order is by start group first, then by direction
   int h = std::min(sort_bits(g), kSortMaxBits);
   const bool sorted = h > 0;
-  const int lvs = sorted && g->has_bool && g->n_lv <= kSortMaxCells / kStartBins ? g->n_lv : 0;
-  while (lvs > 0 && ((int64_t)(lvs * kStartBins) << (2 * h)) > kSortMaxCells) --h;
-  const int cells = sorted ? std::max(lvs * kStartBins, 1) << (2 * h) : 0;
-  const Shape sh = lane_shape(g, start_pv && lvs == 0 ? cells : n);
+  const int groups = sorted ? g->n_groups : 0;
+  while (((int64_t)groups << (2 * h)) > kSortMaxCells) --h;
+  const int cells = sorted ? std::max(groups, 1) << (2 * h) : 0;
+  const Shape sh = lane_shape(g, start_pv && groups == 0 ? cells : n);
   hipLaunchKernelGGL(GV_KIND(k_ls_begin, g->kind), dim3(sh.grid), dim3(sh.block), 0, s, g->dg, n, x, y,
-                     z, dx, dy, dz, start_pv, lvs > 0 ? 1 : 0, L, cells);
+                     z, dx, dy, dz, start_pv, groups, L, cells);
   GV_TRY(launched(fn));
   if (!start_pv) start_pv = L.pv0;
   if (sorted) {
     const unsigned cg = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 4095) / 4096, 256));
-    hipLaunchKernelGGL(k_ls_count, dim3(cg), dim3(1024), 4 * (size_t)cells, s, g->dg, n, dx, dy, dz, start_pv,
-                       h, g->tune.sort_key == 2 ? 1 : 0, lvs, L);
+    hipLaunchKernelGGL(k_ls_count, dim3(cg), dim3(1024), 4 * (size_t)cells, s, n, dx, dy, dz, h,
+                       g->tune.sort_key == 2 ? 1 : 0, groups, L);
     GV_TRY(launched(fn));
     hipLaunchKernelGGL(k_ls_scan, dim3(1), dim3(1024), 0, s, L, cells);
     GV_TRY(launched(fn));

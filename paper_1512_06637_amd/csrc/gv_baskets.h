@@ -464,6 +464,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
   // bucket = (LV, coarse direction cell), so each LV's entries are contiguous
   // and ordered by direction cell; tiles cover whole LV ranges (a tile may
   // span two neighbouring cells) so that cells add no partial tiles.
+  constexpr int S = K == kComposites ? kOneComposite : K;
   extern __shared__ int lds[];
   __shared__ unsigned long long wsum[WK ? kWorkN : 1];
   if (*len_cur == 0) return;  // nothing left to transport: the whole grid leaves
@@ -514,10 +515,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
       double st;
       bool exited = false;
       if (PHYS) {
-        st = step_physics<F32, K>(G, b, r.pv, p, d, (uint32_t)id, k, P, r.safe, &nx, &proc, &fl, w,
+        st = step_physics<F32, S>(G, b, r.pv, p, d, (uint32_t)id, k, P, r.safe, &nx, &proc, &fl, w,
                                   zfc_left(r.zfc), &exited);
       } else {
-        st = step_culled<F32, K>(G, b, r.pv, p, d, &nx, &fl, w, zfc_left(r.zfc), &exited);
+        st = step_culled<F32, S>(G, b, r.pv, p, d, &nx, &fl, w, zfc_left(r.zfc), &exited);
         p = advance(p, st, d);
       }
       // leaving pv into its mother: pv's placement index goes along (see the lane form)

@@ -33,10 +33,12 @@ struct PvRec {
 // doubles: R row-major then t, with x_mother = R x_child + t.
 constexpr int kPhiSectors = 256, kPhiLevels = 8;
 constexpr int kLvSlots = 1024;  // slots of the LVs in the regrouped kernels
+constexpr int kOwnClass = 128;  // an LV that is a composite or holds one has a step class of its own from here on (the world this one)
 
 struct DevGeom {
   int n_lv, n_pv, n_place;
   CQI lv_slot;       // [n_lv] place of each LV in order of step class, then number (scaled into kLvSlots)
+  CQI lv_key;        // [n_lv][2] first start group of each LV's tracks (ordering of transports), and the number of groups
   CQ4 lv_rec;        // [n_lv][2] records of LvRec, one 32-byte load
   CQ par;            // derived solid parameters
   CQ dau_xf;         // [n_place][12] placement transform, LV frame

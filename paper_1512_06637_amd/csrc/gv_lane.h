@@ -86,24 +86,29 @@ struct LaneCtl {
   uint32_t* queue;  // [1] next place to hand out
 };
 
-// Geometries with composites: tracks start in several volumes, and a step
-// there costs what the few daughters on its way cost (a polycone minus a cone
-// takes 20 us of a wavefront's time).  So the tracks are ordered by start
-// volume, then by what their first step will evaluate, then by direction, and
-// in each iteration the lanes of one volume step together (8 % of lanes active
-// per VALU instruction without the bins, 23 % with them; 500,009 tracks: 990
-// and 617 us when the bins came; basket form 1,867 us, most of it 128 step
-// launches for tracks that take 1.7 steps).  The kernel waits on dependent instructions most of
-// its time at any register budget; 2 waves per SIMD (252 VGPRs) spill least:
-// 617 us against 763 at 3 and 920 at 4.
+// Geometries with composites: tracks start in several volumes, and a step in
+// one that is a composite or holds one costs what the few daughters on its way
+// cost (a polycone minus a cone takes 20 us of a wavefront's time).  So the
+// tracks are ordered by start volume, then by what their first step will
+// evaluate, then by direction, and in each iteration the lanes of one such
+// volume step together (8 % of lanes active per VALU instruction without the
+// bins, 23 % with them; 500,009 tracks: 990 and 617 us when the bins came;
+// basket form 1,867 us, most of it 128 step launches for tracks that take 1.7
+// steps).  The volumes that neither are nor hold composites share one start
+// group and the step classes of other geometries: with a class and a group for
+// each, a detector holding one composite kept 2 x 2 direction cells and stepped
+// one layer at a time.
 //
-// Start bin of a track in an LV whose daughters are found by their boxes: 0 no
-// daughter box on its way, else which daughter's box it enters first and
-// whether it enters more than one.
-constexpr int kStartBins = 32;
-__device__ __forceinline__ uint32_t start_bin(const DevGeom& G, int pv, V3 p, V3 d) {
-  const LvRec v = lv_rec(G, pv_rec(G, pv).lv);
-  if (v.loc != kLocBox) return 0;
+// Start group of a track: its LV's first, and in an LV that has several (its
+// daughters are found by their boxes) one more than twice the daughter whose box
+// it enters first, and whether it enters more than one (0: no daughter box on
+// its way).
+constexpr int kStartBoxes = 15;  // daughters that have groups of their own
+__device__ __forceinline__ uint32_t start_group(const DevGeom& G, int pv, V3 p, V3 d) {
+  const int lv = pv_rec(G, pv).lv;
+  const uint32_t g0 = (uint32_t)G.lv_key[2 * lv];
+  if (G.lv_key[2 * lv + 1] == 1) return g0;
+  const LvRec v = lv_rec(G, lv);
   CQ X = G.pv_gxf + 12 * (size_t)pv;
   const V3 pl = to_child_p(X, p), dl = to_child_d(X, d);
   const V3 inv{inv_dir64(dl.x), inv_dir64(dl.y), inv_dir64(dl.z)};
@@ -119,7 +124,7 @@ __device__ __forceinline__ uint32_t start_bin(const DevGeom& G, int pv, V3 p, V3
       bk = k;
     }
   }
-  return bk < 0 ? 0 : 1 + 2 * (bk % 15) + (hits > 1 ? 1 : 0);
+  return g0 + (bk < 0 ? 0 : 1 + 2 * (bk % kStartBoxes) + (hits > 1 ? 1 : 0));
 }
 
 // Before a transport: zeroes the key counts and the work counter, and locates
@@ -127,42 +132,37 @@ __device__ __forceinline__ uint32_t start_bin(const DevGeom& G, int pv, V3 p, V3
 // point lookup inside the transport kernel instead, its code took registers
 // from the step loop (1.89 against 1.85 ms per 2^20-track detector transport,
 // measured before the tubes' closed form);
-// here it runs at full occupancy.  bins: also each track's start bin, into its
-// key.
+// here it runs at full occupancy.  groups: also each track's start group, into
+// its key.
 template <int K>
 __global__ void k_ls_begin(DevGeom G, int64_t n, const double* __restrict__ x, const double* __restrict__ y,
                            const double* __restrict__ z, const double* __restrict__ dx,
                            const double* __restrict__ dy, const double* __restrict__ dz,
-                           const int32_t* __restrict__ start_pv, int bins, LaneCtl L, int cells) {
+                           const int32_t* __restrict__ start_pv, int groups, LaneCtl L, int cells) {
   for (int64_t i = gtid(); i < cells; i += gstride()) L.cnt[i] = 0u;
   if (gtid() == 0) *L.queue = 0u;
-  if (start_pv && !bins) return;
+  if (start_pv && !groups) return;
   for (int64_t i = gtid(); i < n; i += gstride()) {
     const V3 p = ld3(x, y, z, i);
     const int pv = start_pv ? start_pv[i] : locate<K>(G, p);
     if (!start_pv) L.pv0[i] = pv;
-    if (bins) L.key[i] = pv >= 0 && pv < G.n_pv ? start_bin(G, pv, p, ld3(dx, dy, dz, i)) : 0u;
+    if (groups) L.key[i] = pv >= 0 && pv < G.n_pv ? start_group(G, pv, p, ld3(dx, dy, dz, i)) : 0u;
   }
 }
 
-// Key of every track (z-axis or octahedral cell; when lvs > 0, for tracks that
-// start in several volumes, below the logical volume it starts in and its start
-// bin, which its key holds on entry) and the per-key counts
+// Key of every track (z-axis or octahedral cell; when groups > 0, below its
+// start group, which its key holds on entry) and the per-key counts
 // (workgroup histogram in LDS, 4 cells bytes of dynamic LDS, one global
 // atomic per workgroup and key).
-static __global__ void k_ls_count(DevGeom G, int64_t n, const double* __restrict__ dx, const double* __restrict__ dy,
-                                  const double* __restrict__ dz, const int32_t* __restrict__ start_pv, int h,
-                                  int zaxis, int lvs, LaneCtl L) {
+static __global__ void k_ls_count(int64_t n, const double* __restrict__ dx, const double* __restrict__ dy,
+                                  const double* __restrict__ dz, int h, int zaxis, int groups, LaneCtl L) {
   extern __shared__ uint32_t key_hist[];
-  const int cells = max(lvs * kStartBins, 1) << (2 * h);
+  const int cells = max(groups, 1) << (2 * h);
   for (int c = threadIdx.x; c < cells; c += blockDim.x) key_hist[c] = 0u;
   __syncthreads();
   for (int64_t i = gtid(); i < n; i += gstride()) {
     uint32_t k = zaxis ? direction_key_zaxis(dx[i], dy[i], dz[i], h) : direction_key(dx[i], dy[i], dz[i], h);
-    if (lvs > 0) {
-      const int pv = start_pv[i];
-      if (pv >= 0 && pv < G.n_pv) k |= ((uint32_t)pv_rec(G, pv).lv * kStartBins + L.key[i]) << (2 * h);
-    }
+    if (groups > 0) k |= L.key[i] << (2 * h);
     L.key[i] = k;
     atomicAdd(&key_hist[k], 1u);
   }
@@ -451,15 +451,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
       if (live) {  // volume and class in one load
         const PvRec v = pv_rec(G, T.pv);
         lv = v.lv;
-        cl = K == kComposites ? lv : v.cls;  // composites: each volume is a class of its own
+        cl = v.cls;
       }
       // the class most live lanes are in (few classes are present at once;
-      // on equal counts the first found)
+      // on equal counts the first found).  Lanes in a composite below the
+      // world, or in a volume that holds one, come first: they take the few
+      // steps more that it costs and stay near the others; left for last, each
+      // went the rest of its way alone (262,144 tracks of the detector with a
+      // composite in one kind of module 0.85 and 0.65 ms, 4,099 606 and 305 us;
+      // the world as well where it holds the composite: 1.30 and 2.39 ms).
       int best = -1, nbest = 0;
       for (uint64_t rest = lm; rest;) {
         const int c = __builtin_amdgcn_readlane(cl, __ffsll((unsigned long long)rest) - 1);
         const uint64_t m = __ballot(cl == c);
-        const int nm = __popcll(m);
+        const int nm = __popcll(m) + (K == kComposites && c > kOwnClass ? 64 : 0);
         if (nm > nbest) {
           nbest = nm;
           best = c;
@@ -475,18 +480,18 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
       const bool mine = live && cl == best;
       const int lead = __ffsll((unsigned long long)__ballot(mine)) - 1;
       const int lv0 = __builtin_amdgcn_readlane(lv, lead);
-      if (K == kComposites) {  // one volume at a time
-        if (mine) lane_compute<F32, PHYS, K>(G, T, lv0, T.pv, P, R);
-      } else {
-        const bool uni_lv = __ballot(mine && lv != lv0) == 0;
-        const int pv0 = __builtin_amdgcn_readlane(T.pv, lead);
-        if (!PHYS && uni_lv && __ballot(mine && T.pv != pv0) == 0) {
-          if (mine) lane_compute<F32, PHYS, K>(G, T, lv0, pv0, P, R);
-        } else if (uni_lv) {
-          if (mine) lane_compute<F32, PHYS, K>(G, T, lv0, T.pv, P, R);
-        } else if (mine) {
-          lane_compute<F32, PHYS, K>(G, T, lv, T.pv, P, R);
-        }
+      // (A composite, or a volume that holds one, is a class of its own.)
+      constexpr int E = K == kComposites ? kElementary : K;
+      const bool uni_lv = __ballot(mine && lv != lv0) == 0;
+      const int pv0 = __builtin_amdgcn_readlane(T.pv, lead);
+      if (K == kComposites && best >= kOwnClass) {
+        if (mine) lane_compute<F32, PHYS, kOneComposite>(G, T, lv0, T.pv, P, R);
+      } else if (!PHYS && K != kComposites && uni_lv && __ballot(mine && T.pv != pv0) == 0) {
+        if (mine) lane_compute<F32, PHYS, E>(G, T, lv0, pv0, P, R);
+      } else if (uni_lv) {
+        if (mine) lane_compute<F32, PHYS, E>(G, T, lv0, T.pv, P, R);
+      } else if (mine) {
+        lane_compute<F32, PHYS, E>(G, T, lv, T.pv, P, R);
       }
       if (mine)
         live = !lane_record<PHYS, ST>(a, T, R, S);

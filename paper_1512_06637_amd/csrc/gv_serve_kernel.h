@@ -30,7 +30,7 @@ __host__ __device__ inline int64_t serve_out_bytes(int kind, int64_t n) {
 // basket, so the query kind and precision are wavefront-uniform; a basket's
 // tracks may sit in different volumes (per-lane navigation state).
 template <int K>
-__global__ void __launch_bounds__(256) k_serve(DevGeom G, const SDesc* __restrict__ desc, int nb, int64_t ntiles,
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K == kComposites ? 2 : 1))) k_serve(DevGeom G, const SDesc* __restrict__ desc, int nb, int64_t ntiles,
                                                const char* __restrict__ din, char* __restrict__ dout) {
   __shared__ int64_t t0[kServeMaxSlots + 1];
   for (int b = threadIdx.x; b < nb; b += blockDim.x) t0[b] = desc[b].tile0;

@@ -26,8 +26,10 @@ constexpr double kHalf = 5e-10;
 
 enum SolidType { kBox = 0, kTubs = 1, kCons = 2, kSphere = 3, kTrd = 4, kPcon = 5, kBool = 6 };
 // What solids a geometry holds, as far as kernels are instantiated for it:
-// boxes and full tubes only, any elementary solids, or composites as well.
-enum SolidKind { kBoxTube = 0, kElementary = 1, kComposites = 2 };
+// boxes and full tubes only, any elementary solids, or composites as well; the
+// last in code whose active lanes are all in one logical volume, so that every
+// solid they evaluate is the same one.
+enum SolidKind { kBoxTube = 0, kElementary = 1, kComposites = 2, kOneComposite = 3 };
 enum BoolOp { kUnion = 0, kSubtraction = 1, kIntersection = 2 };
 enum { kOutside = 0, kSurface = 1, kInside = 2 };
 
@@ -1093,12 +1095,17 @@ __device__ __forceinline__ CQ uniform_ptr(CQ q) {
 // Out-of-line entry points of the composite code for the navigation kernels
 // (inlined there it would set their register budget for every geometry); the
 // solid-level kernels, instantiated per solid type, inline Bool directly.
-struct BoolCall {  // q is the same in every active lane
-  __device__ __noinline__ static double sgn(CQ q, V3 p) { return Bool::sgn(uniform_ptr(q), p); }
-  __device__ __noinline__ static double safety_in(CQ q, V3 p) { return Bool::safety_in(uniform_ptr(q), p); }
-  __device__ __noinline__ static double safety_out(CQ q, V3 p) { return Bool::safety_out(uniform_ptr(q), p); }
-  __device__ __noinline__ static double dist_in(CQ q, V3 p, V3 d) { return Bool::dist_in(uniform_ptr(q), p, d); }
-  __device__ __noinline__ static double dist_out(CQ q, V3 p, V3 d) { return Bool::dist_out(uniform_ptr(q), p, d); }
+// ONE: q is the same in every active lane, so the composite's table comes as
+// scalar loads and the switches over operation and part types are one branch
+// (262,144 safeties in the composite geometry 32 us, 42 through per-lane tables).
+template <bool ONE>
+struct BoolCall {
+  __device__ static __forceinline__ CQ of(CQ q) { return ONE ? uniform_ptr(q) : q; }
+  __device__ __noinline__ static double sgn(CQ q, V3 p) { return Bool::sgn(of(q), p); }
+  __device__ __noinline__ static double safety_in(CQ q, V3 p) { return Bool::safety_in(of(q), p); }
+  __device__ __noinline__ static double safety_out(CQ q, V3 p) { return Bool::safety_out(of(q), p); }
+  __device__ __noinline__ static double dist_in(CQ q, V3 p, V3 d) { return Bool::dist_in(of(q), p, d); }
+  __device__ __noinline__ static double dist_out(CQ q, V3 p, V3 d) { return Bool::dist_out(of(q), p, d); }
 };
 
 // Any solid of a geometry of kind K.  Kernels instantiated for a kind contain
@@ -1106,25 +1113,17 @@ struct BoolCall {  // q is the same in every active lane
 // step loops of every geometry (the mixed-type daughter loop's box test alone
 // took the detector's transport from 1.87 to 2.27 ms while it shared a kernel
 // with cones, spheres, Trds and polycones).
-// Composites run one solid at a time: the lanes whose solid is that of the first
-// active lane run it with its table as a wavefront-uniform value (scalar loads
-// of the parameters, one branch of the type switches), then the next solid's.
-// Different composites take different paths anyway, and through per-lane
-// table pointers every parameter was a gather and every branch a mask.
-template <class F>
-__device__ __forceinline__ double one_solid_at_a_time(int type, CQ q, F f) {
-  for (;;) {
-    CQ u = uniform_ptr(q);
-    if (u == q) return f(__builtin_amdgcn_readfirstlane(type), u);
-  }
-}
+// Lanes of several composites go through per-lane tables together: taking one
+// composite after another cost 262,144 safeties among 700 composites of one kind
+// 1,631 us instead of 504.
+__device__ __forceinline__ bool one_solid(CQ q) { return __ballot(uniform_ptr(q) != q) == 0; }
 #define GV_ANY_SOLID(name, args, ...)                                                       \
   template <int K>                                                                          \
   __device__ __forceinline__ double solid_##name args {                                     \
-    if constexpr (K == kComposites)                                                         \
-      return one_solid_at_a_time(type, q, [&](int t, CQ u) {                                \
-        return t == kBool ? BoolCall::name(u, __VA_ARGS__) : prim_##name(t, u, __VA_ARGS__); \
-      });                                                                                   \
+    if constexpr (K >= kComposites)                                                         \
+      if (type == kBool)                                                                    \
+        return K == kOneComposite || one_solid(q) ? BoolCall<true>::name(q, __VA_ARGS__)    \
+                                                  : BoolCall<false>::name(q, __VA_ARGS__);  \
     if constexpr (K == kBoxTube)                                                            \
       return type == kBox ? Box::name(q, __VA_ARGS__) : FullTubs::name(q, __VA_ARGS__);     \
     return prim_##name(type, q, __VA_ARGS__);                                               \
