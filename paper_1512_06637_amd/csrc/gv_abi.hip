@@ -794,11 +794,12 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
       lvr[i] = LvRec{lv_type[i], lv_par[i], lv_doff[i], lv_dcnt[i], lv_dtype[i], lv_rad[i], lv_phi[i], lv_loc[i]};
     // placed volumes are numbered in DFS pre-order, so a daughter's number
     // follows its mother's by the sizes of the subtrees placed before it
-    std::vector<DauRec> daur(n_place, DauRec{0, 0, 0, 0});
+    std::vector<int> daur(4 * (size_t)n_place, 0);  // the records of DauRec
     for (int i = 0; i < n_lv; ++i) {
       long delta = 1;
       for (int k = lv_doff[i]; k < lv_doff[i] + lv_dcnt[i]; ++k) {
-        daur[k] = DauRec{dau_lv[k], dau_par[k], dau_ident[k], (int)delta};
+        const int rec[4] = {dau_lv[k], dau_par[k], dau_ident[k] | lv_type[dau_lv[k]] << 1, (int)delta};
+        std::memcpy(&daur[4 * (size_t)k], rec, sizeof rec);
         delta += std::max(0L, subtree[dau_lv[k]]);  // -1: not reached from the world
       }
     }
@@ -820,7 +821,7 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
         {lvr.data(), lvr.size() * 32, 0},
         {par.data(), par.size() * 8, 0},
         {dau_xf.data(), dau_xf.size() * 8, 0},
-        {daur.data(), daur.size() * 16, 0},
+        {daur.data(), daur.size() * 4, 0},
         {pvr.data(), pvr.size() * 16, 0},
         {T.pv_gxf.data(), T.pv_gxf.size() * 8, 0},
         {dau_box.data(), dau_box.size() * 8, 0},

@@ -22,6 +22,7 @@ struct LvRec {
 struct DauRec {
   int lv, par;      // child volume, offset of its solid's parameters
   int ident;        // 1 when the placement is the identity (R = I, t = 0)
+  int type;         // the child's solid type; both share a word of the record
   int delta;        // placed volume of this daughter minus its mother's
 };
 struct PvRec {
@@ -74,7 +75,7 @@ __device__ __forceinline__ LvRec lv_rec(const DevGeom& G, int lv) {
 }
 __device__ __forceinline__ DauRec dau_rec(const DevGeom& G, int k) {
   const Int4 a = G.dau_rec[k];
-  return DauRec{a.x, a.y, a.z, a.w};
+  return DauRec{a.x, a.y, a.z & 1, a.z >> 1, a.w};
 }
 __device__ __forceinline__ PvRec pv_rec(const DevGeom& G, int pv) {
   const Int4 a = G.pv_rec[pv];
@@ -157,7 +158,7 @@ __device__ __forceinline__ int first_daughter(const DevGeom& G, const LvRec& v, 
   auto holds = [&](int k) {
     const DauRec d = dau_rec(G, off + k);
     const V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(off + k), pl);
-    return code_of(solid_sgn<K>(lv_rec(G, d.lv).type, G.par + d.par, pc)) != kOutside;
+    return code_of(solid_sgn<K>(d.type, G.par + d.par, pc)) != kOutside;
   };
   if (mode == kLocRadial) {
     const int r0 = v.rad;
@@ -285,7 +286,7 @@ __device__ __forceinline__ double nav_safety(const DevGeom& G, int pv, V3 p) {
     const DauRec d = dau_rec(G, v.off + k);
     V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(v.off + k), pl);
     CQ qc = G.par + d.par;
-    int tc = lv_rec(G, d.lv).type;
+    int tc = d.type;
     if (code_of(solid_sgn<K>(tc, qc, pc)) != kOutside) return 0.0;
     s = fmin(s, solid_safety_in<K>(tc, qc, pc));
   }

@@ -537,7 +537,7 @@ __device__ __forceinline__ double step_culled(const DevGeom& G, int lv, int pv, 
       CQ Y = G.dau_xf + 12 * (size_t)(off + k);
       const DauRec dr = dau_rec(G, off + k);
       V3 pc = to_child_p(Y, pl), dc = to_child_d(Y, dl);
-      const int ct = lv_rec(G, dr.lv).type;
+      const int ct = dr.type;
       double t = solid_dist_in<K>(ct, G.par + dr.par, pc, dc);
       if (ct <= kPcon) w.add(kWorkPlain + ct);  // composites have no counter
       neg = neg || t < 0.0;
@@ -655,7 +655,7 @@ __device__ __forceinline__ double nav_safety_screened(const DevGeom& G, int pv, 
     const DauRec dr = dau_rec(G, off + k);
     const V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(off + k), pl);
     CQ qc = G.par + dr.par;
-    const int tc = lv_rec(G, dr.lv).type;
+    const int tc = dr.type;
     if (code_of(solid_sgn<K>(tc, qc, pc)) != kOutside) return 0.0;
     s = fmin(s, solid_safety_in<K>(tc, qc, pc));
   }
