@@ -1050,6 +1050,15 @@ unsigned pcon_grid(int64_t n) {
 // on 2^20 and 156 against 110 on 2^22.
 constexpr int64_t kPconOutCompact = 1 << 19;
 
+// A step's tracks are regrouped by volume once every CU has this many.  Below,
+// one wavefront per workgroup with the tracks as they come is as fast or faster
+// (regrouped against as they come, detector: 4,099 tracks 38.7 and 39.2 us,
+// 32,768 41.5 and 39.9, 65,536 42.3 and 44.3; five solids of other types 22.4
+// and 16.5, 22.0 and 17.9, 22.7 and 19.3, 262,144 28.6 and 27.2; 25 boxes
+// 14.3 and 13.2, 14.9 and 13.9, 14.7 and 14.8, 262,144 17.3 and 21.7), and so
+// it is for composites at any size (262,144 tracks 159 and 148 us).
+int step_alone(int kind) { return kind == kBoxTube ? 128 : 256; }
+
 // With GV_PROF_WORK, a polycone query is followed by the kernel that counts
 // its walk's work (profiling only; the query's outputs are untouched).
 int pcon_work(gv_geom* g, int32_t lv, int dir, int64_t n, const double* x, const double* y, const double* z,
@@ -1210,8 +1219,10 @@ extern "C" int basket_step(gv_geom* g, int64_t n, const double* x, const double*
   GV_TRY(check_i32(fn, "out_next_pv", out_next_pv));
   GV_TRY(check_i32(fn, "out_flags", out_flags, true));
   DeviceGuard dgd(g->device);
-  hipLaunchKernelGGL(step_nav_kernel(g->kind, precision == GV_FP32_REFINE), dim3((unsigned)((n + kStepTile - 1) / kStepTile)),
-                     dim3(kStepTile), 0, (hipStream_t)stream, g->dg, n, x, y, z, dx, dy, dz, pv, pstep, out_step,
+  const bool group = g->kind != kComposites && n > (int64_t)step_alone(g->kind) * g->n_cu;
+  const int64_t tile = group ? kStepTile : kWave;
+  hipLaunchKernelGGL(step_nav_kernel(g->kind, precision == GV_FP32_REFINE, group), dim3((unsigned)((n + tile - 1) / tile)),
+                     dim3((unsigned)tile), 0, (hipStream_t)stream, g->dg, n, x, y, z, dx, dy, dz, pv, pstep, out_step,
                      out_next_pv, out_flags);
   return launched(fn);
 }

@@ -23,8 +23,6 @@
 
 namespace gv {
 
-constexpr int kWave = 64;
-
 // One 64-byte record per track (one cache line), read and rewritten whole
 // every step.
 struct alignas(64) TRec {

@@ -32,6 +32,7 @@ struct PvRec {
 
 // All arrays live in HBM; geom_load fills them once.  Transforms are 12
 // doubles: R row-major then t, with x_mother = R x_child + t.
+constexpr int kWave = 64;
 constexpr int kPhiSectors = 256, kPhiLevels = 8;
 constexpr int kLvSlots = 1024;  // slots of the LVs in the regrouped kernels
 constexpr int kOwnClass = 128;  // an LV that is a composite or holds one has a step class of its own from here on (the world this one)

@@ -38,8 +38,8 @@ LaneKernel lane_kernel_phys64(int waves, bool stage, bool cls);
 LaneKernel lane_kernel_phys32(int waves, bool stage, bool cls);
 LaneKernel lane_kernel_composites(bool fp32, bool phys);
 
-// ComputeStep of a basket, and the serving round.
-StepNavKernel step_nav_kernel(int kind, bool fp32);
+// ComputeStep of a basket (group: regrouped by volume), and the serving round.
+StepNavKernel step_nav_kernel(int kind, bool fp32, bool group);
 ServeKernel serve_kernel(int kind);
 
 // The launch shapes of one precision and kind of transport (elementary solids).

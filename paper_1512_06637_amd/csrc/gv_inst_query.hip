@@ -3,10 +3,15 @@
 
 namespace gv {
 
-StepNavKernel step_nav_kernel(int kind, bool fp32) {
-  if (kind == kBoxTube) return fp32 ? k_step_nav<true, kBoxTube> : k_step_nav<false, kBoxTube>;
-  if (kind == kElementary) return fp32 ? k_step_nav<true, kElementary> : k_step_nav<false, kElementary>;
-  return fp32 ? k_step_nav<true, kComposites> : k_step_nav<false, kComposites>;
+template <bool F32>
+static StepNavKernel step_nav_kernel_for(int kind, bool group) {
+  if (kind == kBoxTube) return group ? k_step_nav<F32, kBoxTube, true> : k_step_nav<F32, kBoxTube, false>;
+  if (kind == kElementary) return group ? k_step_nav<F32, kElementary, true> : k_step_nav<F32, kElementary, false>;
+  return k_step_nav<F32, kComposites, false>;
+}
+
+StepNavKernel step_nav_kernel(int kind, bool fp32, bool group) {
+  return fp32 ? step_nav_kernel_for<true>(kind, group) : step_nav_kernel_for<false>(kind, group);
 }
 
 ServeKernel serve_kernel(int kind) {

@@ -663,7 +663,7 @@ __device__ __forceinline__ double nav_safety_screened(const DevGeom& G, int pv, 
 }
 
 // ----------------------------------------------------- regrouped step kernels
-// A basket's tracks sit in any volume.  Taken 64 at a time as they come, a
+// A large basket's tracks sit in any volume.  Taken 64 at a time as they come, a
 // wavefront runs the step code of the world, of the layers and of the modules one
 // after another with 18 % of its lanes active.  So a workgroup takes a tile of
 // tracks and its wavefronts take them ordered by their volumes' slots (LVs in
@@ -739,21 +739,29 @@ __device__ __forceinline__ double step_query(const DevGeom& G, int v, V3 p, V3 d
   return step_culled_limited<F32, K>(G, lv, v, p, d, ps, next, flags, w);
 }
 
-// ComputeStep for every track of a basket, a tile per workgroup.  Composites at
-// 2 waves per SIMD: 262,144 steps through the composite geometry 180 us at 2 and
-// at 4 (524 bytes of scratch), 284 us at 1, which the compiler takes when it may.
-template <bool F32, int K>
-__global__ void __launch_bounds__(kStepTile) __attribute__((amdgpu_waves_per_eu(K == kComposites ? 2 : 1)))
+// ComputeStep for every track of a basket: a regrouped tile per workgroup
+// (GROUP), or one wavefront per workgroup with the tracks as they come.
+// Composites at 2 waves per SIMD: 262,144 steps through the composite geometry
+// 180 us at 2 and at 4 (524 bytes of scratch), 284 us at 1, which the compiler
+// takes when it may.
+template <bool F32, int K, bool GROUP>
+__global__ void __launch_bounds__(GROUP ? kStepTile : kWave) __attribute__((amdgpu_waves_per_eu(K == kComposites ? 2 : 1)))
 k_step_nav(DevGeom G, int64_t n, const double* __restrict__ x, const double* __restrict__ y,
            const double* __restrict__ z, const double* __restrict__ dx, const double* __restrict__ dy,
            const double* __restrict__ dz, const int32_t* __restrict__ pv, const double* __restrict__ pstep,
            double* __restrict__ out_step, int32_t* __restrict__ out_next, uint32_t* __restrict__ out_flags) {
-  __shared__ StepGroup S;
-  const int64_t base = (int64_t)blockIdx.x * kStepTile;
-  const int m = (int)min((int64_t)kStepTile, n - base);
-  step_regroup(G, pv + base, m, S);
-  if ((int)threadIdx.x >= m) return;
-  const int64_t i = base + S.list[threadIdx.x];
+  int64_t i;
+  if constexpr (GROUP) {
+    __shared__ StepGroup S;
+    const int64_t base = (int64_t)blockIdx.x * kStepTile;
+    const int m = (int)min((int64_t)kStepTile, n - base);
+    step_regroup(G, pv + base, m, S);
+    if ((int)threadIdx.x >= m) return;
+    i = base + S.list[threadIdx.x];
+  } else {
+    i = (int64_t)blockIdx.x * kWave + threadIdx.x;
+    if (i >= n) return;
+  }
   int nx;
   uint32_t fl;
   out_step[i] = step_query<F32, K>(G, pv[i], ld3(x, y, z, i), ld3(dx, dy, dz, i), pstep ? pstep[i] : GV_INF, &nx, &fl);
