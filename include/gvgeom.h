@@ -314,7 +314,8 @@ int gv_probe_fma64(double* out, int64_t n_lanes, int32_t iters, void* stream);
  *   sort_key      1 octahedral cells in Morton order, 2 z-axis cells (cos
  *                 theta bands x azimuth sectors, bands outermost) (default 1);
  *   lane_waves    3 or 4: waves per SIMD the lane kernel is built for
- *                 (default 4; 3 for physics-limited transport);
+ *                 (default 4 for navigation of boxes and full tubes, else 3;
+ *                 geometries with composites always 2);
  *   lane_stage    1 off, 2 on: the lane kernel stages 8 steps of outputs in
  *                 LDS before writing a track's rows (default on);
  *   lane_grid     workgroups (256 threads) of the persistent lane kernel,

@@ -1567,11 +1567,13 @@ int lane_transport(gv_geom* g, const LaneCtl& L, int64_t n, const double* x, con
                        chunk, cells, L);
     GV_TRY(launched(fn));
   }
-  // defaults: staged outputs; 4 waves per SIMD for navigation, 3 for
+  // defaults: staged outputs; 4 waves per SIMD for navigation of boxes and full
+  // tubes (2^20 detector tracks 1.31 ms at 4 against 1.50 at 3), 3 where other
+  // solids' code spills at 4 (48 registers; 262,144 tracks of the detector with
+  // a cone in one kind of module 1.12 ms at 4 against 0.74 at 3) and for
   // physics-limited steps (more live state per lane: 400,003 detector tracks
-  // 2.04 ms at 3 against 3.44 at 4; navigation of 2^20 tracks 1.31 ms at 4
-  // against 1.50 at 3)
-  const int waves = g->tune.lane_waves ? g->tune.lane_waves : (phys ? 3 : 4);
+  // 2.04 ms at 3 against 3.44 at 4)
+  const int waves = g->tune.lane_waves ? g->tune.lane_waves : (phys || g->kind != kBoxTube ? 3 : 4);
   const bool stage = g->tune.lane_stage ? g->tune.lane_stage == 2 : true;
   // per-class scheduling by default (2^20 detector tracks 1.31 against 2.21 ms
   // for navigation, 400,003 physics-limited 2.04 against 2.48 ms)

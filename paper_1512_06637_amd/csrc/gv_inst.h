@@ -27,10 +27,10 @@ StepKernel step_kernel_phys(int kind, bool work, bool fp32);
 
 // The lane-transport instance: the geometry's solids, FP32 screens or not,
 // physics-limited or not, the register budget (3 or 4 waves per SIMD), output
-// staging and per-class scheduling.  Boxes and full tubes have instances of their
-// own for the default shapes (staged, per-class scheduling, 4 waves for
-// navigation and 3 for physics) and share the elementary solids' otherwise;
-// geometries with composites run one shape per precision and physics.
+// staging and per-class scheduling (which always stages).  Boxes and full tubes
+// have instances of their own for the default shapes (per-class scheduling, 4
+// waves for navigation and 3 for physics) and share the elementary solids'
+// otherwise; geometries with composites run one shape per precision and physics.
 LaneKernel lane_kernel(int kind, bool fp32, bool phys, int waves, bool stage, bool cls);
 LaneKernel lane_kernel_nav64(int waves, bool stage, bool cls);
 LaneKernel lane_kernel_nav32(int waves, bool stage, bool cls);

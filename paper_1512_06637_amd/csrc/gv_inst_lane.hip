@@ -5,7 +5,7 @@ namespace gv {
 
 LaneKernel lane_kernel(int kind, bool fp32, bool phys, int waves, bool stage, bool cls) {
   if (kind == kComposites) return lane_kernel_composites(fp32, phys);
-  if (kind == kBoxTube && stage && cls && waves == (phys ? 3 : 4)) {
+  if (kind == kBoxTube && cls && waves == (phys ? 3 : 4)) {
     if (phys) return fp32 ? k_lane_transport<true, true, kBoxTube, 3, 8, true> : k_lane_transport<false, true, kBoxTube, 3, 8, true>;
     return fp32 ? k_lane_transport<true, false, kBoxTube, 4, 8, true> : k_lane_transport<false, false, kBoxTube, 4, 8, true>;
   }
