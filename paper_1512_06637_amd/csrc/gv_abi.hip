@@ -437,7 +437,9 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
       for (int j = 0; j < 12; ++j) dau_xf[12 * (size_t)k + j] = rd_f64(b, o + 8 + 8 * (size_t)j);
     }
     // the tables below keep what depends on the mother with each placement:
-    // volumes that share placements get copies of their own
+    // volumes that share placements get copies of their own, those of them that
+    // are in the world's tree (as many placements as it has placed volumes at
+    // most; the others' daughters are never reached)
     std::vector<int> owner(n_place, -1);
     bool shared = false;
     for (int i = 0; i < n_lv; ++i)
@@ -446,14 +448,28 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
         owner[k] = i;
       }
     if (shared) {
+      std::vector<char> reached(n_lv, 0);
+      std::vector<int> todo(1, world);
+      reached[world] = 1;
+      while (!todo.empty()) {
+        const int i = todo.back();
+        todo.pop_back();
+        for (int k = lv_doff[i]; k < lv_doff[i] + lv_dcnt[i]; ++k)
+          if (!reached[dau_lv[k]]) {
+            reached[dau_lv[k]] = 1;
+            todo.push_back(dau_lv[k]);
+          }
+      }
       std::vector<int> lv2;
       std::vector<double> xf2;
       for (int i = 0; i < n_lv; ++i) {
         const int o = lv_doff[i];
         lv_doff[i] = (int)lv2.size();
+        if (!reached[i]) lv_dcnt[i] = 0;
+        if (lv2.size() + (size_t)lv_dcnt[i] > (size_t)kMaxPv)
+          return fail(GV_EFORMAT, "geom_load: volume tree has a cycle or is too large/deep");
         lv2.insert(lv2.end(), dau_lv.begin() + o, dau_lv.begin() + o + lv_dcnt[i]);
         xf2.insert(xf2.end(), dau_xf.begin() + 12 * (size_t)o, dau_xf.begin() + 12 * (size_t)(o + lv_dcnt[i]));
-        if (lv2.size() > (size_t)kMaxPv) return fail(GV_EFORMAT, "geom_load: too many placements");
       }
       dau_lv.swap(lv2);
       dau_xf.swap(xf2);
