@@ -8,7 +8,9 @@ world, recording every track's volume sequence and step lengths.  Inputs are
 resident in HBM before timing starts.
 
 Metric: track-steps/s = (track-steps the batch takes) / (device time per call).
-Prints one JSON line.
+Prints one JSON line on stdout: the metric, its roofline and baseline, and the
+main figures of the other legs (at most LINE_MAX characters, so that a log's tail
+holds it whole).  The full record goes to stderr as one JSON line.
 """
 import argparse
 import json
@@ -19,6 +21,54 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
+
+
+LINE_MAX = 6000
+
+
+def rounded(v):
+    """Floats to six significant digits."""
+    if isinstance(v, float):
+        return float(f"{v:.6g}")
+    if isinstance(v, dict):
+        return {k: rounded(x) for k, x in v.items()}
+    return [rounded(x) for x in v] if isinstance(v, (list, tuple)) else v
+
+
+def summary(res):
+    """The record's line for stdout: what identifies and judges the metric whole
+    (times in full precision), one figure or two per query of the other legs."""
+    legs = ("roofline", "roofs", "work", "fp32_refine", "physics_limited", "serving", "solids", "protocol",
+            "cpu_baseline_solids", "composites")
+    out = {k: v for k, v in res.items() if k not in legs}
+    keep = {"roofline": ("bound", "kernel", "achieved", "peak", "unit", "frac", "traffic", "ops_per_launch",
+                         "launches_per_transport", "avg_launch_ms", "kernel_ms_per_transport",
+                         "algorithmic_bytes_per_transport", "frac_measured_fp64_roof"),
+            "fp32_refine": ("ms_per_step", "identical_to_fp64", "fp32_screened_frac")}
+    for leg, ks in keep.items():
+        if leg in res:
+            out[leg] = {k: res[leg][k] for k in ks if k in res[leg]}
+    if res.get("roofs"):
+        out["roofs"] = {k: v for k, v in res["roofs"].items() if isinstance(v, float)}
+    if "physics_limited" in res:
+        out["physics_limited"] = {k: {q: v[q] for q in ("ms_per_step", "track_steps_per_s")}
+                                  for k, v in res["physics_limited"].items()}
+    if "serving" in res:
+        out["serving"] = {p["precision"]: {"baskets_per_s": p["saturation"]["baskets_per_s"],
+                                           "load_p50_p99_ms": [[x["load"], x["p50_ms"], x["p99_ms"]] for x in p["loads"]]}
+                          for p in res["serving"]["points"]}
+    if "solids" in res:
+        out["solids_us"] = {n: {q: v["us_per_call"] for q, v in r.items() if isinstance(v, dict) and "us_per_call" in v}
+                            for n, r in res["solids"].items()}
+    if "protocol" in res:
+        out["protocol_us"] = {n: [[x["n"], x["us_per_call"]] for x in r] for n, r in res["protocol"].items()}
+    if "composites" in res:
+        c = res["composites"]
+        out["composites"] = {"fused_us": {n: v["fused_us_per_call"] for n, v in c["solids"].items()},
+                             "transport_ms": c["transport"]["ms_per_call"],
+                             "transport_track_steps_per_s": c["transport"]["track_steps_per_s"]}
+    exact = {k: out[k] for k in ("value", "ms_per_step") if k in out}
+    return {**rounded(out), **exact}
 
 
 def cpu_baseline(blob, tracks, target_s=12.0, max_s=30.0):
@@ -652,7 +702,8 @@ def main():
             res["cpu_baseline_solids"] = cpu_baseline_solids(res["protocol"])
     if not args.no_composites:
         res["composites"] = composites_leg(args)
-    print(json.dumps(res), flush=True)
+    print(json.dumps(res), file=sys.stderr, flush=True)
+    print(json.dumps(summary(res)), flush=True)
 
 
 if __name__ == "__main__":
