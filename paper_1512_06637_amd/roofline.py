@@ -15,8 +15,15 @@ PEAK_HBM = 8.0e12  # B/s
 TRANSFORM = 21      # p_loc = R^T (p - t): 3 sub + 9 mul/fma; d_loc = R^T d: 9
 BOX_DIST_IN = 33    # inside test 6, three slabs 24, clip + chord test 3
 BOX_DIST_OUT = 16   # inside test 6, three exit planes 9, clamp 1
-TUBE_DIST_IN = 53   # inside test 9, outer cylinder 16, z slab 6, inner cylinder 12, pieces 10
-TUBE_DIST_OUT = 53
+# Full tubes in closed form, for a ray moving away from the axis: A, B, rho^2 (9),
+# two cylinder constants and |z| - dz (3), side tests (4), z slab (6), its clip
+# (2), the branch (3), the outer root (6); from the bore also the inner root (7);
+# the piece (3).
+TUBE_DIST_IN = 43
+TUBE_DIST_OUT = 36
+# tube segments through the interval algebra: inside test 9, outer cylinder 16, z
+# slab 6, inner cylinder 12, pieces 10
+TUBE_SEGMENT = 53
 SELECT = 1          # running minimum over candidates, per candidate
 STEP_FIXED = 9      # final selection (3) + advance p += s d (6)
 
@@ -74,17 +81,19 @@ DIST_OUT = {"world": BOX_DIST_OUT, "layer": TUBE_DIST_OUT, "module": BOX_DIST_OU
 
 
 # Radial walk (an LV whose daughters are concentric tubes, the detector's
-# world): per step rho^2, A, B (9), the count of tubes with rmin^2 <= rho^2
-# over the world's 20 tubes (2 each), the holding test (1) and the test that
-# the ray leaves a held tube at once (4); per crossing bound C, the
-# discriminant, a square root, the stable root and the margin test (12).
-RADIAL_LOOKUP = 9 + 2 * 20 + 1 + 4
+# world): per step rho^2, A, B (9), the count of tubes with rmin^2 <= rho^2 (one
+# compare per four tubes passed, then a compare and an add each: 8 on average
+# over the ranks of the world's 20 tubes), the holding test (1) and the test that
+# the ray leaves a held tube at once (4); per crossing bound (none for the first
+# tube outward) C, the discriminant, a square root, the stable root and the
+# margin test (12).
+RADIAL_LOOKUP = 9 + 8 + 1 + 4
 RADIAL_BOUND = 12
-# Phi sectors (the detector's layers): per step the segment end (4), the
-# closest approach to the axis (13), its guard (7), two pseudo-angles (8 each,
-# with a division), the turning sense (3) and two sector indices (4); per
-# sector read one OR and one compare.
-PHI_LOOKUP = 4 + 13 + 7 + 16 + 3 + 4
+# Phi sectors (the detector's layers): per step the segment end (4), A, B and the
+# point nearest the axis (10; without a division for a ray moving outward), its
+# guard (7), two pseudo-angles in FP32 (5 each), the turning sense (3) and two
+# sector indices (4); per mask read (two a lookup, of ranges) one OR and its index.
+PHI_LOOKUP = 4 + 10 + 7 + 10 + 3 + 4
 PHI_SECTOR = 2
 
 
@@ -118,7 +127,7 @@ def detector_ops_culled(world, layer, module, work) -> float:
 # meridian safety).  Fused = all four answers from one read of the track.
 SOLID_OPS = {
     "box": {"inside": 7, "safety": 7, "dist_in": BOX_DIST_IN, "dist_out": BOX_DIST_OUT},
-    "tubs": {"inside": 16, "safety": 22, "dist_in": TUBE_DIST_IN, "dist_out": TUBE_DIST_OUT},
+    "tubs": {"inside": 16, "safety": 22, "dist_in": TUBE_SEGMENT, "dist_out": TUBE_SEGMENT},
     "cons": {"inside": 14, "safety": 14, "dist_in": 60, "dist_out": 45},
     "sphere": {"inside": 6, "safety": 7, "dist_in": 25, "dist_out": 20},
     "trd": {"inside": 12, "safety": 12, "dist_in": 45, "dist_out": 20},
