@@ -150,9 +150,11 @@ __device__ __forceinline__ int radial_rank(CQ R2, int cnt, double rho2) {
 // the point's sector.  Boxes: the daughters whose padded box holds the point.
 // The plain loop made a point in the detector evaluate up to 84 daughters (128
 // us per 300,007 points spread over it), the indexes two or three (13 us, most
-// of it the call).
+// of it the call).  few: so few points that the chip is not full, where the boxes
+// in front of eight or more box or tube daughters cost a load each that the points
+// wait for and save nothing (kLocateFew).
 template <int K>
-__device__ __forceinline__ int first_daughter(const DevGeom& G, const LvRec& v, V3 pl) {
+__device__ __forceinline__ int first_daughter(const DevGeom& G, const LvRec& v, V3 pl, bool few) {
   const int off = v.off, cnt = v.cnt;
   if (cnt == 0) return -1;
   const int mode = loc_mode(v, pl);
@@ -188,8 +190,9 @@ __device__ __forceinline__ int first_daughter(const DevGeom& G, const LvRec& v, 
     }
     return -1;
   }
+  const bool boxes = mode == kLocBox && !(few && cnt >= 8 && (v.dtype == kBox || v.dtype == kTubs));
   for (int k = 0; k < cnt; ++k) {
-    if (mode == kLocBox) {
+    if (boxes) {
       CQ X = G.dau_box + 6 * (size_t)(off + k);
       if (pl.x < X[0] || pl.y < X[1] || pl.z < X[2] || pl.x > X[3] || pl.y > X[4] || pl.z > X[5]) continue;
     }
@@ -199,13 +202,13 @@ __device__ __forceinline__ int first_daughter(const DevGeom& G, const LvRec& v, 
 }
 
 template <int K>
-__device__ __forceinline__ int locate(const DevGeom& G, V3 p) {
+__device__ __forceinline__ int locate(const DevGeom& G, V3 p, bool few = false) {
   LvRec v = lv_rec(G, pv_rec(G, 0).lv);
   if (code_of(solid_sgn<K>(v.type, G.par + v.par, p)) == kOutside) return -1;
   int pv = 0;
   V3 pl = p;
   for (;;) {
-    const int k = first_daughter<K>(G, v, pl);
+    const int k = first_daughter<K>(G, v, pl, few);
     if (k < 0) return pv;
     const DauRec d = dau_rec(G, v.off + k);
     pl = to_child_p(G.dau_xf + 12 * (size_t)(v.off + k), pl);
