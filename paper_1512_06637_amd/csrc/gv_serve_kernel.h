@@ -28,7 +28,8 @@ __host__ __device__ inline int64_t serve_out_bytes(int kind, int64_t n) {
 
 // Fused mixed-query kernel: one wavefront answers one tile of 64 tracks of one
 // basket, so the query kind and precision are wavefront-uniform; a basket's
-// tracks may sit in different volumes (per-lane navigation state).
+// tracks may sit in different volumes (per-lane navigation state).  Composites at
+// 2 waves per SIMD, as the single steps (the compiler's choice was 1).
 template <int K>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(K == kComposites ? 2 : 1))) k_serve(DevGeom G, const SDesc* __restrict__ desc, int nb, int64_t ntiles,
                                                const char* __restrict__ din, char* __restrict__ dout) {
