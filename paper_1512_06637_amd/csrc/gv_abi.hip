@@ -805,9 +805,16 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
       open(dau_lv[pl], parent, g);
     }
 
-    std::vector<LvRec> lvr(n_lv);
-    for (int i = 0; i < n_lv; ++i)
-      lvr[i] = LvRec{lv_type[i], lv_par[i], lv_doff[i], lv_dcnt[i], lv_dtype[i], lv_rad[i], lv_phi[i], lv_loc[i]};
+    auto box_or_tube = [&](int i) { return lv_type[i] == kBox || (lv_type[i] == kTubs && par[lv_par[i] + L::TB_PHI] == 0.0); };
+    std::vector<int> lvr;  // the records of LvRec
+    for (int i = 0; i < n_lv; ++i) {
+      bool bt = box_or_tube(i);
+      for (int k = lv_doff[i]; k < lv_doff[i] + lv_dcnt[i]; ++k) bt = bt && box_or_tube(dau_lv[k]);
+      const int rec[8] = {lv_type[i],  lv_par[i], lv_doff[i], lv_dcnt[i],
+                          lv_dtype[i], lv_rad[i], lv_phi[i],  lv_loc[i] | (bt ? 4 : 0)};
+      lvr.insert(lvr.end(), rec, rec + 8);
+    }
+    static_assert(kLocBox <= 3, "kLoc* take two bits of the record");
     // placed volumes are numbered in DFS pre-order, so a daughter's number
     // follows its mother's by the sizes of the subtrees placed before it
     std::vector<int> daur(4 * (size_t)n_place, 0);  // the records of DauRec
@@ -834,7 +841,7 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
       size_t off;
     };
     std::vector<Part> parts = {
-        {lvr.data(), lvr.size() * 32, 0},
+        {lvr.data(), lvr.size() * 4, 0},
         {par.data(), par.size() * 8, 0},
         {dau_xf.data(), dau_xf.size() * 8, 0},
         {daur.data(), daur.size() * 4, 0},
@@ -920,7 +927,7 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
     g->kind = g->has_bool ? kComposites
                              : kBoxTube;
     for (int i = 0; i < n_lv && g->kind == kBoxTube; ++i)
-      if (!(lv_type[i] == kBox || (lv_type[i] == kTubs && par[lv_par[i] + L::TB_PHI] == 0.0))) g->kind = kElementary;
+      if (!box_or_tube(i)) g->kind = kElementary;
     g->lv_par = lv_par;
     *out = g;
     t_err.clear();

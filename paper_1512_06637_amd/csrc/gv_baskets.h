@@ -515,6 +515,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WV))) 
       if (PHYS) {
         st = step_physics<F32, S>(G, b, r.pv, p, d, (uint32_t)id, k, P, r.safe, &nx, &proc, &fl, w,
                                   zfc_left(r.zfc), &exited);
+      } else if (K == kElementary && !WK && lv_rec(G, b).boxtube) {
+        // boxes and tubes apart: their steps do not pay for the registers that
+        // the other solids' code spills
+        st = step_culled<F32, kBoxTube>(G, b, r.pv, p, d, &nx, &fl, w, zfc_left(r.zfc), &exited);
+        p = advance(p, st, d);
       } else {
         st = step_culled<F32, S>(G, b, r.pv, p, d, &nx, &fl, w, zfc_left(r.zfc), &exited);
         p = advance(p, st, d);

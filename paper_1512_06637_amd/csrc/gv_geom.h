@@ -18,6 +18,7 @@ struct LvRec {
   int dtype;        // solid type shared by all daughters, -1 if mixed or none
   int rad, phi;     // first entry of its radial list / first phi mask, -1 without
   int loc;          // how point lookups reach the daughters (kLoc*)
+  int boxtube;      // 1 when it and its daughters are boxes and full tubes; both share a word of the record
 };
 struct DauRec {
   int lv, par;      // child volume, offset of its solid's parameters
@@ -72,7 +73,7 @@ struct DevGeom {
 
 __device__ __forceinline__ LvRec lv_rec(const DevGeom& G, int lv) {
   const Int4 a = G.lv_rec[2 * (size_t)lv], b = G.lv_rec[2 * (size_t)lv + 1];
-  return LvRec{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  return LvRec{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w & 3, b.w >> 2};
 }
 __device__ __forceinline__ DauRec dau_rec(const DevGeom& G, int k) {
   const Int4 a = G.dau_rec[k];
