@@ -706,16 +706,31 @@ struct Pcon {
     v.inner = v.ci + (nz - 1);
     return v;
   }
-  // Not built on Sections: with a base the registers of the composites' fused
-  // query fall out otherwise, 44 of them spilled instead of 36 (a polycone minus
-  // a cone, 2^20 tracks: 365 against 345 us).
-  struct View {
-    int nz;
-    CQ z, rmin, rmax, bo, co, bi, ci, inner, ilo, ili, icap;
+  struct View : Sections<CQ> {
+    CQ ilo, ili, icap;
     double rbound;
   };
   __device__ static __forceinline__ View view(CQ q) {
     View v;
+    static_cast<Sections<CQ>&>(v) = sections<CQ>((int)q[0], q + 1);
+    v.ilo = v.inner + (v.nz - 1);
+    v.ili = v.ilo + (v.nz - 1);
+    v.icap = v.ili + (v.nz - 1);
+    v.rbound = v.icap[2];
+    return v;
+  }
+  // The same as one plain struct, for the composites' parts: with a base the
+  // registers of their fused query fall out otherwise, 44 of them spilled
+  // instead of 36 (a polycone minus a cone, 2^20 tracks: 365 against 345 us),
+  // while elsewhere the plain struct is the worse one (5,000 safeties among 56
+  // polycones 141 against 130 us).
+  struct PartView {
+    int nz;
+    CQ z, rmin, rmax, bo, co, bi, ci, inner, ilo, ili, icap;
+    double rbound;
+  };
+  __device__ static __forceinline__ PartView part_view(CQ q) {
+    PartView v;
     v.nz = (int)q[0];
     v.z = q + 1;
     v.rmin = v.z + v.nz;
@@ -730,6 +745,11 @@ struct Pcon {
     v.icap = v.ili + (v.nz - 1);
     v.rbound = v.icap[2];
     return v;
+  }
+  template <bool PART>
+  __device__ static __forceinline__ auto view_of(CQ q) {
+    if constexpr (PART) return part_view(q);
+    else return view(q);
   }
   // largest j with z_j <= z, clamped to [0, nz-2]
   template <class V>
@@ -876,22 +896,24 @@ struct Pcon {
   // The ray's interval inside the bounding cylinder (padded by 1e-6 mm, far
   // above the rounding of either test) within the z range: every piece of the
   // solid along the ray lies in it.
-  __device__ static __forceinline__ Iv bound_iv(const View& v, V3 p, V3 d) {
+  template <class V>
+  __device__ static __forceinline__ Iv bound_iv(const V& v, V3 p, V3 d) {
     const double rb = v.rbound + 1e-6;
     return iv_and(cyl_interior(rb * rb, p, d), zrange(p.z, d.z, v.z[0] - 1e-6, v.z[v.nz - 1] + 1e-6));
   }
   __device__ static __forceinline__ bool misses(Iv B) { return !(B.hi >= fmax(B.lo, 0.0)); }
-  template <bool PASS = true>
+  // PART: as a part of a composite
+  template <bool PASS = true, bool PART = false>
   __device__ static __forceinline__ double dist_in(CQ q, V3 p, V3 d) {
-    if (sgn(q, p) < -kHalf) return -1.0;
-    const Iv B = bound_iv(view(q), p, d);
+    if (sgn_of(view_of<PART>(q), p) < -kHalf) return -1.0;
+    const Iv B = bound_iv(view_of<PART>(q), p, d);
     if (misses(B)) return GV_INF;
-    return walk<false, PASS>(view(q), p, d, true, nullptr, fmax(B.lo, 0.0), B.hi);
+    return walk<false, PASS>(view_of<PART>(q), p, d, true, nullptr, fmax(B.lo, 0.0), B.hi);
   }
-  template <bool PASS = true>
+  template <bool PASS = true, bool PART = false>
   __device__ static __forceinline__ double dist_out(CQ q, V3 p, V3 d) {
-    if (sgn(q, p) > kHalf) return -1.0;
-    return walk<false, PASS>(view(q), p, d, false);
+    if (sgn_of(view_of<PART>(q), p) > kHalf) return -1.0;
+    return walk<false, PASS>(view_of<PART>(q), p, d, false);
   }
 };
 
@@ -915,7 +937,7 @@ __device__ __forceinline__ double prim_dist_in(int type, CQ q, V3 p, V3 d) {
     case kCons: return Cons::dist_in(q, p, d);
     case kSphere: return Sphere::dist_in(q, p, d);
     case kTrd: return Trd::dist_in(q, p, d);
-    default: return Pcon::dist_in<false>(q, p, d);
+    default: return Pcon::dist_in<false, !FULL>(q, p, d);
   }
 }
 template <bool FULL = true>
@@ -926,7 +948,7 @@ __device__ __forceinline__ double prim_dist_out(int type, CQ q, V3 p, V3 d) {
     case kCons: return Cons::dist_out(q, p, d);
     case kSphere: return Sphere::dist_out(q, p, d);
     case kTrd: return Trd::dist_out(q, p, d);
-    default: return Pcon::dist_out<false>(q, p, d);
+    default: return Pcon::dist_out<false, !FULL>(q, p, d);
   }
 }
 __device__ __forceinline__ double prim_safety_in(int type, CQ q, V3 p) {
