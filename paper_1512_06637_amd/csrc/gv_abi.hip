@@ -1073,12 +1073,6 @@ unsigned pcon_grid(int64_t n) {
 // on 2^20 and 156 against 110 on 2^22.
 constexpr int64_t kPconOutCompact = 1 << 19;
 
-// Points per CU up to which a point lookup goes to box and tube daughters without
-// their padded boxes first (without and with them, 25 boxes: 4,099 points 13.3 and
-// 16.2 us, 65,536 16.1 and 17.7, 131,072 21.9 and 19.8, 262,144 35.7 and 25.4; 10
-// boxes with 70 composites in each 49.4 and 53.9, 50.1 and 54.1, 55.0 and 60.1).
-constexpr int kLocateFew = 256;
-
 // A step's tracks are regrouped by volume once every CU has this many.  Below,
 // one wavefront per workgroup with the tracks as they come is as fast or faster
 // (regrouped against as they come, detector: 4,099 tracks 38.7 and 39.2 us,
@@ -1228,7 +1222,7 @@ extern "C" int basket_locate(gv_geom* g, int64_t n, const double* x, const doubl
   GV_TRY(check_i32(fn, "out_pv", out_pv));
   DeviceGuard dgd(g->device);
   hipLaunchKernelGGL(GV_KIND(k_locate, g->kind), dim3(lane_shape(g, n).grid), dim3(lane_shape(g, n).block), 0, (hipStream_t)stream, g->dg, n, x, y, z,
-                     n <= (int64_t)kLocateFew * g->n_cu ? 1 : 0, out_pv);
+                     out_pv);
   return launched(fn);
 }
 

@@ -151,11 +151,14 @@ __device__ __forceinline__ int radial_rank(CQ R2, int cnt, double rho2) {
 // the point's sector.  Boxes: the daughters whose padded box holds the point.
 // The plain loop made a point in the detector evaluate up to 84 daughters (128
 // us per 300,007 points spread over it), the indexes two or three (13 us, most
-// of it the call).  few: so few points that the chip is not full, where the boxes
-// in front of eight or more box or tube daughters cost a load each that the points
-// wait for and save nothing (kLocateFew).
+// of it the call).  With the boxes, first the mask of all that hold the point,
+// then those daughters in turn: with each box in front of its daughter a
+// wavefront waits for the box and then, as nearly every daughter has a lane in
+// its box, for the daughter's tables, one after another (23 spheres, 5,000
+// points 21.4 us, by masks 14.1, without boxes 16; 56 polycones, 300,000 points
+// 79 and 48).
 template <int K>
-__device__ __forceinline__ int first_daughter(const DevGeom& G, const LvRec& v, V3 pl, bool few) {
+__device__ __forceinline__ int first_daughter(const DevGeom& G, const LvRec& v, V3 pl) {
   const int off = v.off, cnt = v.cnt;
   if (cnt == 0) return -1;
   const int mode = loc_mode(v, pl);
@@ -191,25 +194,38 @@ __device__ __forceinline__ int first_daughter(const DevGeom& G, const LvRec& v, 
     }
     return -1;
   }
-  const bool boxes = mode == kLocBox && !(few && cnt >= 8 && (v.dtype == kBox || v.dtype == kTubs));
-  for (int k = 0; k < cnt; ++k) {
-    if (boxes) {
-      CQ X = G.dau_box + 6 * (size_t)(off + k);
-      if (pl.x < X[0] || pl.y < X[1] || pl.z < X[2] || pl.x > X[3] || pl.y > X[4] || pl.z > X[5]) continue;
+  if (mode == kLocBox) {
+    for (int c0 = 0; c0 < cnt; c0 += 64) {
+      const int m = min(cnt - c0, 64);
+      uint64_t cand = 0;
+#pragma unroll 4
+      for (int j = 0; j < m; ++j) {
+        CQ X = G.dau_box + 6 * (size_t)(off + c0 + j);
+        const bool in =
+            !(pl.x < X[0] || pl.y < X[1] || pl.z < X[2] || pl.x > X[3] || pl.y > X[4] || pl.z > X[5]);
+        cand |= (uint64_t)in << j;
+      }
+      while (cand) {
+        const int k = c0 + __builtin_ctzll(cand);
+        cand &= cand - 1;
+        if (holds(k)) return k;
+      }
     }
-    if (holds(k)) return k;
+    return -1;
   }
+  for (int k = 0; k < cnt; ++k)
+    if (holds(k)) return k;
   return -1;
 }
 
 template <int K>
-__device__ __forceinline__ int locate(const DevGeom& G, V3 p, bool few = false) {
+__device__ __forceinline__ int locate(const DevGeom& G, V3 p) {
   LvRec v = lv_rec(G, pv_rec(G, 0).lv);
   if (code_of(solid_sgn<K>(v.type, G.par + v.par, p)) == kOutside) return -1;
   int pv = 0;
   V3 pl = p;
   for (;;) {
-    const int k = first_daughter<K>(G, v, pl, few);
+    const int k = first_daughter<K>(G, v, pl);
     if (k < 0) return pv;
     const DauRec d = dau_rec(G, v.off + k);
     pl = to_child_p(G.dau_xf + 12 * (size_t)(v.off + k), pl);

@@ -294,8 +294,8 @@ static __global__ void k_pcon_work(CQ q, int dir, int64_t n, const double* __res
 // ------------------------------------------------------------- navigation
 template <int K>
 __global__ void k_locate(DevGeom G, int64_t n, const double* __restrict__ x, const double* __restrict__ y,
-                         const double* __restrict__ z, int few, int32_t* __restrict__ out) {
-  for (int64_t i = gtid(); i < n; i += gstride()) out[i] = locate<K>(G, ld3(x, y, z, i), few != 0);
+                         const double* __restrict__ z, int32_t* __restrict__ out) {
+  for (int64_t i = gtid(); i < n; i += gstride()) out[i] = locate<K>(G, ld3(x, y, z, i));
 }
 
 template <int K>

@@ -1,6 +1,6 @@
-"""Point lookups around the size up to which box and tube daughters are tested
-without their padded boxes first (256 points per CU), against the oracle: 25
-boxes, 12 tilted tubes, boxes in composites."""
+"""Point lookups around 256 points per CU, below which the chip is not full and a
+daughter's tables are waited for, against the oracle: 25 boxes, 12 tilted tubes,
+boxes in composites."""
 import numpy as np
 import pytest
 
