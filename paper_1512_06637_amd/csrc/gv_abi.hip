@@ -631,7 +631,7 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
     // type (box or tube) that each lie within less than a half turn around the
     // z axis (angular extent of the corners of the child's padded local box
     // through its placement, in the mother frame)
-    std::vector<int> lv_phi(n_lv, -1);
+    std::vector<int> lv_phi(n_lv, -1), phi_thin(n_lv, 0);
     std::vector<unsigned long long> phi_mask;
     for (int i = 0; i < n_lv; ++i) {
       const int c = lv_dcnt[i], o = lv_doff[i];
@@ -679,6 +679,9 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
         }
       }
       if (!ok) continue;
+      int held = 0;
+      for (unsigned long long w : m) held += __builtin_popcountll(w);
+      phi_thin[i] = 16 * held <= kPhiSectors * c;
       lv_phi[i] = (int)phi_mask.size();
       for (int l = 0; l < kPhiLevels; ++l) {
         phi_mask.insert(phi_mask.end(), m.begin(), m.end());
@@ -811,7 +814,7 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
       bool bt = box_or_tube(i);
       for (int k = lv_doff[i]; k < lv_doff[i] + lv_dcnt[i]; ++k) bt = bt && box_or_tube(dau_lv[k]);
       const int rec[8] = {lv_type[i],  lv_par[i], lv_doff[i], lv_dcnt[i],
-                          lv_dtype[i], lv_rad[i], lv_phi[i],  lv_loc[i] | (bt ? 4 : 0)};
+                          lv_dtype[i], lv_rad[i], lv_phi[i],  lv_loc[i] | (bt ? 4 : 0) | phi_thin[i] << 3};
       lvr.insert(lvr.end(), rec, rec + 8);
     }
     static_assert(kLocBox <= 3, "kLoc* take two bits of the record");
