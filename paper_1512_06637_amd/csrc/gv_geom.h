@@ -301,6 +301,23 @@ __device__ __forceinline__ bool safety_indexed(const DevGeom& G, const LvRec& v,
   return true;
 }
 
+// NavSafety's loop over daughters that are all boxes or all full tubes, that
+// solid's code alone: with the choice of solid inside the loop both are worked
+// out and waited for (25 boxes, 5,000 points 12.4 and 7.1 us; 300,000 points among
+// layers of modules 117 and 72).  Only for geometries of boxes and full tubes:
+// where a wavefront also has volumes that take the loop of all types, it runs
+// one loop after the other (60 and 70 us).
+template <class S>
+__device__ __forceinline__ double safety_of_type(const DevGeom& G, const LvRec& v, V3 pl, double s) {
+  for (int k = 0; k < v.cnt; ++k) {
+    CQ q = G.par + dau_rec(G, v.off + k).par;
+    const V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(v.off + k), pl);
+    if (code_of(S::sgn(q, pc)) != kOutside) return 0.0;
+    s = fmin(s, S::safety_in(q, pc));
+  }
+  return fmax(s, 0.0);
+}
+
 template <int K>
 __device__ __forceinline__ double nav_safety(const DevGeom& G, int pv, V3 p) {
   const LvRec v = lv_rec(G, pv_rec(G, pv).lv);
@@ -309,6 +326,8 @@ __device__ __forceinline__ double nav_safety(const DevGeom& G, int pv, V3 p) {
   if (code_of(solid_sgn<K>(v.type, q, pl)) != kInside) return 0.0;
   double s = solid_safety_out<K>(v.type, q, pl);
   if (safety_indexed(G, v, pl, s)) return fmax(s, 0.0);
+  if (K == kBoxTube && v.dtype == kBox) return safety_of_type<Box>(G, v, pl, s);
+  if (K == kBoxTube && v.dtype == kTubs) return safety_of_type<FullTubs>(G, v, pl, s);
   for (int k = 0; k < v.cnt; ++k) {
     const DauRec d = dau_rec(G, v.off + k);
     V3 pc = to_child_p(G.dau_xf + 12 * (size_t)(v.off + k), pl);
