@@ -681,7 +681,7 @@ extern "C" int geom_load(const void* blob, size_t nbytes, gv_geom** out) {
       if (!ok) continue;
       int held = 0;
       for (unsigned long long w : m) held += __builtin_popcountll(w);
-      phi_thin[i] = 16 * held <= kPhiSectors * c;
+      phi_thin[i] = c >= kSafetySectors && 16 * held <= kPhiSectors * c;
       lv_phi[i] = (int)phi_mask.size();
       for (int l = 0; l < kPhiLevels; ++l) {
         phi_mask.insert(phi_mask.end(), m.begin(), m.end());

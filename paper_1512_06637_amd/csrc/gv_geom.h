@@ -19,7 +19,8 @@ struct LvRec {
   int rad, phi;     // first entry of its radial list / first phi mask, -1 without
   int loc;          // how point lookups reach the daughters (kLoc*)
   int boxtube;      // 1 when it and its daughters are boxes and full tubes
-  int thin;         // 1 when each sector holds a sixteenth of its daughters or less on average; all three share a word
+  int thin;         // 1 when it has kSafetySectors daughters or more and each phi sector a sixteenth of them or less on
+                    // average; all three share a word
 };
 struct DauRec {
   int lv, par;      // child volume, offset of its solid's parameters
@@ -35,7 +36,7 @@ struct PvRec {
 // All arrays live in HBM; geom_load fills them once.  Transforms are 12
 // doubles: R row-major then t, with x_mother = R x_child + t.
 constexpr int kWave = 64;
-constexpr int kPhiSectors = 256, kPhiLevels = 8;
+constexpr int kPhiSectors = 256, kPhiLevels = 8, kSafetySectors = 20;
 constexpr int kLvSlots = 1024;  // slots of the LVs in the regrouped kernels
 constexpr int kOwnClass = 128;  // an LV that is a composite or holds one has a step class of its own from here on (the world this one)
 
@@ -249,8 +250,11 @@ __device__ __forceinline__ int locate(const DevGeom& G, V3 p) {
 // Where a sector holds more than a sixteenth of the daughters (boxes all over a
 // volume and not on a ring), the loop over all is the faster one: it takes each
 // for all lanes at once, while through the sectors each lane takes its own, one
-// after another (300,000 points in boxes with up to 33 boxes 77 and 51 us; on
-// rings of 8 to 15 boxes the loop takes 2 % more).
+// after another (300,000 points in boxes with up to 33 boxes 77 and 51 us).  The
+// same for a few daughters, kSafetySectors: with two rings of 6 and 11 boxes
+// 300,000 safeties take 28 us through the sectors and 22 in the loop, with one of
+// 18 boxes 33 and 25, among many rings of 8 to 19 boxes 97 and 104, with rings of
+// 19 and 13 in thick tubes 24 and 33.
 __device__ __forceinline__ bool safety_indexed(const DevGeom& G, const LvRec& v, V3 pl, double& s) {
   const int mode = loc_mode(v, pl);
   if (mode != kLocRadial && !(mode == kLocPhi && v.dtype == kBox && v.thin)) return false;
